@@ -9,6 +9,7 @@ import os
 import subprocess
 import sys
 import time
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -25,8 +26,13 @@ FLAGS = [
 ]
 
 UNITS = [
-    ("ffth_kernels_fft.hip", "k_fft_f32.o", ["-DFFTH_REAL=float"]),
-    ("ffth_kernels_fft.hip", "k_fft_f64.o", ["-DFFTH_REAL=double"]),
+    ("ffth_kernels_fft.hip", f"k_fft{part}_{tag}.o", [f"-DFFTH_REAL={real}", f"-DFFTH_PART={part}"])
+    for real, tag in (("float", "f32"), ("double", "f64")) for part in (1, 3, 4, 0, 2)
+] + [
+    ("ffth_kernels_group.hip", f"k_grp{part}_{tag}.o", [f"-DFFTH_REAL={real}", f"-DFFTH_PART={part}"]
+     + (["-DFFTH_GROUP_RULE"] if part == 0 and tag == "f32" else []))
+    for real, tag in (("float", "f32"), ("double", "f64")) for part in (1, 3, 4, 2, 0)
+] + [
     ("ffth_kernels_common.hip", "k_common.o", []),
     ("ffth_kernels_multi.hip", "k_multi.o", []),
     ("ffth_host.hip", "host.o", []),
@@ -37,13 +43,17 @@ UNITS = [
 def build(verbose=True):
     os.makedirs(BUILD, exist_ok=True)
     t0 = time.time()
-    procs = []
-    for src, obj, extra in UNITS:
-        cmd = [HIPCC] + FLAGS + extra + ["-c", os.path.join(CSRC, src), "-o", os.path.join(BUILD, obj)]
-        procs.append((cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    cmds = [[HIPCC] + FLAGS + extra + ["-c", os.path.join(CSRC, src), "-o", os.path.join(BUILD, obj)]
+            for src, obj, extra in UNITS]
+
+    def compile_one(cmd):
+        return cmd, subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+
     failed = False
-    for cmd, p in procs:
-        out, _ = p.communicate()
+    with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as pool:
+        done = list(pool.map(compile_one, cmds))
+    for cmd, p in done:
+        out = p.stdout
         lines = [l for l in out.splitlines() if "packed-fp32-ops" not in l and l.strip()]
         if p.returncode != 0:
             failed = True

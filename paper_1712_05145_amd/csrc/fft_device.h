@@ -119,6 +119,14 @@ template <int DIR, typename T> __device__ __forceinline__ C2<T> w16(int m) {
   return C2<T>{c[m & 15], DIR > 0 ? s : -s};
 }
 
+// exp(DIR * 2 pi i * m / 12) for m in [0, 12)
+template <int DIR, typename T> __device__ __forceinline__ C2<T> w12(int m) {
+  const T c[12] = {T(1), T(FFTH_S3), T(0.5), T(0), T(-0.5), T(-FFTH_S3), T(-1), T(-FFTH_S3), T(-0.5), T(0), T(0.5),
+                   T(FFTH_S3)};
+  const T s = c[(m + 9) % 12];  // sin(2 pi m/12) = cos(2 pi (m - 3)/12)
+  return C2<T>{c[m % 12], DIR > 0 ? s : -s};
+}
+
 template <int R, int DIR, typename T> __device__ __forceinline__ void dft(C2<T>* a) {
   if constexpr (R == 2) {
     dft2<DIR>(a[0], a[1]);
@@ -128,6 +136,17 @@ template <int R, int DIR, typename T> __device__ __forceinline__ void dft(C2<T>*
     dft4<DIR>(a[0], a[1], a[2], a[3]);
   } else if constexpr (R == 5) {
     dft5<DIR>(a[0], a[1], a[2], a[3], a[4]);
+  } else if constexpr (R == 6) {
+    // 6 = 2 x 3: X[k] = E[k mod 3] + w6^k O[k mod 3]
+    dft3<DIR>(a[0], a[2], a[4]);
+    dft3<DIR>(a[1], a[3], a[5]);
+    const C2<T> e[3] = {a[0], a[2], a[4]};
+    const C2<T> o[3] = {a[1], cmul(a[3], C2<T>{T(0.5), T(DIR * FFTH_S3)}), cmul(a[5], C2<T>{T(-0.5), T(DIR * FFTH_S3)})};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      a[k] = e[k] + o[k];
+      a[k + 3] = e[k] - o[k];
+    }
   } else if constexpr (R == 8) {
     // 8 = 2 x 4: Y_s = DFT4(a[2m+s]); X[k2 + 4 k1] = sum_s w2^{k1 s} w8^{k2 s} Y_s[k2]
     dft4<DIR>(a[0], a[2], a[4], a[6]);
@@ -138,6 +157,26 @@ template <int R, int DIR, typename T> __device__ __forceinline__ void dft(C2<T>*
     for (int k = 0; k < 4; ++k) {
       a[k] = y0[k] + y1[k];
       a[k + 4] = y0[k] - y1[k];
+    }
+  } else if constexpr (R == 12) {
+    // 12 = 3 x 4: Y_s = DFT4(a[3m+s]); X[k2 + 4 k1] = sum_s w3^{k1 s} w12^{k2 s} Y_s[k2]
+    C2<T> y[3][4];
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      C2<T> b0 = a[s], b1 = a[s + 3], b2 = a[s + 6], b3 = a[s + 9];
+      dft4<DIR>(b0, b1, b2, b3);
+      y[s][0] = b0;
+      y[s][1] = s ? cmul(b1, w12<DIR, T>(s)) : b1;
+      y[s][2] = s ? cmul(b2, w12<DIR, T>(2 * s)) : b2;
+      y[s][3] = s ? cmul(b3, w12<DIR, T>(3 * s)) : b3;
+    }
+#pragma unroll
+    for (int k2 = 0; k2 < 4; ++k2) {
+      C2<T> b0 = y[0][k2], b1 = y[1][k2], b2 = y[2][k2];
+      dft3<DIR>(b0, b1, b2);
+      a[k2] = b0;
+      a[k2 + 4] = b1;
+      a[k2 + 8] = b2;
     }
   } else if constexpr (R == 16) {
     // 16 = 4 x 4: Y_s = DFT4(a[4m+s]); twiddle w16^{k2 s}; X[k2 + 4 k1] = DFT4_s

@@ -267,6 +267,8 @@ struct ffth_plan {
   int nx64, nx32;         // forward x-pass blocks per precision
   int ni64, ni32;         // inverse x-pass blocks per precision
   int var[4][2] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};   // tile variant per pass (xf, y, z, xi) and FP32/FP64
+  GroupShape grp[2];      // grouped passes, FP32/FP64 (off: the plan runs the five classical passes)
+  bool plane = false;     // 2-D grid whose axis-1 transforms and operator are one pass
   int bw[2] = {0, 0};     // loads per launch of the iteration passes, FP32/FP64 (0: all at once)
   std::vector<Desc> h_desc;
   // kernel timing (diagnostics): events bracket every launch when enabled
@@ -281,11 +283,21 @@ struct ffth_plan {
 
 namespace {
 
+// Passes of the plan.  Grouped where the grid allows it (group_shape), in
+// each precision by itself; 2-D grids take the one-pass spectral step.  Pinned
+// tile shapes are those of the classical passes, which such a plan then runs.
+void set_passes(ffth_plan* P, bool pinned) {
+  for (int pi = 0; pi < 2; ++pi) P->grp[pi] = pinned ? GroupShape{} : group_shape(P->n, pi == 1);
+  P->plane = !pinned && P->n[0] == 1;
+}
+
 void set_blocks(ffth_plan* P) {
   P->nx32 = x_blocks(P->n[0], P->n[1], P->n[2], false, false, P->var[0][0]);
   P->nx64 = x_blocks(P->n[0], P->n[1], P->n[2], true, false, P->var[0][1]);
   P->ni32 = x_blocks(P->n[0], P->n[1], P->n[2], false, true, P->var[3][0]);
   P->ni64 = x_blocks(P->n[0], P->n[1], P->n[2], true, true, P->var[3][1]);
+  if (P->grp[0].on) P->nx32 = P->ni32 = P->grp[0].xblocks;
+  if (P->grp[1].on) P->nx64 = P->ni64 = P->grp[1].xblocks;
 }
 
 double* part_ptr(ffth_plan* P, int slot) { return (double*)(P->ws + P->L.part + (size_t)slot * P->L.part_stride); }
@@ -440,10 +452,15 @@ template <typename T> int chunk_of(ffth_plan* P, int nb) {
   return w > 0 && w < nb ? w : nb;
 }
 
+template <typename T> const GroupShape& grp(const ffth_plan* P) { return P->grp[sizeof(T) == 8 ? 1 : 0]; }
+
 template <typename T> ffth_status xfwd(ffth_plan* P, const Desc* d, int nb, int mode, bool h16 = false) {
   ProfScope ps(P, mode == XF_R3 ? (sizeof(T) == 8 ? C_CG3S_64 : C_CG3S) : sizeof(T) == 8 ? C_XF64 : C_XF32, nb);
-  HIPCHK(Launch<T>::xfwd(P->n[2], P->iso, pv<T>(P, PS_XF), h16, dim3(xblocks<T>(P), nb), P->stream, d, mode, P->rows,
-                         P->nvox));
+  if (grp<T>(P).on)
+    HIPCHK(GLaunch<T>::xfwd(P->n[2], grp<T>(P), P->iso, h16, nb, P->stream, d, mode, P->rows, P->nvox));
+  else
+    HIPCHK(Launch<T>::xfwd(P->n[2], P->iso, pv<T>(P, PS_XF), h16, dim3(xblocks<T>(P), nb), P->stream, d, mode, P->rows,
+                           P->nvox));
   return FFTH_OK;
 }
 
@@ -455,21 +472,50 @@ int kchunk_host(int h) {
   return c;
 }
 
-template <typename T> ffth_status yzy(ffth_plan* P, const Desc* d, int nb, int op, bool h16 = false) {
+// Whether the spectral step carries the finalize asked of it.
+template <typename T> bool carries_fin(const ffth_plan* P) { return grp<T>(P).on || P->plane; }
+
+ffth_status fin(ffth_plan* P, const Desc* d, int nb, int op, int nblk_f, int nblk_i) {
+  ProfScope ps(P, C_FIN, nb);
+  HIPCHK(launch_finalize(nb, P->stream, d, op, nblk_f, nblk_i));
+  return FFTH_OK;
+}
+
+// Spectral step between the x-passes: the rest of the forward transform, the
+// operator and the inverse.  fin_op >= 0: that finalize of the x-pass before
+// it as well, as a block of the pass where it carries one, else ahead of it.
+template <typename T>
+ffth_status spectral(ffth_plan* P, const Desc* d, int nb, int op, bool h16 = false, int fin_op = -1, int nblk_f = 0,
+                     int nblk_i = 0) {
+  const int cy = sizeof(T) == 8 ? C_Y64 : C_Y32, cz = sizeof(T) == 8 ? C_Z64 : C_Z32;
+  const double scale = 1.0 / (double)P->nvox;
+  ffth_status s;
+  if (grp<T>(P).on) {
+    ProfScope ps(P, cz, nb);
+    HIPCHK(GLaunch<T>::gz(P->n[0], grp<T>(P), h16, nb, P->stream, d, op, P->n[1], scale, fin_op, nblk_f, nblk_i));
+    return FFTH_OK;
+  }
   const int kc = kchunk_host(P->h);
+  const int vy = pv<T>(P, PS_Y), vz = pv<T>(P, PS_Z);
+  if (P->plane) {
+    ProfScope ps(P, cz, nb);
+    const int tk = Launch<T>::z_cols(P->n[1], vz);
+    const int nzb = (kc + tk - 1) / tk * (P->h / kc) + (fin_op >= 0 ? 1 : 0);
+    HIPCHK(Launch<T>::zpass(P->n[1], vz, h16, dim3(nzb, nb), P->stream, d, op, 1, P->h, scale, true, fin_op, nblk_f,
+                            nblk_i));
+    return FFTH_OK;
+  }
+  if (fin_op >= 0 && (s = fin(P, d, nb, fin_op, nblk_f, nblk_i)) != FFTH_OK) return s;
   const int ncols = kc * 6;
   const int nplanes = P->n[0] * (P->h / kc);
-  const int vy = pv<T>(P, PS_Y), vz = pv<T>(P, PS_Z);
   const int cw = Launch<T>::y_cols(P->n[1], vy);
   const int ntiles = (ncols + cw - 1) / cw;
-  const int cy = sizeof(T) == 8 ? C_Y64 : C_Y32, cz = sizeof(T) == 8 ? C_Z64 : C_Z32;
   {
     ProfScope ps(P, cy, nb);
     HIPCHK(Launch<T>::ypass(P->n[1], vy, h16, dim3(nplanes * ntiles, nb), P->stream, d, -1, ncols, ntiles));
   }
   const long M = (long)P->n[1] * kc;
   const int tk = Launch<T>::z_cols(P->n[0], vz);
-  const double scale = 1.0 / (double)P->nvox;
   {
     ProfScope ps(P, cz, nb);
     const int nzb = (int)((M + tk - 1) / tk) * (P->h / kc);
@@ -485,14 +531,22 @@ template <typename T> ffth_status yzy(ffth_plan* P, const Desc* d, int nb, int o
 
 template <typename T> ffth_status xinv(ffth_plan* P, const Desc* d, int nb, int mode) {
   ProfScope ps(P, sizeof(T) == 8 ? C_XI64 : C_XI32, nb);
-  HIPCHK(Launch<T>::xinv(P->n[2], P->iso, pv<T>(P, PS_XI), dim3(iblocks<T>(P), nb), P->stream, d, mode, P->rows,
-                         P->nvox));
+  if (grp<T>(P).on)
+    HIPCHK(GLaunch<T>::xinv(P->n[2], grp<T>(P), P->iso, nb, P->stream, d, mode, P->rows, P->nvox));
+  else
+    HIPCHK(Launch<T>::xinv(P->n[2], P->iso, pv<T>(P, PS_XI), dim3(iblocks<T>(P), nb), P->stream, d, mode, P->rows,
+                           P->nvox));
   return FFTH_OK;
 }
 
-ffth_status fin(ffth_plan* P, const Desc* d, int nb, int op, int nblk_f, int nblk_i) {
-  ProfScope ps(P, C_FIN, nb);
-  HIPCHK(launch_finalize(nb, P->stream, d, op, nblk_f, nblk_i));
+template <typename T> ffth_status xcg3(ffth_plan* P, const Desc* d, int nb, bool h16) {
+  ProfScope ps(P, sizeof(T) == 8 ? C_XCG3_64 : C_XCG3, nb);
+  if (grp<T>(P).on)
+    HIPCHK(P->iso ? GLaunch<T>::template xcg3<true>(P->n[2], grp<T>(P), h16, nb, P->stream, d, P->rows, P->nvox)
+                  : GLaunch<T>::template xcg3<false>(P->n[2], grp<T>(P), h16, nb, P->stream, d, P->rows, P->nvox));
+  else
+    HIPCHK(Launch<T>::xcg3(P->n[2], P->iso, pv<T>(P, PS_XI), h16, dim3(iblocks<T>(P), nb), P->stream, d, P->rows,
+                           P->nvox));
   return FFTH_OK;
 }
 
@@ -505,20 +559,25 @@ template <typename T> ffth_status cg3_start(ffth_plan* P, const Desc* d, int nb,
   return fin(P, d, nb, FIN_CG3_INIT, xblocks<T>(P), 0);
 }
 
-// One three-term CG iteration: y, z (Green operator), y, fused x-pass (per
-// group of chunk_of loads), then the scalars of every load.
-template <typename T> ffth_status cg3_iter(ffth_plan* P, const Desc* d, int nb, bool h16) {
+// k three-term CG iterations: spectral step (Green operator), fused x-pass (per
+// group of chunk_of loads), then the scalars of every load.  Where the
+// spectral step carries a finalize, that of iteration j rides in iteration
+// j + 1 and only the last is a launch of its own.
+template <typename T> ffth_status cg3_iters(ffth_plan* P, const Desc* d, int nb, int n, bool h16) {
   ffth_status s;
   if (nb <= 0) return FFTH_OK;
   const int c = chunk_of<T>(P, nb);
-  for (int i = 0; i < nb; i += c) {
-    const int k = std::min(c, nb - i);
-    if ((s = yzy<T>(P, d + i, k, OP_GAMMA, h16)) != FFTH_OK) return s;
-    ProfScope ps(P, sizeof(T) == 8 ? C_XCG3_64 : C_XCG3, k);
-    HIPCHK(Launch<T>::xcg3(P->n[2], P->iso, pv<T>(P, PS_XI), h16, dim3(iblocks<T>(P), k), P->stream, d + i, P->rows,
-                           P->nvox));
+  const bool carry = carries_fin<T>(P);
+  for (int j = 0; j < n; ++j) {
+    for (int i = 0; i < nb; i += c) {
+      const int k = std::min(c, nb - i);
+      if ((s = spectral<T>(P, d + i, k, OP_GAMMA, h16, carry && j > 0 ? FIN_CG3 : -1, 0, iblocks<T>(P))) != FFTH_OK)
+        return s;
+      if ((s = xcg3<T>(P, d + i, k, h16)) != FFTH_OK) return s;
+    }
+    if ((!carry || j == n - 1) && (s = fin(P, d, nb, FIN_CG3, 0, iblocks<T>(P))) != FFTH_OK) return s;
   }
-  return fin(P, d, nb, FIN_CG3, 0, iblocks<T>(P));
+  return FFTH_OK;
 }
 
 // ---- autotuner ------------------------------------------------------------
@@ -561,6 +620,8 @@ void tune_prec(ffth_plan* P, const Desc* d, int nt, int xf_mode, int xi_mode, bo
   const int ncols = kc * 6, nplanes = P->n[0] * (P->h / kc);
   const long M = (long)P->n[1] * kc;
   for (int pass = 0; pass < 4; ++pass) {
+    // grouped passes have one shape; a 2-D grid has no y-pass
+    if (P->grp[pi].on || (P->plane && pass == PS_Y)) continue;
     double best = 1e30;
     int bv = 0;
     for (int v = 0; v < NVAR; ++v) {
@@ -579,6 +640,12 @@ void tune_prec(ffth_plan* P, const Desc* d, int nt, int xf_mode, int xi_mode, bo
         t = time_launches(P->stream, e0, e1, [&] {
           (void)Launch<T>::ypass(P->n[1], v, h16, dim3(nplanes * ntl, nt), P->stream, d, -1, ncols, ntl);
           if (h16) (void)Launch<T>::ypass(P->n[1], v, false, dim3(nplanes * ntl, nt), P->stream, d, +1, ncols, ntl);
+        });
+      } else if (pass == PS_Z && P->plane) {
+        const int tk = Launch<T>::z_cols(P->n[1], v), nzb = (kc + tk - 1) / tk * (P->h / kc);
+        t = time_launches(P->stream, e0, e1, [&] {
+          (void)Launch<T>::zpass(P->n[1], v, h16, dim3(nzb, nt), P->stream, d, OP_GAMMA, 1, P->h,
+                                 1.0 / (double)P->nvox, true);
         });
       } else if (pass == PS_Z) {
         const int tk = Launch<T>::z_cols(P->n[0], v);
@@ -610,27 +677,13 @@ void tune_prec(ffth_plan* P, const Desc* d, int nt, int xf_mode, int xi_mode, bo
   // through every pass before the next
   P->bw[pi] = 0;
   if (nt > 1) {
-    const int cw = Launch<T>::y_cols(P->n[1], P->var[PS_Y][pi]), ntl = (ncols + cw - 1) / cw;
-    const int tk = Launch<T>::z_cols(P->n[0], P->var[PS_Z][pi]);
-    const int nzb = (int)((M + tk - 1) / tk) * (P->h / kc);
     auto iteration = [&](int w) {
       for (int i = 0; i < nt; i += w) {
         const int k = std::min(w, nt - i);
-        if (!fused)
-          (void)Launch<T>::xfwd(P->n[2], P->iso, P->var[PS_XF][pi], h16, dim3(xblocks<T>(P), k), P->stream, d + i,
-                                xf_mode, P->rows, P->nvox);
-        (void)Launch<T>::ypass(P->n[1], P->var[PS_Y][pi], h16, dim3(nplanes * ntl, k), P->stream, d + i, -1, ncols,
-                               ntl);
-        (void)Launch<T>::zpass(P->n[0], P->var[PS_Z][pi], h16, dim3(nzb, k), P->stream, d + i, OP_GAMMA, P->n[1],
-                               P->h, 1.0 / (double)P->nvox);
-        (void)Launch<T>::ypass(P->n[1], P->var[PS_Y][pi], false, dim3(nplanes * ntl, k), P->stream, d + i, +1, ncols,
-                               ntl);
-        if (fused)
-          (void)Launch<T>::xcg3(P->n[2], P->iso, P->var[PS_XI][pi], h16, dim3(iblocks<T>(P), k), P->stream, d + i,
-                                P->rows, P->nvox);
-        else
-          (void)Launch<T>::xinv(P->n[2], P->iso, P->var[PS_XI][pi], dim3(iblocks<T>(P), k), P->stream, d + i,
-                                xi_mode, P->rows, P->nvox);
+        if (!fused) (void)xfwd<T>(P, d + i, k, xf_mode, h16);
+        (void)spectral<T>(P, d + i, k, OP_GAMMA, h16);
+        if (fused) (void)xcg3<T>(P, d + i, k, h16);
+        else (void)xinv<T>(P, d + i, k, xi_mode);
       }
     };
     double best = time_launches(P->stream, e0, e1, [&] { iteration(nt); });
@@ -762,8 +815,8 @@ ffth_status apply(ffth_plan* P, const Desc* d, int nb, int xf, int spec_op, int 
   for (int i = 0; i < nb; i += c) {
     const int k = std::min(c, nb - i);
     if ((s = xfwd<T>(P, d + i, k, xf)) != FFTH_OK) return s;
-    if (xf == XF_CG && (s = fin(P, d + i, k, FIN_CG_ALPHA, xblocks<T>(P), 0)) != FFTH_OK) return s;
-    if ((s = yzy<T>(P, d + i, k, spec_op)) != FFTH_OK) return s;
+    if ((s = spectral<T>(P, d + i, k, spec_op, false, xf == XF_CG ? FIN_CG_ALPHA : -1, xblocks<T>(P), 0)) != FFTH_OK)
+      return s;
     if ((s = xinv<T>(P, d + i, k, xi)) != FFTH_OK) return s;
   }
   if (fin_op >= 0 && (s = fin(P, d, nb, fin_op, xblocks<T>(P), iblocks<T>(P))) != FFTH_OK) return s;
@@ -808,11 +861,11 @@ template <typename T> ffth_status bicg_iter(ffth_plan* P, const Desc* d, int nb)
     const int k = std::min(c, nb - i);
     const Desc* g = d + i;
     if ((s = xfwd<T>(P, g, k, XF_BI1)) != FFTH_OK) return s;
-    if ((s = yzy<T>(P, g, k, OP_GAMMA)) != FFTH_OK) return s;
+    if ((s = spectral<T>(P, g, k, OP_GAMMA)) != FFTH_OK) return s;
     if ((s = xinv<T>(P, g, k, XI_BI1)) != FFTH_OK) return s;
     if ((s = fin(P, g, k, FIN_BI_ALPHA, 0, iblocks<T>(P))) != FFTH_OK) return s;
     if ((s = xfwd<T>(P, g, k, XF_BI2)) != FFTH_OK) return s;
-    if ((s = yzy<T>(P, g, k, OP_GAMMA)) != FFTH_OK) return s;
+    if ((s = spectral<T>(P, g, k, OP_GAMMA)) != FFTH_OK) return s;
     if ((s = xinv<T>(P, g, k, XI_BI2)) != FFTH_OK) return s;
   }
   return fin(P, d, nb, FIN_BI_OMEGA, 0, iblocks<T>(P));
@@ -874,8 +927,7 @@ template <typename T> ffth_status run_cg3(ffth_plan* P, int nl) {
   while (it < o.max_iter && any_active(P, 0, nl)) {
     const int k = std::min(o.check_every, o.max_iter - it);
     if ((as = active_set(P, R_MAIN, 0, nl, 0)).n < 0) return FFTH_ERR_DEVICE;
-    for (int j = 0; j < k; ++j)
-      if ((s = cg3_iter<T>(P, as.d, as.n, false)) != FFTH_OK) return s;
+    if ((s = cg3_iters<T>(P, as.d, as.n, k, false)) != FFTH_OK) return s;
     it += k;
     if ((s = read_states(P)) != FFTH_OK) return s;
   }
@@ -1083,10 +1135,11 @@ ffth_status group_issue(std::vector<Job*>& jobs, Stage& st, int* kin_out, InnerS
     *kin_out = kin;
     return FFTH_OK;
   }
-  for (int j = 0; j < kin && nIN > 0; ++j) {
-    if (o.scheme == FFTH_BASIC) s = apply<float>(dims, din, nIN, XF_MATVEC, OP_GAMMA, XI_BS_INNER, FIN_BS);
-    else s = cg3_iter<float>(dims, din, nIN, dims->h16);
-    if (s != FFTH_OK) return s;
+  if (o.scheme == FFTH_BASIC) {
+    for (int j = 0; j < kin; ++j)
+      if ((s = apply<float>(dims, din, nIN, XF_MATVEC, OP_GAMMA, XI_BS_INNER, FIN_BS)) != FFTH_OK) return s;
+  } else if ((s = cg3_iters<float>(dims, din, nIN, kin, dims->h16)) != FFTH_OK) {
+    return s;
   }
   for (Job* J : jobs) J->fresh = false;
   for (Job* J : jobs)
@@ -1500,6 +1553,7 @@ ffth_status plan_create(ffth_plan** out, const ffth_problem* p, const ffth_opts*
   P->d_desc = (Desc*)(P->ws + L.desc);
   P->d_state = (SolverState*)(P->ws + L.state);
   P->d_cdesc = (Desc*)(P->ws + L.cdesc);
+  set_passes(P, false);
   set_blocks(P);
   P->h_desc.assign(L.ndesc, Desc{});
   P->hpool = pool;
@@ -1663,7 +1717,7 @@ ffth_status build_rhs(ffth_plan* P, int order, int nl, const double* eps, const 
   if ((s = fin(P, dptr(P, R_POST), nl, FIN_O1RHS, 0, nms)) != FFTH_OK) return s;
   const Desc* dt = dptr(P, R_THETA);
   if ((s = xfwd<double>(P, dt, nl, XF_COPY)) != FFTH_OK) return s;
-  if ((s = yzy<double>(P, dt, nl, OP_THETA)) != FFTH_OK) return s;
+  if ((s = spectral<double>(P, dt, nl, OP_THETA)) != FFTH_OK) return s;
   if ((s = xinv<double>(P, dt, nl, XI_ACCUM)) != FFTH_OK) return s;
   if ((s = read_states(P)) != FFTH_OK) return s;
   gmean.assign(3 * nl, 0.0);
@@ -1712,7 +1766,7 @@ ffth_status make_x1_block(ffth_plan* P, const double* eps0, double* out, int cou
     const int nb = std::min(k, count - J0);
     const Desc* d = P->d_desc + util6_slot(P, J0);
     if ((s = xfwd<double>(P, d, nb, XF_COPY)) != FFTH_OK) return s;
-    if ((s = yzy<double>(P, d, nb, OP_DISP)) != FFTH_OK) return s;
+    if ((s = spectral<double>(P, d, nb, OP_DISP)) != FFTH_OK) return s;
     if ((s = xinv<double>(P, d, nb, XI_STORE)) != FFTH_OK) return s;
   }
   return FFTH_OK;
@@ -1813,11 +1867,11 @@ ffth_status ffth_green_apply(ffth_plan* P, const double* tau, double* eta, int32
   const Desc* dd = dptr(P, R_UTIL);
   if (precision == FFTH_FP64) {
     if ((s = xfwd<double>(P, dd, 1, XF_COPY)) != FFTH_OK) return s;
-    if ((s = yzy<double>(P, dd, 1, OP_GAMMA)) != FFTH_OK) return s;
+    if ((s = spectral<double>(P, dd, 1, OP_GAMMA)) != FFTH_OK) return s;
     if ((s = xinv<double>(P, dd, 1, XI_STORE)) != FFTH_OK) return s;
   } else {
     if ((s = xfwd<float>(P, dd, 1, XF_COPY)) != FFTH_OK) return s;
-    if ((s = yzy<float>(P, dd, 1, OP_GAMMA)) != FFTH_OK) return s;
+    if ((s = spectral<float>(P, dd, 1, OP_GAMMA)) != FFTH_OK) return s;
     if ((s = xinv<float>(P, dd, 1, XI_STORE)) != FFTH_OK) return s;
   }
   HIPCHK(hipStreamSynchronize(P->stream));
@@ -1844,7 +1898,7 @@ ffth_status ffth_displacement(ffth_plan* P, const double* eps, double* u) {
   if ((s = upload_states(P, st, 3 * P->nloads)) != FFTH_OK) return s;
   const Desc* dd = dptr(P, R_UTIL);
   if ((s = xfwd<double>(P, dd, 1, XF_COPY)) != FFTH_OK) return s;
-  if ((s = yzy<double>(P, dd, 1, OP_DISP)) != FFTH_OK) return s;
+  if ((s = spectral<double>(P, dd, 1, OP_DISP)) != FFTH_OK) return s;
   if ((s = xinv<double>(P, dd, 1, XI_STORE)) != FFTH_OK) return s;
   HIPCHK(hipStreamSynchronize(P->stream));
   return FFTH_OK;
@@ -1911,6 +1965,7 @@ ffth_status ffth_set_tile_variants(ffth_plan* P, const int32_t in[8]) {
     }
   }
   for (int i = 0; i < 8; ++i) P->var[i / 2][i % 2] = in[i];
+  set_passes(P, true);
   set_blocks(P);
   return FFTH_OK;
 }
@@ -2119,7 +2174,7 @@ ffth_status issue_merged(ffth_server* S, Stage& stage, GroupMap& groups, const s
         const int from = stage.cursor;
         int cnt = 0, kmin = INT32_MAX;
         struct Seg {
-          int first, count, nb[3];
+          int first, count, nb[2], lds[2];
         };
         std::vector<Seg> segs;   // one per grid with inner loads, descriptors consecutive from `from`
         std::vector<size_t> members;
@@ -2134,11 +2189,11 @@ ffth_status issue_merged(ffth_server* S, Stage& stage, GroupMap& groups, const s
               g_last_error = "descriptor staging area too small for the step";
               return FFTH_ERR_INVALID;
             }
-            Seg sg{cnt, is.cnt, {0, 0, 0}};
-            multi_blocks(P0->n, sg.nb);
+            Seg sg{cnt, is.cnt, {0, 0}, {0, 0}};
+            multi_blocks(P0->n, sg.nb, sg.lds);
             for (int i = 0; i < is.cnt; ++i) {
               Desc dd = stage.h[is.from + i];
-              dd.nblk_multi = sg.nb[2];
+              dd.nblk_multi = sg.nb[1];
               stage.h[stage.cursor++] = dd;
             }
             if (is.cnt > 0) {
@@ -2159,29 +2214,32 @@ ffth_status issue_merged(ffth_server* S, Stage& stage, GroupMap& groups, const s
           if ((s = stage_upload(m, stage, from, cnt, &d)) != FFTH_OK) return s;
           // segment tables per pass, MULTI_SEGS grids per launch; each load's
           // blocks are padded to a multiple of the 8 XCDs
-          std::vector<std::array<MultiSegs, 3>> tabs;
+          struct Tab {
+            MultiSegs ms[2];
+            int lds[2];
+          };
+          std::vector<Tab> tabs;
           for (size_t c0 = 0; c0 < segs.size(); c0 += MULTI_SEGS) {
-            std::array<MultiSegs, 3> t;
-            for (int pass = 0; pass < 3; ++pass) {
-              MultiSegs& ms = t[pass];
-              std::memset(&ms, 0, sizeof(ms));
+            Tab t;
+            std::memset(&t, 0, sizeof(t));
+            for (int pass = 0; pass < 2; ++pass) {
+              MultiSegs& ms = t.ms[pass];
               for (size_t c = c0; c < segs.size() && c < c0 + MULTI_SEGS; ++c) {
                 const int k = ms.n++;
                 ms.first[k] = segs[c].first;
                 ms.bpd[k] = segs[c].nb[pass];
                 ms.off[k + 1] = ms.off[k] + segs[c].count * ((segs[c].nb[pass] + 7) / 8 * 8);
+                ms.nload += segs[c].count;
+                t.lds[pass] = std::max(t.lds[pass], segs[c].lds[pass]);
               }
             }
             tabs.push_back(t);
           }
           for (int j = 0; j < kmin; ++j) {
-            for (auto& t : tabs) HIPCHK(multi_ypass(t[0], m, d, -1, h16 != 0));
-            for (auto& t : tabs) HIPCHK(multi_zpass(t[1], m, d, OP_GAMMA, h16 != 0));
-            // the inverse y-transform reads the FP32 copy of a binary16 inner solve
-            for (auto& t : tabs) HIPCHK(multi_ypass(t[0], m, d, +1, false));
-            for (auto& t : tabs) HIPCHK(multi_xcg3(t[2], m, d, iso != 0, h16 != 0));
-            HIPCHK(launch_finalize(cnt, m, d, FIN_CG3, 0, -1));
+            for (auto& t : tabs) HIPCHK(multi_gz(t.ms[0], t.lds[0], m, d, OP_GAMMA, h16 != 0, j > 0 ? FIN_CG3 : -1));
+            for (auto& t : tabs) HIPCHK(multi_xcg3(t.ms[1], t.lds[1], m, d, iso != 0, h16 != 0));
           }
+          HIPCHK(launch_finalize(cnt, m, d, FIN_CG3, 0, -1));
           S->multi_iterations += kmin;
           S->multi_max_grids = std::max(S->multi_max_grids, (int32_t)std::min<size_t>(segs.size(), MULTI_SEGS));
         }

@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "fft_device.h"
+#include "ffth_finalize.h"
 #include "ffth_types.h"
 
 namespace ffth {
@@ -242,17 +243,142 @@ __device__ __forceinline__ void load_rows_c2r(const S* spec, C2<T>* z, long row0
   }
 }
 
-template <typename T, int N2, bool ISO, int ROWS = x_rows<T>(N2), int NTB = NT, typename S = C2<T>, int PLAN = 0>
-__global__ __launch_bounds__(NTB) void k_xfwd(const Desc* __restrict__ descs, int mode, long rows_total,
-                                              long nvox) {
+// ---------------------------------------------------------------------------
+// Grouped x-passes (R1 > 1): axis 1 is transformed by two kernels.  With
+// n1 = R1 R2, i1 = a R2 + b and k1 = q + R1 p,
+//   sum_i1 x[i1] w_n1^(i1 k1) = sum_b w_R2^(b p) [ w_n1^(b q) sum_a w_R1^(a q) x[a R2 + b] ]:
+// an x-pass block holds whole groups, the R1 rows (i0, a R2 + b) of fixed i0
+// and b, and does the bracket in registers while it stores its half spectrum
+// (value q in the place of row q R2 + b); the z-pass does the sum over b
+// around its operator (k_gz).  The y-passes and their two trips through
+// memory go; an application is three passes instead of five.
+// ---------------------------------------------------------------------------
+
+// Grid row of local row rr of a block (base: its first row, or first group).
+template <int R1> __device__ __forceinline__ long tile_row(long base, int rr, long rows_total, int r2) {
+  if constexpr (R1 == 1) {
+    return base + rr;
+  } else {
+    const int gi = (int)base + rr / R1;
+    const int i0 = gi / r2;
+    return (long)gi * R1 < rows_total ? ((long)i0 * R1 + rr % R1) * r2 + (gi - i0 * r2) : rows_total;
+  }
+}
+
+// tw1[g R1 + q] = exp(-2 pi i b q / n1) of the block's groups
+template <typename T, int R1, int G, int NTB>
+__device__ __forceinline__ void build_group_twiddles(C2<T>* tw1, long g0, int r2) {
+  for (int m = threadIdx.x; m < G * R1; m += NTB) {
+    const int b = (int)(g0 + m / R1) % r2, q = m % R1;
+    double s, c;
+    sincospi(-2.0 * (double)(b * q) / (double)(R1 * r2), &s, &c);
+    tw1[m] = C2<T>{(T)c, (T)s};
+  }
+}
+
+// store_rows_r2c for groups: the R1 rows of a (k2, component) are transformed
+// along a in registers.  Chunks of 1 << kcs values of k2.  Binary16 storage
+// divides by R1 so that the stored values stay in range.
+template <typename T, int N2, int R1, int G, int NTB, typename S>
+__device__ __forceinline__ void store_groups_r2c(S* spec, const C2<T>* z, const C2<T>* tw1, long g0, long rows_total,
+                                                 int r2, int kcs) {
   constexpr int RS = N2 + N2 / 16;
   constexpr int H = N2 / 2;
+  constexpr bool FULL = std::is_same<S, C2<T>>::value;
+  for (int v = threadIdx.x; v < G * H * 6; v += NTB) {
+    const int g = v / (H * 6), rem = v % (H * 6);
+    const int gi = (int)g0 + g;
+    if ((long)gi * R1 >= rows_total) continue;
+    const int k = rem / 6, c = rem % 6, q = c >> 1;
+    const C2<T>* zr = z + (g * R1 * 3 + q) * RS;
+    const int kp = padx<true>(k), km = padx<true>((N2 - k) % N2);
+    C2<T> o[R1];
+#pragma unroll
+    for (int a = 0; a < R1; ++a) {
+      const C2<T> z1 = zr[a * 3 * RS + kp];
+      const C2<T> z2 = conj(zr[a * 3 * RS + km]);
+      if ((c & 1) == 0) o[a] = (z1 + z2) * T(0.5);
+      else o[a] = C2<T>{(z1.y - z2.y) * T(0.5), -(z1.x - z2.x) * T(0.5)};
+    }
+    dft<R1, -1>(o);
+    const int i0 = gi / r2, b = gi - i0 * r2;
+    S* dst = spec + ((((long)(k >> kcs) * rows_total + (long)i0 * R1 * r2 + b) << kcs) + (k & ((1 << kcs) - 1))) * 6 + c;
+    const int step = (r2 << kcs) * 6;
+#pragma unroll
+    for (int p = 0; p < R1; ++p) {
+      C2<T> w = p ? cmul(o[p], tw1[g * R1 + p]) : o[p];
+      if constexpr (!FULL) w = w * T(1.0 / R1);
+      sstore<T>(dst + p * step, w);
+    }
+  }
+}
+
+// load_rows_c2r for groups: the inverse transform along q in registers first.
+template <typename T, int N2, int R1, int G, int NTB>
+__device__ __forceinline__ void load_groups_c2r(const C2<T>* spec, C2<T>* z, const C2<T>* tw1, long g0,
+                                                long rows_total, int r2, int kcs) {
+  constexpr int RS = N2 + N2 / 16;
+  constexpr int H = N2 / 2;
+  for (int v = threadIdx.x; v < G * H * 3; v += NTB) {
+    const int g = v / (H * 3), rem = v % (H * 3);
+    const int gi = (int)g0 + g;
+    if ((long)gi * R1 >= rows_total) continue;   // rows past the end are never used
+    const int k = rem / 3, q = rem % 3;
+    const int i0 = gi / r2, b = gi - i0 * r2;
+    const C2<T>* src =
+        spec + ((((long)(k >> kcs) * rows_total + (long)i0 * R1 * r2 + b) << kcs) + (k & ((1 << kcs) - 1))) * 6 + 2 * q;
+    const int step = (r2 << kcs) * 6;
+    C2<T> a[R1], e[R1];
+#pragma unroll
+    for (int p = 0; p < R1; ++p) {
+      C2<T> w[2];
+      load_v<T, 2>(src + p * step, w);   // 2 q and the row offset are even: aligned to a pair
+      a[p] = w[0];
+      e[p] = w[1];
+    }
+#pragma unroll
+    for (int p = 1; p < R1; ++p) {
+      const C2<T> w = conj(tw1[g * R1 + p]);
+      a[p] = cmul(a[p], w);
+      e[p] = cmul(e[p], w);
+    }
+    dft<R1, 1>(a);
+    dft<R1, 1>(e);
+    C2<T>* zr = z + (g * R1 * 3 + q) * RS;
+    if (k == 0) {
+#pragma unroll
+      for (int p = 0; p < R1; ++p) {
+        zr[p * 3 * RS + padx<true>(0)] = C2<T>{a[p].x, e[p].x};
+        zr[p * 3 * RS + padx<true>(H)] = C2<T>{0, 0};
+      }
+    } else {
+      const int kp = padx<true>(k), km = padx<true>(N2 - k);
+#pragma unroll
+      for (int p = 0; p < R1; ++p) {
+        zr[p * 3 * RS + kp] = C2<T>{a[p].x - e[p].y, a[p].y + e[p].x};
+        zr[p * 3 * RS + km] = C2<T>{a[p].x + e[p].y, e[p].x - a[p].y};
+      }
+    }
+  }
+}
+
+// groups per block of a grouped x-pass: at least 256 voxels
+__host__ __device__ constexpr int group_count(int n2, int r1) { return 256 / (n2 * r1) > 1 ? 256 / (n2 * r1) : 1; }
+
+template <typename T, int N2, bool ISO, int ROWS = x_rows<T>(N2), int NTB = NT, typename S = C2<T>, int PLAN = 0,
+          int R1 = 1>
+__global__ __launch_bounds__(NTB) void k_xfwd(const Desc* __restrict__ descs, int mode, long rows_total,
+                                              long nvox, int r2, int kcs) {
+  constexpr int RS = N2 + N2 / 16;
   __shared__ C2<T> z[ROWS * 3 * RS];
   __shared__ C2<T> tw[N2];
+  __shared__ C2<T> tw1[R1 > 1 ? ROWS : 1];
   const Desc& d = descs[blockIdx.y];
   if (!d.st->active) return;
   build_twiddles<T, N2, NTB>(tw);
-  const long row0 = (long)blockIdx.x * ROWS;
+  const int bid = R1 > 1 ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const long row0 = (long)bid * (ROWS / R1);   // first row, or first group
+  if constexpr (R1 > 1) build_group_twiddles<T, R1, ROWS / R1, NTB>(tw1, row0, r2);
   const T* mat = mat_of<T>(d);
   double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0;
   const T beta = (T)d.st->beta;
@@ -264,7 +390,7 @@ __global__ __launch_bounds__(NTB) void k_xfwd(const Desc* __restrict__ descs, in
 
   for (int v = threadIdx.x; v < ROWS * N2; v += NTB) {
     const int rr = v / N2, i2 = v % N2;
-    const long row = row0 + rr;
+    const long row = tile_row<R1>(row0, rr, rows_total, r2);
     T tau[6] = {0, 0, 0, 0, 0, 0};
     if (row < rows_total) {
       const long vox = row * N2 + i2;
@@ -414,25 +540,34 @@ __global__ __launch_bounds__(NTB) void k_xfwd(const Desc* __restrict__ descs, in
   __syncthreads();
   lds_fft<T, N2, ROWS * 3, NTB, 1, RS, false, true, -1, 1, PLAN>(z, tw);
 
-  store_rows_r2c<T, N2, ROWS, NTB, S>((S*)d.spec, z, row0, rows_total);
+  if constexpr (R1 > 1) store_groups_r2c<T, N2, R1, ROWS / R1, NTB, S>((S*)d.spec, z, tw1, row0, rows_total, r2, kcs);
+  else store_rows_r2c<T, N2, ROWS, NTB, S>((S*)d.spec, z, row0, rows_total);
   double sums[3] = {acc0, acc1, acc2};
-  block_sums<3, NTB>(sums, d.part_f + blockIdx.x, gridDim.x);
+  block_sums<3, NTB>(sums, d.part_f + bid, gridDim.x);
 }
 
 // ---------------------------------------------------------------------------
 // x-pass, inverse: complex-to-real FFT along axis 2 + update + reductions.
 // ---------------------------------------------------------------------------
-template <typename T, int N2, bool ISO, int ROWS = xi_rows<T>(N2), int NTB = NT, int PLAN = 0>
-__global__ __launch_bounds__(NTB) void k_xinv(const Desc* __restrict__ descs, int mode, long rows_total, long nvox) {
+template <typename T, int N2, bool ISO, int ROWS = xi_rows<T>(N2), int NTB = NT, int PLAN = 0, int R1 = 1>
+__global__ __launch_bounds__(NTB) void k_xinv(const Desc* __restrict__ descs, int mode, long rows_total, long nvox,
+                                              int r2, int kcs) {
   constexpr int RS = N2 + N2 / 16;
-  constexpr int H = N2 / 2;
   __shared__ C2<T> z[ROWS * 3 * RS];
   __shared__ C2<T> tw[N2];
+  __shared__ C2<T> tw1[R1 > 1 ? ROWS : 1];
   const Desc& d = descs[blockIdx.y];
   if (!d.st->active) return;
   build_twiddles<T, N2, NTB>(tw);
-  const long row0 = (long)blockIdx.x * ROWS;
-  load_rows_c2r<T, N2, ROWS, NTB>((const C2<T>*)d.spec, z, row0, rows_total);
+  const int bid = R1 > 1 ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const long row0 = (long)bid * (ROWS / R1);   // first row, or first group
+  if constexpr (R1 > 1) {
+    build_group_twiddles<T, R1, ROWS / R1, NTB>(tw1, row0, r2);
+    __syncthreads();
+    load_groups_c2r<T, N2, R1, ROWS / R1, NTB>((const C2<T>*)d.spec, z, tw1, row0, rows_total, r2, kcs);
+  } else {
+    load_rows_c2r<T, N2, ROWS, NTB>((const C2<T>*)d.spec, z, row0, rows_total);
+  }
   __syncthreads();
   lds_fft<T, N2, ROWS * 3, NTB, 1, RS, false, true, +1, 1, PLAN>(z, tw);
 
@@ -440,7 +575,7 @@ __global__ __launch_bounds__(NTB) void k_xinv(const Desc* __restrict__ descs, in
   double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0, acc3 = 0.0, acc4 = 0.0;
   for (int v = threadIdx.x; v < ROWS * N2; v += NTB) {
     const int rr = v / N2, i2 = v % N2;
-    const long row = row0 + rr;
+    const long row = tile_row<R1>(row0, rr, rows_total, r2);
     if (row >= rows_total) continue;
     const long vox = row * N2 + i2;
     T eta[6];
@@ -576,10 +711,10 @@ __global__ __launch_bounds__(NTB) void k_xinv(const Desc* __restrict__ descs, in
   }
   if (mode == XI_BI2) {
     double sums[5] = {acc0, acc1, acc2, acc3, acc4};
-    block_sums<5, NTB>(sums, d.part_i + blockIdx.x, gridDim.x);
+    block_sums<5, NTB>(sums, d.part_i + bid, gridDim.x);
   } else {
     double sums[2] = {acc0, acc1};
-    block_sums<2, NTB>(sums, d.part_i + blockIdx.x, gridDim.x);
+    block_sums<2, NTB>(sums, d.part_i + bid, gridDim.x);
   }
 }
 
@@ -600,17 +735,24 @@ __global__ __launch_bounds__(NTB) void k_xinv(const Desc* __restrict__ descs, in
 // that stops after an even iteration forms its last x in k_cg3_finish.
 // ---------------------------------------------------------------------------
 // Row block b of nblk (its partial sums go to slot k at part_i + k nblk + b);
-// z: ROWS * 3 * (N2 + N2/16) LDS elements, tw: N2.
-template <typename T, int N2, bool ISO, int ROWS, int NTB, typename S, int PLAN>
+// z: ROWS * 3 * (N2 + N2/16) LDS elements, tw: N2, tw1: ROWS (R1 > 1).
+template <typename T, int N2, bool ISO, int ROWS, int NTB, typename S, int PLAN, int R1 = 1>
 __device__ __forceinline__ void xcg3_tile(const Desc& d, int b, int nblk, long rows_total, long nvox, C2<T>* z,
-                                          C2<T>* tw) {
+                                          C2<T>* tw, C2<T>* tw1 = nullptr, int r2 = 1, int kcs = 0) {
   constexpr int RS = N2 + N2 / 16;
   build_twiddles<T, N2, NTB>(tw);
-  const long row0 = (long)b * ROWS;
+  const long row0 = (long)b * (ROWS / R1);   // first row, or first group
   // binary16 inner solve: eta comes from the FP32 copy, tau goes out in binary16
   constexpr bool FULL = std::is_same<S, C2<T>>::value;
   S* spec = (S*)d.spec;
-  load_rows_c2r<T, N2, ROWS, NTB>((const C2<T>*)(FULL ? d.spec : d.spec2), z, row0, rows_total);
+  if constexpr (R1 > 1) {
+    build_group_twiddles<T, R1, ROWS / R1, NTB>(tw1, row0, r2);
+    __syncthreads();
+    load_groups_c2r<T, N2, R1, ROWS / R1, NTB>((const C2<T>*)(FULL ? d.spec : d.spec2), z, tw1, row0, rows_total, r2,
+                                               kcs);
+  } else {
+    load_rows_c2r<T, N2, ROWS, NTB>((const C2<T>*)(FULL ? d.spec : d.spec2), z, row0, rows_total);
+  }
   __syncthreads();
   lds_fft<T, N2, ROWS * 3, NTB, 1, RS, false, true, +1, 1, PLAN>(z, tw);
 
@@ -631,7 +773,7 @@ __device__ __forceinline__ void xcg3_tile(const Desc& d, int b, int nblk, long r
   double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0;
   for (int v = threadIdx.x; v < ROWS * N2; v += NTB) {
     const int rr = v / N2, i2 = v % N2;
-    const long row = row0 + rr;
+    const long row = tile_row<R1>(row0, rr, rows_total, r2);
     T tau[6] = {0, 0, 0, 0, 0, 0};
     if (row < rows_total) {
       const long vox = row * N2 + i2;
@@ -689,18 +831,23 @@ __device__ __forceinline__ void xcg3_tile(const Desc& d, int b, int nblk, long r
   }
   __syncthreads();
   lds_fft<T, N2, ROWS * 3, NTB, 1, RS, false, true, -1, 1, PLAN>(z, tw);
-  store_rows_r2c<T, N2, ROWS, NTB, S>(spec, z, row0, rows_total);
+  if constexpr (R1 > 1) store_groups_r2c<T, N2, R1, ROWS / R1, NTB, S>(spec, z, tw1, row0, rows_total, r2, kcs);
+  else store_rows_r2c<T, N2, ROWS, NTB, S>(spec, z, row0, rows_total);
   double sums[3] = {acc0, acc1, acc2};
   block_sums<3, NTB>(sums, d.part_i + b, nblk);
 }
 
-template <typename T, int N2, bool ISO, int ROWS = xi_rows<T>(N2), int NTB = NT, typename S = C2<T>, int PLAN = 0>
-__global__ __launch_bounds__(NTB) void k_xcg3(const Desc* __restrict__ descs, long rows_total, long nvox) {
+template <typename T, int N2, bool ISO, int ROWS = xi_rows<T>(N2), int NTB = NT, typename S = C2<T>, int PLAN = 0,
+          int R1 = 1>
+__global__ __launch_bounds__(NTB) void k_xcg3(const Desc* __restrict__ descs, long rows_total, long nvox, int r2,
+                                              int kcs) {
   __shared__ C2<T> z[ROWS * 3 * (N2 + N2 / 16)];
   __shared__ C2<T> tw[N2];
+  __shared__ C2<T> tw1[R1 > 1 ? ROWS : 1];
   const Desc& d = descs[blockIdx.y];
   if (!d.st->active) return;
-  xcg3_tile<T, N2, ISO, ROWS, NTB, S, PLAN>(d, (int)blockIdx.x, (int)gridDim.x, rows_total, nvox, z, tw);
+  const int bid = R1 > 1 ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  xcg3_tile<T, N2, ISO, ROWS, NTB, S, PLAN, R1>(d, bid, (int)gridDim.x, rows_total, nvox, z, tw, tw1, r2, kcs);
 }
 
 // Three-term CG: the last x of loads whose solve stopped after an even
@@ -931,9 +1078,11 @@ __device__ __forceinline__ void spectral_op(int op, T (&in)[6][2], T (&out)[6][2
 
 // Tile bid (chunk bid / bpc, columns from (bid % bpc) TK) of one load; buf:
 // N0 * 6 TK LDS elements (16-byte aligned), tw: N0.
+// plane: a 2-D grid (axis 0 of length 1).  N0 is then the length of axis 1 (n1
+// is passed as 1), so this pass replaces both y-passes and the z-pass.
 template <typename T, int N0, int TK, int NTB, int V, typename S, int PLAN>
 __device__ __forceinline__ void zpass_tile(const Desc& d, int bid, int op, int n1, int h, double scale, C2<T>* buf,
-                                           C2<T>* tw) {
+                                           C2<T>* tw, bool plane = false) {
   constexpr int W = TK * 6;
   build_twiddles<T, N0, NTB>(tw);
   // columns (i1, k2 % kc) of one k2-chunk form a [N0][M][6] sub-array
@@ -953,7 +1102,8 @@ __device__ __forceinline__ void zpass_tile(const Desc& d, int bid, int op, int n
   // binary16 storage: the spectral operator also restores the scale of the
   // forward transforms (the descriptor's factor times the right-hand side's
   // RMS replaces 1/N)
-  const T sc = FULL ? (T)scale : (T)(d.op_scale * d.st->dscale);
+  // (2-D: no forward y-pass divided by the axis length)
+  const T sc = FULL ? (T)scale : (T)(d.op_scale * d.st->dscale / (plane ? N0 : 1));
   // all of a thread's loads are issued before the first LDS write, so their
   // latencies overlap (the tile's rows are far apart in memory)
   constexpr int NA = N0 * W / GZ, NL = (NA + NTB - 1) / NTB;
@@ -1007,7 +1157,7 @@ __device__ __forceinline__ void zpass_tile(const Desc& d, int bid, int op, int n
 #pragma unroll
       for (int c = 0; c < 6; ++c) out[c][0] = out[c][1] = T(0);
     } else {
-      spectral_op<T>(op, in, out, (T)k0s, (T)k1s, (T)k2, d.lam0, d.mu0, sc);
+      spectral_op<T>(op, in, out, (T)(plane ? 0 : k0s), (T)(plane ? k0s : k1s), (T)k2, d.lam0, d.mu0, sc);
     }
 #pragma unroll
     for (int c = 0; c < 6; c += V) {
@@ -1040,142 +1190,278 @@ __device__ __forceinline__ void zpass_tile(const Desc& d, int bid, int op, int n
   }
 }
 
+// fin >= 0 (z-passes of 2-D grids, grouped z-passes): the first block of every
+// entry does that finalize instead of a tile.  The operator needs none of the
+// scalars a finalize sets; blocks that still see a load active which it stops
+// write a spectrum that nothing reads.
+template <int NTB>
+__device__ __forceinline__ bool carried_finalize(const Desc& d, int fin, int nblk_f, int nblk_i, int& bid, int& nblk) {
+  bid = blockIdx.x;
+  nblk = gridDim.x;
+  if (fin < 0) return false;
+  --nblk;
+  if (bid-- > 0) return false;
+  if (threadIdx.x < 256) finalize_entry<256, true>(d, fin, nblk_f, nblk_i);   // whole waves leave
+  return true;
+}
+
 template <typename T, int N0, int TK = z_cols<T>(N0), int NTB = NT, bool REMAP = true, int V = vec_width<T>(),
           typename S = C2<T>, int PLAN = 0>
-__global__ __launch_bounds__(NTB) void k_zpass(const Desc* __restrict__ descs, int op, int n1, int h, double scale) {
+__global__ __launch_bounds__(NTB) void k_zpass(const Desc* __restrict__ descs, int op, int n1, int h, double scale,
+                                               int plane, int fin, int nblk_f, int nblk_i) {
   __shared__ __attribute__((aligned(16))) C2<T> buf[N0 * TK * 6];
   __shared__ C2<T> tw[N0];
   const Desc& d = descs[blockIdx.y];
   if (!d.st->active) return;
-  const int bid = REMAP ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
-  zpass_tile<T, N0, TK, NTB, V, S, PLAN>(d, bid, op, n1, h, scale, buf, tw);
+  int bid, nblk;
+  if (carried_finalize<NTB>(d, fin, nblk_f, nblk_i, bid, nblk)) return;
+  if (REMAP) bid = xcd_tile(bid, nblk);
+  zpass_tile<T, N0, TK, NTB, V, S, PLAN>(d, bid, op, n1, h, scale, buf, tw, plane != 0);
 }
 
 // ---------------------------------------------------------------------------
-// Multi-size launches of the FP32 inner iteration: one launch per pass
-// covers loads of grids of different sizes (axis lengths from
-// FFTH_MULTI_SIZES).  Each load's descriptor carries its grid (n); the
-// launch's blocks are the tiles of all its loads, listed by a segment table
-// (MultiSegs) of consecutive loads of one grid, each tile with the default
-// tile shape of its lengths (variant 0, radix plan 0, 256 threads: the
-// arithmetic of the per-size kernels with their default tiles, bit for bit).
-// LDS is sized for the largest length.
+// Grouped z-pass (after grouped x-passes, which did the radix-R1 part of axis
+// 1): R2-point transforms along axis 1, forward FFT along axis 0, spectral
+// operator at k1 = q + R1 p, and the inverses.  Block = KC values of k2, one
+// q, every b and i0; a row of the tile, [b][k2][6], is contiguous.  Rows are
+// an odd number of elements apart (WP): the passes along a column and the
+// operator's threads then spread over the banks.
+// ---------------------------------------------------------------------------
+template <typename T> __host__ __device__ constexpr int gz_kc(int n0, int r2) { return n0 * r2 * 6 * 2 * (int)sizeof(T) <= 16384 ? 2 : 1; }
+
+// R2-point transforms along axis 1 of the tile, in place: each thread reads
+// and writes the R2 values of its own (i0, k2, component).
+template <typename T, int N0, int R2, int KC, int NTB, int DIR>
+__device__ __forceinline__ void gz_axis1(C2<T>* buf) {
+  constexpr int C = KC * 6, WP = R2 * C + 1;
+  for (int v = threadIdx.x; v < N0 * C; v += NTB) {
+    C2<T>* e = buf + (v / C) * WP + v % C;
+    C2<T> x[R2];
+#pragma unroll
+    for (int b = 0; b < R2; ++b) x[b] = e[b * C];
+    dft<R2, DIR>(x);
+#pragma unroll
+    for (int b = 0; b < R2; ++b) e[b * C] = x[b];
+  }
+}
+
+template <typename T, int N0, int R2, int KC, int NTB, typename S>
+__device__ __forceinline__ void gz_tile(const Desc& d, int bid, int op, int n1, double scale, C2<T>* buf, C2<T>* tw) {
+  constexpr int W = KC * R2 * 6, WP = W + 1;
+  constexpr bool FULL = std::is_same<S, C2<T>>::value;
+  constexpr int GZ = FULL ? (sizeof(T) == 4 ? 2 : 1) : 4;   // 16 bytes per access
+  build_twiddles<T, N0, NTB>(tw);
+  const int r1 = n1 / R2, chunk = bid / r1, q = bid - chunk * r1;
+  const long rs = (long)n1 * KC * 6;   // elements between rows i0
+  const long base = (long)chunk * N0 * rs + (long)q * W;
+  const S* src = (const S*)d.spec + base;
+  C2<T>* dst = (C2<T>*)(FULL ? d.spec : d.spec2) + base;
+  // binary16 storage: the operator restores the scale of the forward
+  // transforms (the x-pass divided by R1 only)
+  const T sc = FULL ? (T)scale : (T)(d.op_scale * d.st->dscale / R2);
+  constexpr int NA = N0 * W / GZ, NL = (NA + NTB - 1) / NTB;
+  {
+    C2<T> a[NL][GZ];
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+      const int v = threadIdx.x + k * NTB;
+      if (NA % NTB == 0 || v < NA) {
+        const S* s = src + (v / (W / GZ)) * rs + (v % (W / GZ)) * GZ;
+        if constexpr (FULL) load_v<T, GZ>(s, a[k]);
+        else hload_g<T, GZ>(s, a[k]);
+      } else {
+#pragma unroll
+        for (int g = 0; g < GZ; ++g) a[k][g] = C2<T>{0, 0};
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+      const int v = threadIdx.x + k * NTB;
+      if (NA % NTB == 0 || v < NA) {
+#pragma unroll
+        for (int g = 0; g < GZ; ++g) buf[(v / (W / GZ)) * WP + (v % (W / GZ)) * GZ + g] = a[k][g];
+      }
+    }
+  }
+  __syncthreads();
+  gz_axis1<T, N0, R2, KC, NTB, -1>(buf);
+  __syncthreads();
+  lds_fft<T, N0, W, NTB, WP, 1, true, false, -1>(buf, tw);
+  for (int v = threadIdx.x; v < N0 * R2 * KC; v += NTB) {
+    const int k0 = v / (R2 * KC), m = v % (R2 * KC), p = m / KC;
+    const int k1 = q + r1 * p, k2 = chunk * KC + m % KC;
+    const bool nyq = (N0 % 2 == 0 && k0 == N0 / 2) || (n1 % 2 == 0 && k1 == n1 / 2);
+    const int k0s = k0 < (N0 + 1) / 2 ? k0 : k0 - N0;
+    const int k1s = k1 < (n1 + 1) / 2 ? k1 : k1 - n1;
+    C2<T>* e = buf + k0 * WP + m * 6;
+    T in[6][2], out[6][2];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      in[c][0] = e[c].x;
+      in[c][1] = e[c].y;
+    }
+    if (nyq || (k0s == 0 && k1s == 0 && k2 == 0)) {
+#pragma unroll
+      for (int c = 0; c < 6; ++c) out[c][0] = out[c][1] = T(0);
+    } else {
+      spectral_op<T>(op, in, out, (T)k0s, (T)k1s, (T)k2, d.lam0, d.mu0, sc);
+    }
+#pragma unroll
+    for (int c = 0; c < 6; ++c) e[c] = C2<T>{out[c][0], out[c][1]};
+  }
+  __syncthreads();
+  lds_fft<T, N0, W, NTB, WP, 1, true, false, +1>(buf, tw);
+  gz_axis1<T, N0, R2, KC, NTB, +1>(buf);
+  __syncthreads();
+  constexpr int GS = sizeof(T) == 4 ? 2 : 1;
+  for (int v = threadIdx.x; v < N0 * W / GS; v += NTB) {
+    const int i0 = v / (W / GS), w = (v % (W / GS)) * GS;
+    C2<T> a[GS];
+#pragma unroll
+    for (int g = 0; g < GS; ++g) a[g] = buf[i0 * WP + w + g];
+    store_v<T, GS>(dst + i0 * rs + w, a);
+  }
+}
+
+// LDS elements of the tile
+template <typename T> constexpr int gz_elems(int n0, int r2) { return n0 * (gz_kc<T>(n0, r2) * r2 * 6 + 1); }
+
+template <typename T, int N0, int R2, int NTB, typename S>
+__global__ __launch_bounds__(NTB) void k_gz(const Desc* __restrict__ descs, int op, int n1, double scale, int fin,
+                                            int nblk_f, int nblk_i) {
+  __shared__ __attribute__((aligned(16))) C2<T> buf[gz_elems<T>(N0, R2)];
+  __shared__ C2<T> tw[N0];
+  const Desc& d = descs[blockIdx.y];
+  if (!d.st->active) return;
+  int bid, nblk;
+  if (carried_finalize<NTB>(d, fin, nblk_f, nblk_i, bid, nblk)) return;
+  gz_tile<T, N0, R2, gz_kc<T>(N0, R2), NTB, S>(d, xcd_tile(bid, nblk), op, n1, scale, buf, tw);
+}
+
+// Which grids take the grouped passes: axis lengths whose kernels are compiled
+// and whose tiles leave room for three blocks per CU (R2 0: not grouped).
+// FP64 tiles are twice as large: R2 = 4 balances the two passes there.
+constexpr int GROUP_LDS = 56 * 1024;
+template <typename T> __host__ __device__ constexpr int group_r2(int n1) {
+  if (sizeof(T) == 8) return n1 >= 8 && n1 <= 64 ? 4 : 0;
+  return n1 == 8 ? 4 : n1 == 16 || n1 == 32 || n1 == 64 || n1 == 128 ? 8 : n1 == 12 || n1 == 24 || n1 == 48 || n1 == 96 ? 6 : 0;
+}
+template <typename T> constexpr int gx_rows(int n2, int r1) { return group_count(n2, r1) * r1; }
+template <typename T> constexpr bool gx_fits(int n2, int r1) {
+  return gx_rows<T>(n2, r1) * 3 * (n2 + n2 / 16) * 2 * (int)sizeof(T) <= GROUP_LDS;
+}
+template <typename T> constexpr bool gz_fits(int n0, int r2) {
+  return gz_elems<T>(n0, r2) * 2 * (int)sizeof(T) <= GROUP_LDS;
+}
+
+// ---------------------------------------------------------------------------
+// Multi-size launches of the FP32 inner iteration: one launch per grouped
+// pass covers loads of grids of different sizes (axis lengths from
+// FFTH_MULTI_SIZES, all grouped).  Each load's descriptor carries its grid
+// (n); the launch's blocks are the tiles of all its loads, listed by a segment
+// table (MultiSegs) of consecutive loads of one grid, each tile the code of
+// the per-size kernel of its lengths (256 threads): the same arithmetic bit
+// for bit.  LDS is sized by the launch for its largest tile.
 // ---------------------------------------------------------------------------
 #define FFTH_MULTI_SIZES(X) X(16) X(24) X(32) X(48) X(64) X(96) X(128)
 constexpr int MULTI_NT = 256;
-constexpr int MULTI_MAXN = 128;
 constexpr int MULTI_SIZES[] = {16, 24, 32, 48, 64, 96, 128};   // the lengths of FFTH_MULTI_SIZES
 constexpr bool multi_size(int n) {
   for (int m : MULTI_SIZES)
     if (m == n) return true;
   return false;
 }
-#define FFTH_MULTI_CHECK(N) static_assert(multi_size(N), "FFTH_MULTI_SIZES and MULTI_SIZES differ");
+#define FFTH_MULTI_CHECK(N) static_assert(multi_size(N) && group_r2<float>(N) >= 6 && gz_fits<float>(N, 8) && gx_fits<float>(N, 16), "multi-size lengths are grouped");
 FFTH_MULTI_SIZES(FFTH_MULTI_CHECK)
 #undef FFTH_MULTI_CHECK
 #define FFTH_MULTI_COUNT(N) +1
 static_assert(0 FFTH_MULTI_SIZES(FFTH_MULTI_COUNT) == sizeof(MULTI_SIZES) / sizeof(int), "FFTH_MULTI_SIZES and MULTI_SIZES differ");
 #undef FFTH_MULTI_COUNT
-// blocks of one load of grid n in each multi-size pass (host and device)
-__host__ __device__ constexpr int multi_y_blocks(int n0, int n1, int n2) {
-  const int h = n2 / 2, kc = kchunk(h), cw = y_cols<float>(n1);
-  return n0 * (h / kc) * ((kc * 6 + cw - 1) / cw);
+// blocks of one load of grid n in each multi-size pass, and its LDS bytes (host and device)
+__host__ __device__ constexpr int multi_z_blocks(const int* n) {
+  const int r2 = group_r2<float>(n[1]);
+  return n[2] / 2 / gz_kc<float>(n[0], r2) * (n[1] / r2);
 }
-__host__ __device__ constexpr int multi_z_blocks(int n0, int n1, int n2) {
-  const int h = n2 / 2, kc = kchunk(h), tk = z_cols<float>(n0);
-  return (int)(((long)n1 * kc + tk - 1) / tk) * (h / kc);
+__host__ __device__ constexpr int multi_x_blocks(const int* n) {
+  const int r2 = group_r2<float>(n[1]), g = group_count(n[2], n[1] / r2);
+  return (n[0] * r2 + g - 1) / g;
 }
-__host__ __device__ constexpr int multi_x_blocks(int n0, int n1, int n2) {
-  const int r = xi_rows<float>(n2);
-  return (int)(((long)n0 * n1 + r - 1) / r);
+constexpr int multi_z_lds(const int* n) { return (gz_elems<float>(n[0], group_r2<float>(n[1])) + n[0]) * 8; }
+constexpr int multi_x_lds(const int* n) {
+  const int rows = gx_rows<float>(n[2], n[1] / group_r2<float>(n[1]));
+  return (rows * 3 * (n[2] + n[2] / 16) + n[2] + rows) * 8;
 }
-// FP32 LDS elements of each pass at length n, and their maxima over the set
-constexpr int multi_lds(int pass, int n) {
-  return pass == 0 ? n * y_cols<float>(n) : pass == 1 ? n * 6 * z_cols<float>(n) : xi_rows<float>(n) * 3 * (n + n / 16);
-}
-constexpr int multi_lds_max(int pass) {
-  int m = 0;
-  for (int n : MULTI_SIZES) m = multi_lds(pass, n) > m ? multi_lds(pass, n) : m;
-  return m;
-}
-constexpr int MULTI_LDS_Y = multi_lds_max(0), MULTI_LDS_Z = multi_lds_max(1), MULTI_LDS_X = multi_lds_max(2);
 
 // Block of a multi-size launch: its load (descriptor index, -1 for padding)
 // and that load's tile.  Each load of segment s owns bpd[s] blocks padded to
 // a multiple of 8 (the XCDs; segments start at multiples of 8 too), so a
-// block's XCD is its tile slot mod 8; with REMAP the tiles of every load are
-// renumbered XCD-aware as the per-size y and z passes do (each XCD walks a
-// contiguous run of each load's tiles), without it a load's tiles are taken
-// in order as in the per-size fused pass.
-template <bool REMAP> __device__ __forceinline__ int multi_block(const MultiSegs& sg, int& tile) {
+// block's XCD is its tile slot mod 8; the tiles of every load are renumbered
+// XCD-aware as the per-size passes do (each XCD walks a contiguous run of
+// each load's tiles).
+__device__ __forceinline__ int multi_block(const MultiSegs& sg, int& tile) {
   const int b = blockIdx.x;
   int s = 0;
   while (s + 1 < sg.n && b >= sg.off[s + 1]) ++s;
   const int bpd = sg.bpd[s], slots = (bpd + 7) / 8 * 8;
   const int r = b - sg.off[s], load = r / slots, t = r % slots;
   if (t >= bpd) return -1;
-  tile = REMAP ? xcd_tile(t, bpd) : t;
+  tile = xcd_tile(t, bpd);
   return sg.first[s] + load;
 }
-template <typename S>
-__global__ __launch_bounds__(MULTI_NT) void k_ypass_multi(const Desc* __restrict__ descs, int dir, MultiSegs sg) {
-  __shared__ __attribute__((aligned(16))) C2<float> buf[MULTI_LDS_Y];
-  __shared__ C2<float> tw[MULTI_MAXN];
-  int bid;
-  const int di = multi_block<true>(sg, bid);
-  if (di < 0) return;
-  const Desc& d = descs[di];
-  if (!d.st->active) return;
-  const int kc = kchunk(d.n[2] / 2), ncols = kc * 6;
-  switch (d.n[1]) {
-#define FFTH_MULTI_Y(N)                                                                                   \
-  case N: {                                                                                               \
-    constexpr int CW = y_cols<float>(N);                                                                  \
-    ypass_tile<float, N, CW, MULTI_NT, 1, S, 0>(d, bid, dir, ncols, (ncols + CW - 1) / CW, buf, tw);    \
-    break;                                                                                                \
-  }
-    FFTH_MULTI_SIZES(FFTH_MULTI_Y)
-#undef FFTH_MULTI_Y
-  }
-}
 
+// fin >= 0: the blocks after the last segment finalize the launch's loads
 template <typename S>
-__global__ __launch_bounds__(MULTI_NT) void k_zpass_multi(const Desc* __restrict__ descs, int op, MultiSegs sg) {
-  __shared__ __attribute__((aligned(16))) C2<float> buf[MULTI_LDS_Z];
-  __shared__ C2<float> tw[MULTI_MAXN];
+__global__ __launch_bounds__(MULTI_NT) void k_gz_multi(const Desc* __restrict__ descs, int op, MultiSegs sg, int fin) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  if ((int)blockIdx.x >= sg.off[sg.n]) {
+    finalize_entry<MULTI_NT, true>(descs[sg.first[0] + blockIdx.x - sg.off[sg.n]], fin, 0, -1);
+    return;
+  }
   int bid;
-  const int di = multi_block<true>(sg, bid);
+  const int di = multi_block(sg, bid);
   if (di < 0) return;
   const Desc& d = descs[di];
   if (!d.st->active) return;
+  const int n1 = d.n[1];
+  C2<float>* tw = (C2<float>*)lds;   // N0 values, then the tile
   switch (d.n[0]) {
-#define FFTH_MULTI_Z(N)                                                                                   \
-  case N:                                                                                                 \
-    zpass_tile<float, N, z_cols<float>(N), MULTI_NT, 1, S, 0>(d, bid, op, d.n[1], d.n[2] / 2, d.inv_nvox, buf, tw); \
+#define FFTH_MULTI_Z(N)                                                                                               \
+  case N:                                                                                                             \
+    if (group_r2<float>(n1) == 8)                                                                                     \
+      gz_tile<float, N, 8, gz_kc<float>(N, 8), MULTI_NT, S>(d, bid, op, n1, d.inv_nvox, tw + N, tw);                 \
+    else                                                                                                              \
+      gz_tile<float, N, 6, gz_kc<float>(N, 6), MULTI_NT, S>(d, bid, op, n1, d.inv_nvox, tw + N, tw);                 \
     break;
     FFTH_MULTI_SIZES(FFTH_MULTI_Z)
 #undef FFTH_MULTI_Z
   }
 }
 
-// The tile of the fused pass is the load's row block b, whose partial sums
-// go to slot b of the load's array.
+// The tile of the fused pass is block b of its load, whose partial sums go to
+// slot b of the load's array.
+template <int N, bool ISO, typename S, int R1>
+__device__ __forceinline__ void multi_x_tile(const Desc& d, int b, C2<float>* lds, int r2) {
+  constexpr int ROWS = gx_rows<float>(N, R1);
+  const int nb = (d.n[0] * r2 + ROWS / R1 - 1) / (ROWS / R1);
+  const long rows = (long)d.n[0] * d.n[1];
+  const int kcs = d.n[0] * r2 * 48 <= 16384 ? 1 : 0;   // gz_kc<float>
+  xcg3_tile<float, N, ISO, ROWS, MULTI_NT, S, 0, R1>(d, b, nb, rows, rows * N, lds + N + ROWS, lds, lds + N, r2, kcs);
+}
 template <bool ISO, typename S>
 __global__ __launch_bounds__(MULTI_NT) void k_xcg3_multi(const Desc* __restrict__ descs, MultiSegs sg) {
-  __shared__ C2<float> z[MULTI_LDS_X];
-  __shared__ C2<float> tw[MULTI_MAXN];
+  extern __shared__ __attribute__((aligned(16))) char lds[];
   int b;
-  const int di = multi_block<false>(sg, b);
+  const int di = multi_block(sg, b);
   if (di < 0) return;
   const Desc& d = descs[di];
   if (!d.st->active) return;
-  const int nb = multi_x_blocks(d.n[0], d.n[1], d.n[2]);
-  const long rows = (long)d.n[0] * d.n[1];
-  switch (d.n[2]) {
-#define FFTH_MULTI_X(N)                                                                                   \
-  case N:                                                                                                 \
-    xcg3_tile<float, N, ISO, xi_rows<float>(N), MULTI_NT, S, 0>(d, b, nb, rows, rows * N, z, tw);        \
-    break;
+  const int r2 = group_r2<float>(d.n[1]);
+  switch (d.n[2] * 32 + d.n[1] / r2) {
+#define FFTH_MULTI_X(N)                                                                       \
+  case N * 32 + 2: multi_x_tile<N, ISO, S, 2>(d, b, (C2<float>*)lds, r2); break;             \
+  case N * 32 + 4: multi_x_tile<N, ISO, S, 4>(d, b, (C2<float>*)lds, r2); break;             \
+  case N * 32 + 8: multi_x_tile<N, ISO, S, 8>(d, b, (C2<float>*)lds, r2); break;             \
+  case N * 32 + 16: multi_x_tile<N, ISO, S, 16>(d, b, (C2<float>*)lds, r2); break;
     FFTH_MULTI_SIZES(FFTH_MULTI_X)
 #undef FFTH_MULTI_X
   }
@@ -1183,11 +1469,9 @@ __global__ __launch_bounds__(MULTI_NT) void k_xcg3_multi(const Desc* __restrict_
 
 // ---------------------------------------------------------------------------
 // Finalize: fixed-order sum of the block partials of one batch entry, then
-// the scalar update of its iteration state.  One block per entry.
+// the scalar update of its iteration state.  One block per entry
+// (ffth_finalize.h).
 // ---------------------------------------------------------------------------
-constexpr int NT_FIN = 1024;
-__global__ __launch_bounds__(NT_FIN) void k_finalize(const Desc* __restrict__ descs, int op, int nblk_f, int nblk_i);
-
 // Volume averages of sigma = P_rhs + C:x (or C:(E + x)): 6 sums per block.
 template <bool ISO>
 __global__ __launch_bounds__(NT) void k_mean_stress(const Desc* __restrict__ descs, long nvox);

@@ -1,319 +1,13 @@
 // Finalize, volume-average and order-1 pointwise kernels (FP64).
+#include "ffth_finalize.h"
 #include "ffth_kernels.h"
 #include "ffth_launch.h"
 
 namespace ffth {
 
-__device__ static void fin_check(SolverState* st) {
-  const double r = st->res;
-  if (!(r == r) || r > 1e6) {
-    st->flag = FLAG_DIVERGED;
-    st->active = 0;
-  } else if (r < st->tol) {
-    st->flag = FLAG_CONVERGED;
-    st->active = 0;
-  } else if (st->iters >= st->max_iter) {
-    st->active = 0;  // flag stays RUNNING: not converged
-  }
-}
-
-// Partial sums are slot-major: part[k * nblk + block].  Each op names how
-// many slots of each array it reads.
-// Reduction asked of the FP32 inner solve that starts now.  The outer residual
-// must still drop by need = 0.8 tol / res (the margin covers the FP32
-// round-off of the correction); with at most tmin per solve that takes
-// k = ceil(log need / log tmin) more solves, and the reduction is split evenly
-// over them: every solve asks for need^(1/k) >= tmin.  Fewer restarts of the
-// Krylov iteration than a fixed tmin, and no solve tighter than the sweeps
-// still ahead require.
-__device__ static double inner_target(double tmin, double outer_tol, double outer_res) {
-  if (!(outer_res > 0.0) || !(tmin > 0.0) || !(tmin < 1.0)) return tmin;
-  const double need = 0.8 * outer_tol / outer_res;
-  if (!(need < 1.0)) return fmax(tmin, 0.5);
-  if (need >= tmin) return need;
-  const double k = ceil(log(need) / log(tmin));
-  return fmax(tmin, pow(need, 1.0 / k));
-}
-
-__device__ static void fin_slots(int op, int& nf, int& ni) {
-  nf = 0;
-  ni = 0;
-  switch (op) {
-    case FIN_LS_FIRST: nf = 1; ni = 1; break;
-    case FIN_BS: ni = 1; break;
-    case FIN_RESID_INIT: ni = 2; break;
-    case FIN_CG_ALPHA: nf = 1; break;
-    case FIN_CG_BETA: ni = 2; break;
-    case FIN_OUTER: case FIN_OUTER_P: nf = 1; ni = 2; break;
-    case FIN_PROJ: ni = 2; break;
-    case FIN_CG3_INIT: nf = 3; break;
-    case FIN_CG3: ni = 3; break;
-    case FIN_BI_INIT: ni = 1; break;
-    case FIN_BI_ALPHA: ni = 1; break;
-    case FIN_BI_OMEGA: ni = 5; break;
-    case FIN_SUMS_I: case FIN_O1RHS: ni = NRED; break;
-  }
-}
-
-// This thread's share (i = threadIdx.x mod NT_FIN) of n partials, in a fixed
-// order, with 8 independent accumulators so that 8 loads are in flight.
-__device__ static double strided_sum(const double* __restrict__ p, int n) {
-  double a[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  int i = threadIdx.x;
-  for (; i + 7 * NT_FIN < n; i += 8 * NT_FIN) {
-#pragma unroll
-    for (int u = 0; u < 8; ++u) a[u] += p[i + u * NT_FIN];
-  }
-  for (int u = 0; i < n; i += NT_FIN, ++u) a[u & 7] += p[i];
-  return ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
-}
-
-__global__ __launch_bounds__(NT_FIN) void k_finalize(const Desc* __restrict__ descs, int op, int nblk_f, int nblk_i) {
-  const Desc& d = descs[blockIdx.x];
-  SolverState* st = d.st;
-  if (!st->active) return;
-  if (nblk_i < 0) nblk_i = d.nblk_multi;   // multi-size launch: each entry's own block count
-  __shared__ double sf[NRED], si[NRED];
-  int nf, ni;
-  fin_slots(op, nf, ni);
-  double af[NRED], ai[NRED];
-#pragma unroll
-  for (int k = 0; k < NRED; ++k) {
-    af[k] = k < nf ? strided_sum(d.part_f + (long)k * nblk_f, nblk_f) : 0.0;
-    ai[k] = k < ni ? strided_sum(d.part_i + (long)k * nblk_i, nblk_i) : 0.0;
-  }
-  block_sums<NRED, NT_FIN>(af, sf);
-  block_sums<NRED, NT_FIN>(ai, si);
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  const double amu = fabs(d.mu0);
-  switch (op) {
-    case FIN_LS_FIRST: {
-      st->nb2 = si[0];
-      const double gs = st->gscale > 0.0 ? st->gscale : sqrt(sf[0]) / (2.0 * amu);
-      st->iters = 0;
-      st->first = 1;
-      st->res = 1.0;
-      if (sqrt(si[0]) <= st->guard_eps * gs) {
-        st->flag = FLAG_ZERO_RHS;
-        st->res = 0.0;
-        st->active = 0;
-      }
-      break;
-    }
-    case FIN_BS:
-      st->res = sqrt(si[0] / st->nb2);
-      st->iters++;
-      st->total++;
-      fin_check(st);
-      break;
-    case FIN_RESID_INIT:
-      st->rr = si[1];
-      st->res = sqrt(si[0] / st->nb2);
-      st->first = 1;
-      if (st->res < st->tol) {
-        st->flag = FLAG_CONVERGED;
-        st->active = 0;
-      }
-      break;
-    case FIN_CG_ALPHA: {
-      const double pq = sf[0];
-      if (!(pq > 0.0) || !(st->rr == st->rr)) {
-        st->flag = FLAG_DIVERGED;
-        st->active = 0;
-      } else {
-        st->alpha = st->rr / pq;
-      }
-      break;
-    }
-    case FIN_CG_BETA:
-      st->res = sqrt(si[1] / st->nb2);
-      st->iters++;
-      st->total++;
-      st->beta = si[0] / st->rr;
-      st->rr = si[0];
-      st->first = 0;
-      fin_check(st);
-      break;
-    case FIN_CG3_INIT: {
-      // three-term CG: rho_0 = <r,r>_C0, mu_0 = <r,Ar>_C0, gamma_0 = rho_0 / mu_0, omega_0 = 1
-      if (!(sf[1] > 0.0) || !(sf[0] > 0.0)) {
-        st->flag = sf[0] > 0.0 ? FLAG_DIVERGED : FLAG_CONVERGED;
-        st->active = 0;
-        break;
-      }
-      st->rr = sf[0];
-      st->alpha = sf[0] / sf[1];
-      st->beta = 1.0;
-      st->alpha_prev = 0.0;
-      st->beta_prev = 1.0;
-      st->xpend = 0;
-      st->best_res = 1.0;
-      st->best_it = 0;
-      st->stalled = 0;
-      st->first = 1;
-      break;
-    }
-    case FIN_CG3: {
-      // si = (rho_{k+1}, mu_{k+1}, ||r_{k+1}||^2); state holds rho_k, gamma_k, omega_k
-      st->res = sqrt(si[2] / st->nb2);
-      st->iters++;
-      st->total++;
-      const double g = si[0] / si[1];
-      const double den = 1.0 - (g / st->alpha) * (si[0] / st->rr) / st->beta;
-      const double om = 1.0 / den;
-      st->first = 0;
-      // stop before the scalars advance: a solve that stops keeps gamma_k,
-      // omega_k (and gamma_{k-1}, omega_{k-1}) of its last iteration k, from
-      // which k_cg3_finish forms x_{k+1} when k was even
-      if (st->res < st->tol) {
-        st->flag = FLAG_CONVERGED;
-        st->active = 0;
-      } else if (!(si[1] > 0.0) || !(om == om) || !(fabs(om) < 1e6) || !(st->res == st->res) || st->res > 1e6) {
-        st->flag = FLAG_DIVERGED;
-        st->active = 0;
-      } else if (st->total >= st->max_iter) {
-        // iteration budget (over all solves sharing the state: the mixed
-        // scheme's inner solves count together) spent; flag stays RUNNING
-        st->active = 0;
-      } else if (st->iters - st->best_it >= CG3_STALL && !(st->res < st->best_res)) {
-        // no new smallest residual for CG3_STALL iterations: the rounding
-        // floor of this precision; flag stays RUNNING
-        st->stalled = 1;
-        st->active = 0;
-      } else {
-        st->rr = si[0];
-        st->alpha_prev = st->alpha;
-        st->beta_prev = st->beta;
-        st->alpha = g;
-        st->beta = om;
-      }
-      if (st->res < st->best_res) {
-        st->best_res = st->res;
-        st->best_it = st->iters;
-      }
-      // x is formed on odd iterations: after an even last one (iters odd) it is owed
-      if (!st->active) st->xpend = st->iters & 1;
-      break;
-    }
-    case FIN_BI_INIT:
-      // BiCGSTAB start: r_0 = b - A b, rho = <r^, r_0> = ||r_0||^2
-      st->rr = si[0];
-      st->res = sqrt(si[0] / st->nb2);
-      st->alpha = st->omega = 1.0;
-      st->beta = 0.0;
-      st->first = 1;
-      st->pending = 0;
-      if (st->res < st->tol) {
-        st->flag = FLAG_CONVERGED;
-        st->active = 0;
-      }
-      break;
-    case FIN_BI_ALPHA: {
-      // alpha = rho / <r^, v>; the previous x update is applied by now
-      st->pending = 0;
-      const double rv = si[0];
-      if (!(fabs(rv) > 0.0) || !(rv == rv)) {
-        st->flag = FLAG_DIVERGED;
-        st->active = 0;
-      } else {
-        st->alpha = st->rr / rv;
-      }
-      break;
-    }
-    case FIN_BI_OMEGA: {
-      // si = (<t,s>, <t,t>, <r^,s>, <r^,t>, <s,s>)
-      const double ts = si[0], tt = si[1];
-      const double om = tt > 0.0 ? ts / tt : 0.0;
-      const double rho = si[2] - om * si[3];
-      const double r2 = fmax(0.0, si[4] - 2.0 * om * ts + om * om * tt);   // ||s - omega t||^2
-      st->omega = om;
-      st->pending = 1;
-      st->first = 0;
-      st->iters++;
-      st->total++;
-      st->res = sqrt(r2 / st->nb2);
-      if (st->res < st->tol) {
-        st->flag = FLAG_CONVERGED;
-        st->active = 0;
-      } else if (!(om != 0.0) || !(rho == rho) || !(fabs(rho) > 0.0)) {
-        st->flag = FLAG_DIVERGED;   // breakdown
-        st->active = 0;
-      } else {
-        st->beta = (rho / st->rr) * (st->alpha / om);
-        st->rr = rho;
-        fin_check(st);
-      }
-      break;
-    }
-    case FIN_PROJ: {
-      // compatible part of the FP64 residual: restart the FP32 inner solve on it
-      SolverState* in = d.st2;
-      st->proj++;
-      in->tol = inner_target(in->tol0, st->tol, st->res);
-      in->active = si[0] > 0.0 ? 1 : 0;
-      in->nb2 = si[0];
-      in->dscale = si[0] > 0.0 ? sqrt(si[0] * d.inv_nvox) : 1.0;
-      in->rr = si[1];
-      in->first = 1;
-      in->iters = 0;
-      in->xpend = 0;
-      in->flag = FLAG_RUNNING;
-      in->res = 1.0;
-      break;
-    }
-    case FIN_OUTER:
-    case FIN_OUTER_P: {
-      SolverState* in = d.st2;
-      if (st->iters == 0) {
-        st->nb2 = si[0];
-        const double gs = st->gscale > 0.0 ? st->gscale : sqrt(sf[0]) / (2.0 * amu);
-        if (sqrt(si[0]) <= st->guard_eps * gs) {
-          st->flag = FLAG_ZERO_RHS;
-          st->res = 0.0;
-          st->active = 0;
-          in->active = 0;
-          break;
-        }
-      }
-      st->res = sqrt(si[0] / st->nb2);
-      st->iters++;
-      st->fp64_apps++;
-      if (!(st->res == st->res) || st->res > 1e6) {
-        st->flag = FLAG_DIVERGED;
-        st->active = 0;
-      } else if (st->res < st->tol) {
-        st->flag = FLAG_CONVERGED;
-        st->active = 0;
-      } else if (st->iters >= st->max_iter) {
-        st->active = 0;
-      }
-      if (!st->active) {
-        in->active = 0;
-      } else if (op == FIN_OUTER_P) {
-        in->active = 0;  // the projection pass sets the inner solve up
-      } else {
-        in->active = 1;
-        in->tol = inner_target(in->tol0, st->tol, st->res);
-        in->nb2 = si[0];
-        in->dscale = si[0] > 0.0 ? sqrt(si[0] * d.inv_nvox) : 1.0;
-        in->rr = si[1];
-        in->first = 1;
-        in->iters = 0;
-        in->xpend = 0;
-        in->flag = FLAG_RUNNING;
-        in->res = 1.0;
-      }
-      break;
-    }
-    case FIN_SUMS_I:
-      for (int k = 0; k < NRED; ++k) st->sums[k] = si[k];
-      break;
-    case FIN_O1RHS:
-      for (int k = 0; k < NRED; ++k) st->sums[k] = si[k];
-      st->gscale = (sqrt(si[0]) + sqrt(si[1])) / (2.0 * amu);
-      break;
-  }
+template <int NTF>
+__global__ __launch_bounds__(NTF) void k_finalize(const Desc* __restrict__ descs, int op, int nblk_f, int nblk_i) {
+  finalize_entry<NTF, false>(descs[blockIdx.x], op, nblk_f, nblk_i);
 }
 
 template <bool ISO>
@@ -490,7 +184,12 @@ bool grid_supported(const int n[3]) {
 }
 
 hipError_t launch_finalize(int nbatch, hipStream_t s, const Desc* d, int op, int nblk_f, int nblk_i) {
-  hipLaunchKernelGGL(k_finalize, dim3(nbatch), dim3(NT_FIN), 0, s, d, op, nblk_f, nblk_i);
+  // few partials: a small block, whose reduction is shorter; the passes that
+  // carry a finalize run the same one, so a load's sums do not depend on which
+  if (nblk_f <= FIN_SMALL && nblk_i <= FIN_SMALL)
+    hipLaunchKernelGGL(k_finalize<256>, dim3(nbatch), dim3(256), 0, s, d, op, nblk_f, nblk_i);
+  else
+    hipLaunchKernelGGL(k_finalize<1024>, dim3(nbatch), dim3(1024), 0, s, d, op, nblk_f, nblk_i);
   return hipGetLastError();
 }
 

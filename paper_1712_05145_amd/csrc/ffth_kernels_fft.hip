@@ -1,17 +1,20 @@
 // Instantiations of the FFT-pass kernels for one precision (FFTH_REAL is
 // float or double, set on the compiler command line) and every axis length
-// in FFTH_SIZES.
+// in FFTH_SIZES, one kernel per translation unit (FFTH_PART: 0 z-pass, finish
+// kernels and tile shapes, 1 x-forward, 2 x-inverse, 3 fused three-term CG
+// pass, 4 y-pass).
 #include "ffth_kernels.h"
 #include "ffth_launch.h"
 
-#ifndef FFTH_REAL
-#error "compile with -DFFTH_REAL=float or -DFFTH_REAL=double"
+#if !defined(FFTH_REAL) || !defined(FFTH_PART)
+#error "compile with -DFFTH_REAL=float|double and -DFFTH_PART=0..4"
 #endif
 
 namespace ffth {
 
 using R = FFTH_REAL;
 
+#if FFTH_PART == 0
 template <typename T> int Launch<T>::x_rows(int n, int v) {
 #define FFTH_CASE(N) if (n == N) return ffth::xf_rows_v<T>(N, v);
   FFTH_SIZES(FFTH_CASE)
@@ -36,6 +39,7 @@ template <typename T> int Launch<T>::z_cols(int n, int v) {
 #undef FFTH_CASE
   return 0;
 }
+#endif
 
 // one launcher per (length, variant): the tile shape is a template argument
 // Storage type of the spectrum: full precision, or binary16 (FP32 only)
@@ -45,22 +49,22 @@ template <typename T, int N, int V, typename S = C2<T>>
 static void xfwd_v(bool iso, dim3 grid, hipStream_t s, const Desc* d, int mode, long rows, long nvox) {
   constexpr int RW = ffth::xf_rows_v<T>(N, V), TB = ffth::x_threads_v<T>(N, V);
   constexpr int PL = ffth::plan_of(V);
-  if (iso) hipLaunchKernelGGL((k_xfwd<T, N, true, RW, TB, S, PL>), grid, dim3(TB), 0, s, d, mode, rows, nvox);
-  else hipLaunchKernelGGL((k_xfwd<T, N, false, RW, TB, S, PL>), grid, dim3(TB), 0, s, d, mode, rows, nvox);
+  if (iso) hipLaunchKernelGGL((k_xfwd<T, N, true, RW, TB, S, PL>), grid, dim3(TB), 0, s, d, mode, rows, nvox, 1, 0);
+  else hipLaunchKernelGGL((k_xfwd<T, N, false, RW, TB, S, PL>), grid, dim3(TB), 0, s, d, mode, rows, nvox, 1, 0);
 }
 template <typename T, int N, int V, typename S = C2<T>>
 static void xinv_v(bool iso, dim3 grid, hipStream_t s, const Desc* d, int mode, long rows, long nvox) {
   constexpr int RW = ffth::xi_rows_v<T>(N, V), TB = ffth::xi_threads_v<T>(N, V);
   constexpr int PL = ffth::plan_of(V);
-  if (iso) hipLaunchKernelGGL((k_xinv<T, N, true, RW, TB, PL>), grid, dim3(TB), 0, s, d, mode, rows, nvox);
-  else hipLaunchKernelGGL((k_xinv<T, N, false, RW, TB, PL>), grid, dim3(TB), 0, s, d, mode, rows, nvox);
+  if (iso) hipLaunchKernelGGL((k_xinv<T, N, true, RW, TB, PL>), grid, dim3(TB), 0, s, d, mode, rows, nvox, 1, 0);
+  else hipLaunchKernelGGL((k_xinv<T, N, false, RW, TB, PL>), grid, dim3(TB), 0, s, d, mode, rows, nvox, 1, 0);
 }
 template <typename T, int N, int V, typename S = C2<T>>
 static void xcg3_v(bool iso, dim3 grid, hipStream_t s, const Desc* d, long rows, long nvox) {
   constexpr int RW = ffth::xi_rows_v<T>(N, V), TB = ffth::xi_threads_v<T>(N, V);
   constexpr int PL = ffth::plan_of(V);
-  if (iso) hipLaunchKernelGGL((k_xcg3<T, N, true, RW, TB, S, PL>), grid, dim3(TB), 0, s, d, rows, nvox);
-  else hipLaunchKernelGGL((k_xcg3<T, N, false, RW, TB, S, PL>), grid, dim3(TB), 0, s, d, rows, nvox);
+  if (iso) hipLaunchKernelGGL((k_xcg3<T, N, true, RW, TB, S, PL>), grid, dim3(TB), 0, s, d, rows, nvox, 1, 0);
+  else hipLaunchKernelGGL((k_xcg3<T, N, false, RW, TB, S, PL>), grid, dim3(TB), 0, s, d, rows, nvox, 1, 0);
 }
 template <typename T, int N, int V, typename S = C2<T>>
 static void ypass_v(dim3 grid, hipStream_t s, const Desc* d, int dir, int ncols, int ntiles) {
@@ -70,10 +74,11 @@ static void ypass_v(dim3 grid, hipStream_t s, const Desc* d, int dir, int ncols,
                      ntiles);
 }
 template <typename T, int N, int V, typename S = C2<T>>
-static void zpass_v(dim3 grid, hipStream_t s, const Desc* d, int op, int n1, int h, double scale) {
+static void zpass_v(dim3 grid, hipStream_t s, const Desc* d, int op, int n1, int h, double scale, bool plane, int fin,
+                    int nblk_f, int nblk_i) {
   constexpr int TK = ffth::z_cols_v<T>(N, V), TB = ffth::z_threads_v<T>(N, V);
   hipLaunchKernelGGL((k_zpass<T, N, TK, TB, true, 1, S, ffth::plan_of(V)>), grid, dim3(TB), 0, s, d, op, n1, h,
-                     scale);
+                     scale, plane ? 1 : 0, fin, nblk_f, nblk_i);
 }
 
 #define FFTH_VARIANTS_S(F, N, S, ...)        \
@@ -98,6 +103,7 @@ static void zpass_v(dim3 grid, hipStream_t s, const Desc* d, int op, int n1, int
     FFTH_VARIANTS_S(F, N, C2<T>, __VA_ARGS__)                            \
   }
 
+#if FFTH_PART == 1
 template <typename T> hipError_t Launch<T>::xfwd(int n2, bool iso, int v, bool h16, dim3 grid, hipStream_t s,
                                                 const Desc* d, int mode, long rows, long nvox) {
 #define FFTH_CASE(N)                                                          \
@@ -109,7 +115,9 @@ template <typename T> hipError_t Launch<T>::xfwd(int n2, bool iso, int v, bool h
 #undef FFTH_CASE
   return hipErrorInvalidValue;
 }
+#endif
 
+#if FFTH_PART == 2
 template <typename T> hipError_t Launch<T>::xinv(int n2, bool iso, int v, dim3 grid, hipStream_t s, const Desc* d,
                                                 int mode, long rows, long nvox) {
 #define FFTH_CASE(N)                                                          \
@@ -121,7 +129,9 @@ template <typename T> hipError_t Launch<T>::xinv(int n2, bool iso, int v, dim3 g
 #undef FFTH_CASE
   return hipErrorInvalidValue;
 }
+#endif
 
+#if FFTH_PART == 3
 template <typename T> hipError_t Launch<T>::xcg3(int n2, bool iso, int v, bool h16, dim3 grid, hipStream_t s,
                                                 const Desc* d, long rows, long nvox) {
 #define FFTH_CASE(N)                                                          \
@@ -133,7 +143,9 @@ template <typename T> hipError_t Launch<T>::xcg3(int n2, bool iso, int v, bool h
 #undef FFTH_CASE
   return hipErrorInvalidValue;
 }
+#endif
 
+#if FFTH_PART == 4
 template <typename T> hipError_t Launch<T>::ypass(int n1, int v, bool h16, dim3 grid, hipStream_t s, const Desc* d,
                                                  int dir, int ncols, int ntiles) {
 #define FFTH_CASE(N)                                                          \
@@ -145,12 +157,15 @@ template <typename T> hipError_t Launch<T>::ypass(int n1, int v, bool h16, dim3 
 #undef FFTH_CASE
   return hipErrorInvalidValue;
 }
+#endif
 
+#if FFTH_PART == 0
 template <typename T> hipError_t Launch<T>::zpass(int n0, int v, bool h16, dim3 grid, hipStream_t s, const Desc* d,
-                                                 int op, int n1, int h, double scale) {
+                                                 int op, int n1, int h, double scale, bool plane, int fin,
+                                                 int nblk_f, int nblk_i) {
 #define FFTH_CASE(N)                                                          \
   if (n0 == N) {                                                              \
-    FFTH_VARIANTS_H(zpass_v, N, grid, s, d, op, n1, h, scale)                \
+    FFTH_VARIANTS_H(zpass_v, N, grid, s, d, op, n1, h, scale, plane, fin, nblk_f, nblk_i)                \
     return hipGetLastError();                                                 \
   }
   FFTH_ZSIZES(FFTH_CASE)
@@ -167,6 +182,7 @@ template <typename T> hipError_t Launch<T>::cg3_finish(dim3 grid, hipStream_t s,
   hipLaunchKernelGGL((k_cg3_finish<T>), grid, dim3(NT), 0, s, d, n);
   return hipGetLastError();
 }
+#endif
 
 template struct Launch<R>;
 

@@ -1,0 +1,153 @@
+// Instantiations of the grouped passes for one precision (FFTH_REAL) and one
+// kernel (FFTH_PART: 0 z-pass, 1 x-forward, 2 x-inverse, 3 and 4 fused
+// three-term CG pass of isotropic and of general phases).
+#include "ffth_kernels.h"
+#include "ffth_launch.h"
+
+#if !defined(FFTH_REAL) || !defined(FFTH_PART)
+#error "compile with -DFFTH_REAL=float|double and -DFFTH_PART=0..4"
+#endif
+
+// axis lengths of the grouped passes: axes 0 and 1, axis 2
+#define FFTH_GROUP_N01(X) X(8) X(12) X(16) X(24) X(32) X(48) X(64) X(96) X(128)
+#define FFTH_GROUP_N2(X) FFTH_GROUP_N01(X) X(256)
+
+namespace ffth {
+
+using R = FFTH_REAL;
+constexpr bool DBL = sizeof(R) == 8;
+
+#if FFTH_PART == 0
+template <int N, int R2> static void gz_r(dim3 grid, bool h16, hipStream_t s, const Desc* d, int op, int n1,
+                                          double scale, int fin, int nblk_f, int nblk_i) {
+  if constexpr (gz_fits<R>(N, R2)) {
+    if constexpr (!DBL) {
+      if (h16) {
+        hipLaunchKernelGGL((k_gz<R, N, R2, NT, H2>), grid, dim3(NT), 0, s, d, op, n1, scale, fin, nblk_f, nblk_i);
+        return;
+      }
+    }
+    hipLaunchKernelGGL((k_gz<R, N, R2, NT, C2<R>>), grid, dim3(NT), 0, s, d, op, n1, scale, fin, nblk_f, nblk_i);
+  }
+}
+template <> hipError_t GLaunch<R>::gz(int n0, const GroupShape& g, bool h16, int nb, hipStream_t s, const Desc* d,
+                                      int op, int n1, double scale, int fin, int nblk_f, int nblk_i) {
+  const dim3 grid(g.zblocks + (fin >= 0 ? 1 : 0), nb);
+  switch (n0) {
+#define FFTH_CASE(N)                                                                          \
+  case N:                                                                                     \
+    if (g.r2 == 4) gz_r<N, 4>(grid, h16, s, d, op, n1, scale, fin, nblk_f, nblk_i);          \
+    if constexpr (!DBL) {                                                                     \
+      if (g.r2 == 6) gz_r<N, 6>(grid, h16, s, d, op, n1, scale, fin, nblk_f, nblk_i);        \
+      if (g.r2 == 8) gz_r<N, 8>(grid, h16, s, d, op, n1, scale, fin, nblk_f, nblk_i);        \
+    }                                                                                         \
+    return hipGetLastError();
+    FFTH_GROUP_N01(FFTH_CASE)
+#undef FFTH_CASE
+  }
+  return hipErrorInvalidValue;
+}
+
+static bool n01_compiled(int n) {
+#define FFTH_CASE(N) if (n == N) return true;
+  FFTH_GROUP_N01(FFTH_CASE)
+#undef FFTH_CASE
+  return false;
+}
+static bool n2_compiled(int n) {
+#define FFTH_CASE(N) if (n == N) return true;
+  FFTH_GROUP_N2(FFTH_CASE)
+#undef FFTH_CASE
+  return false;
+}
+#ifdef FFTH_GROUP_RULE   // defined for one of the two precisions
+template <typename T> static GroupShape shape_of(const int n[3]) {
+  GroupShape g;
+  const int r2 = group_r2<T>(n[1]);
+  if (!n01_compiled(n[0]) || !n01_compiled(n[1]) || !n2_compiled(n[2]) || r2 == 0) return g;
+  const int r1 = n[1] / r2;
+  if (!gx_fits<T>(n[2], r1) || !gz_fits<T>(n[0], r2)) return g;
+  const int kc = gz_kc<T>(n[0], r2), grp = group_count(n[2], r1);
+  g.on = true;
+  g.r1 = r1;
+  g.r2 = r2;
+  g.kcs = kc == 2 ? 1 : 0;
+  g.xblocks = (n[0] * r2 + grp - 1) / grp;
+  g.zblocks = n[2] / 2 / kc * r1;
+  return g;
+}
+GroupShape group_shape(const int n[3], bool dbl) { return dbl ? shape_of<double>(n) : shape_of<float>(n); }
+#endif
+#else
+// kernel launch for (axis-2 length, R1): f(integral constants).  R1 = 3, 6, 12
+// come up with R2 = 4 in FP64 (12, 24, 48 = 4 R1)
+template <int N> struct IC { static constexpr int v = N; };
+template <int N, class F> static bool for_r1(int r1, F&& f) {
+  switch (r1) {
+#define FFTH_R1(K) case K: if constexpr (gx_fits<R>(N, K)) { f(IC<N>(), IC<K>()); return true; } break;
+#define FFTH_R1D(K) case K: if constexpr (DBL && gx_fits<R>(N, K)) { f(IC<N>(), IC<K>()); return true; } break;
+    FFTH_R1(2) FFTH_R1(4) FFTH_R1(8) FFTH_R1(16)
+    FFTH_R1D(3) FFTH_R1D(6) FFTH_R1D(12)
+#undef FFTH_R1
+#undef FFTH_R1D
+  }
+  return false;
+}
+template <class F> static hipError_t for_shape(int n2, int r1, F&& f) {
+  bool ok = false;
+  switch (n2) {
+#define FFTH_CASE(N) case N: ok = for_r1<N>(r1, f); break;
+    FFTH_GROUP_N2(FFTH_CASE)
+#undef FFTH_CASE
+  }
+  return ok ? hipGetLastError() : hipErrorInvalidValue;
+}
+#endif
+
+#if FFTH_PART == 1
+template <> hipError_t GLaunch<R>::xfwd(int n2, const GroupShape& g, bool iso, bool h16, int nb, hipStream_t s,
+                                        const Desc* d, int mode, long rows, long nvox) {
+  const dim3 grid(g.xblocks, nb);
+  return for_shape(n2, g.r1, [&](auto n, auto r) {
+    constexpr int N = decltype(n)::v, K = decltype(r)::v, RW = gx_rows<R>(N, K);
+    if constexpr (!DBL) {
+      if (h16) {
+        if (iso) hipLaunchKernelGGL((k_xfwd<R, N, true, RW, NT, H2, 0, K>), grid, dim3(NT), 0, s, d, mode, rows, nvox, g.r2, g.kcs);
+        else hipLaunchKernelGGL((k_xfwd<R, N, false, RW, NT, H2, 0, K>), grid, dim3(NT), 0, s, d, mode, rows, nvox, g.r2, g.kcs);
+        return;
+      }
+    }
+    if (iso) hipLaunchKernelGGL((k_xfwd<R, N, true, RW, NT, C2<R>, 0, K>), grid, dim3(NT), 0, s, d, mode, rows, nvox, g.r2, g.kcs);
+    else hipLaunchKernelGGL((k_xfwd<R, N, false, RW, NT, C2<R>, 0, K>), grid, dim3(NT), 0, s, d, mode, rows, nvox, g.r2, g.kcs);
+  });
+}
+#elif FFTH_PART == 2
+template <> hipError_t GLaunch<R>::xinv(int n2, const GroupShape& g, bool iso, int nb, hipStream_t s, const Desc* d,
+                                        int mode, long rows, long nvox) {
+  const dim3 grid(g.xblocks, nb);
+  return for_shape(n2, g.r1, [&](auto n, auto r) {
+    constexpr int N = decltype(n)::v, K = decltype(r)::v, RW = gx_rows<R>(N, K);
+    if (iso) hipLaunchKernelGGL((k_xinv<R, N, true, RW, NT, 0, K>), grid, dim3(NT), 0, s, d, mode, rows, nvox, g.r2, g.kcs);
+    else hipLaunchKernelGGL((k_xinv<R, N, false, RW, NT, 0, K>), grid, dim3(NT), 0, s, d, mode, rows, nvox, g.r2, g.kcs);
+  });
+}
+#elif FFTH_PART >= 3
+// (one translation unit per material kind)
+constexpr bool ISO = FFTH_PART == 3;
+template <> template <> hipError_t GLaunch<R>::xcg3<ISO>(int n2, const GroupShape& g, bool h16, int nb, hipStream_t s,
+                                                        const Desc* d, long rows, long nvox) {
+  const dim3 grid(g.xblocks, nb);
+  return for_shape(n2, g.r1, [&](auto n, auto r) {
+    constexpr int N = decltype(n)::v, K = decltype(r)::v, RW = gx_rows<R>(N, K);
+    if constexpr (!DBL) {
+      if (h16) {
+        hipLaunchKernelGGL((k_xcg3<R, N, ISO, RW, NT, H2, 0, K>), grid, dim3(NT), 0, s, d, rows, nvox, g.r2, g.kcs);
+        return;
+      }
+    }
+    hipLaunchKernelGGL((k_xcg3<R, N, ISO, RW, NT, C2<R>, 0, K>), grid, dim3(NT), 0, s, d, rows, nvox, g.r2, g.kcs);
+  });
+}
+#endif
+
+}  // namespace ffth

@@ -37,8 +37,31 @@ template <typename T> struct Launch {
   static hipError_t cg3_finish(dim3 grid, hipStream_t s, const Desc* d, long n);
   static hipError_t ypass(int n1, int v, bool h16, dim3 grid, hipStream_t s, const Desc* d, int dir, int ncols,
                           int ntiles);
+  // plane: 2-D grid, n0 = the length of axis 1, n1 = 1 (no y-passes then); fin
+  // >= 0: one block more per load, which does that finalize
   static hipError_t zpass(int n0, int v, bool h16, dim3 grid, hipStream_t s, const Desc* d, int op, int n1, int h,
-                          double scale);
+                          double scale, bool plane = false, int fin = -1, int nblk_f = 0, int nblk_i = 0);
+};
+
+// Grouped passes (three passes per application instead of five): the x-passes
+// do the radix-r1 part of axis 1, the z-pass the radix-r2 part; 1 << kcs
+// values of k2 per chunk of the half spectrum; xblocks / zblocks per load.
+struct GroupShape {
+  bool on = false;
+  int r1 = 1, r2 = 1, kcs = 0, xblocks = 0, zblocks = 0;
+};
+// the rule: axis lengths, precision and the LDS of the tiles
+GroupShape group_shape(const int n[3], bool dbl);
+template <typename T> struct GLaunch {
+  static hipError_t xfwd(int n2, const GroupShape& g, bool iso, bool h16, int nb, hipStream_t s, const Desc* d,
+                         int mode, long rows, long nvox);
+  static hipError_t xinv(int n2, const GroupShape& g, bool iso, int nb, hipStream_t s, const Desc* d, int mode,
+                         long rows, long nvox);
+  template <bool ISO>
+  static hipError_t xcg3(int n2, const GroupShape& g, bool h16, int nb, hipStream_t s, const Desc* d, long rows,
+                         long nvox);
+  static hipError_t gz(int n0, const GroupShape& g, bool h16, int nb, hipStream_t s, const Desc* d, int op, int n1,
+                       double scale, int fin, int nblk_f, int nblk_i);
 };
 
 
@@ -48,16 +71,16 @@ hipError_t launch_finalize(int nbatch, hipStream_t s, const Desc* d, int op, int
 
 // Multi-size launches of the FP32 inner iteration (ffth_kernels_multi.hip)
 // for grids whose three axis lengths are all in the multi-size set (16, 24,
-// 32, 48, 64, 96, 128): one launch per pass over loads of different grids,
-// each descriptor carrying its grid (n) and, for the finalize, the block count
-// of its fused pass (nblk_multi).  The launch's blocks are listed by the
+// 32, 48, 64, 96, 128): one launch per grouped pass over loads of different
+// grids, each descriptor carrying its grid (n) and, for the finalize, the block
+// count of its fused pass (nblk_multi).  The launch's blocks are listed by the
 // segment table sg (one grid per segment, at most MULTI_SEGS; bpd from
-// multi_blocks: y, z, fused x blocks per load), grid = sg.off[sg.n] blocks.
+// multi_blocks: z, fused x blocks per load), grid = sg.off[sg.n] blocks and,
+// with fin >= 0, one more per load; lds: the largest of its grids' bytes.
 bool multi_grid(const int n[3]);
-void multi_blocks(const int n[3], int out[3]);
-hipError_t multi_ypass(const MultiSegs& sg, hipStream_t s, const Desc* d, int dir, bool h16);
-hipError_t multi_zpass(const MultiSegs& sg, hipStream_t s, const Desc* d, int op, bool h16);
-hipError_t multi_xcg3(const MultiSegs& sg, hipStream_t s, const Desc* d, bool iso, bool h16);
+void multi_blocks(const int n[3], int out[2], int lds[2]);
+hipError_t multi_gz(const MultiSegs& sg, int lds, hipStream_t s, const Desc* d, int op, bool h16, int fin);
+hipError_t multi_xcg3(const MultiSegs& sg, int lds, hipStream_t s, const Desc* d, bool iso, bool h16);
 hipError_t launch_mean_stress(bool iso, int nblk, int nbatch, hipStream_t s, const Desc* d, long nvox);
 hipError_t launch_order1_point(bool iso, int nblk, int nbatch, hipStream_t s, const Desc* d, const double* eps0,
                                const double* x1, long nvox);

@@ -65,12 +65,27 @@ int kchunk_of(int h) {
 
 template <typename T> hipError_t green_passes(const int n[3], hipStream_t st, const Desc* d) {
   const long rows = (long)n[0] * n[1], nvox = rows * n[2];
+  const GroupShape g = group_shape(n, sizeof(T) == 8);
+  if (g.on) {   // grouped passes, as a plan takes them
+    hipError_t e;
+    if ((e = GLaunch<T>::xfwd(n[2], g, true, false, 1, st, d, XF_COPY, rows, nvox)) != hipSuccess) return e;
+    if ((e = GLaunch<T>::gz(n[0], g, false, 1, st, d, OP_GAMMA, n[1], 1.0 / (double)nvox, -1, 0, 0)) != hipSuccess)
+      return e;
+    return GLaunch<T>::xinv(n[2], g, true, 1, st, d, XI_STORE, rows, nvox);
+  }
   const int h = n[2] / 2, kc = kchunk_of(h);
   const int xr = Launch<T>::x_rows(n[2], 0), xir = Launch<T>::xi_rows(n[2], 0);
   hipError_t e;
   if ((e = Launch<T>::xfwd(n[2], true, 0, false, dim3((unsigned)((rows + xr - 1) / xr), 1), st, d, XF_COPY, rows,
                            nvox)) != hipSuccess)
     return e;
+  if (n[0] == 1) {   // 2-D: one spectral pass
+    const int tk = Launch<T>::z_cols(n[1], 0);
+    if ((e = Launch<T>::zpass(n[1], 0, false, dim3((kc + tk - 1) / tk * (h / kc), 1), st, d, OP_GAMMA, 1, h,
+                              1.0 / (double)nvox, true)) != hipSuccess)
+      return e;
+    return Launch<T>::xinv(n[2], true, 0, dim3((unsigned)((rows + xir - 1) / xir), 1), st, d, XI_STORE, rows, nvox);
+  }
   const int ncols = kc * 6, nplanes = n[0] * (h / kc);
   const int cw = Launch<T>::y_cols(n[1], 0), ntiles = (ncols + cw - 1) / cw;
   if ((e = Launch<T>::ypass(n[1], 0, false, dim3(nplanes * ntiles, 1), st, d, -1, ncols, ntiles)) != hipSuccess)

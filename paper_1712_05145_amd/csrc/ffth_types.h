@@ -108,11 +108,15 @@ enum : int32_t {
 constexpr int MULTI_SEGS = 16;
 struct MultiSegs {
   int32_t n;
+  int32_t nload;              // loads of all segments (consecutive from first[0])
   int32_t first[MULTI_SEGS];
   int32_t bpd[MULTI_SEGS];
   int32_t off[MULTI_SEGS + 1];
 };
 
+// finalize blocks: entries with at most this many partials per slot (and every
+// multi-size launch) take 256 threads, the others 1024
+constexpr int FIN_SMALL = 1024;
 constexpr int NRED = 8;   // doubles per block in the partial-sum arrays
 constexpr int NVAR = 6;   // compiled tile shapes / radix plans per pass (autotuner candidates)
 

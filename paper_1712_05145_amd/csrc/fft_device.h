@@ -151,7 +151,7 @@ template <int R, int DIR, typename T> __device__ __forceinline__ void dft(C2<T>*
     // 8 = 2 x 4: Y_s = DFT4(a[2m+s]); X[k2 + 4 k1] = sum_s w2^{k1 s} w8^{k2 s} Y_s[k2]
     dft4<DIR>(a[0], a[2], a[4], a[6]);
     dft4<DIR>(a[1], a[3], a[5], a[7]);
-    C2<T> y1[4] = {a[1], cmul(a[3], w16<DIR, T>(2)), cmul(a[5], w16<DIR, T>(4)), cmul(a[7], w16<DIR, T>(6))};
+    C2<T> y1[4] = {a[1], cmul(a[3], w16<DIR, T>(2)), mul_i<DIR>(a[5]), cmul(a[7], w16<DIR, T>(6))};
     C2<T> y0[4] = {a[0], a[2], a[4], a[6]};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -168,7 +168,7 @@ template <int R, int DIR, typename T> __device__ __forceinline__ void dft(C2<T>*
       y[s][0] = b0;
       y[s][1] = s ? cmul(b1, w12<DIR, T>(s)) : b1;
       y[s][2] = s ? cmul(b2, w12<DIR, T>(2 * s)) : b2;
-      y[s][3] = s ? cmul(b3, w12<DIR, T>(3 * s)) : b3;
+      y[s][3] = s == 1 ? mul_i<DIR>(b3) : s == 2 ? b3 * T(-1) : b3;   // w12^3 = DIR i, w12^6 = -1
     }
 #pragma unroll
     for (int k2 = 0; k2 < 4; ++k2) {
@@ -187,7 +187,7 @@ template <int R, int DIR, typename T> __device__ __forceinline__ void dft(C2<T>*
       dft4<DIR>(b0, b1, b2, b3);
       y[s][0] = b0;
       y[s][1] = s ? cmul(b1, w16<DIR, T>(s)) : b1;
-      y[s][2] = s ? cmul(b2, w16<DIR, T>(2 * s)) : b2;
+      y[s][2] = s == 2 ? mul_i<DIR>(b2) : s ? cmul(b2, w16<DIR, T>(2 * s)) : b2;
       y[s][3] = s ? cmul(b3, w16<DIR, T>(3 * s)) : b3;
     }
 #pragma unroll
@@ -203,15 +203,34 @@ template <int R, int DIR, typename T> __device__ __forceinline__ void dft(C2<T>*
 }
 
 // ---------------------------------------------------------------------------
-// Twiddle table w[m] = exp(-2 pi i m / N), m in [0, N), built in LDS from
-// sincospi in FP64 (then rounded to T).
+// Twiddle tables w[m] = exp(-2 pi i m / N), m in [0, N): computed at compile
+// time (Taylor series in the first octant, FP64, then rounded to T) and copied
+// to LDS by every block.  Evaluating sincospi in the block cost each wave
+// about 90 of the 790 vector instructions of the 128-point fused pass.
 // ---------------------------------------------------------------------------
-template <typename T, int N, int NT> __device__ __forceinline__ void build_twiddles(C2<T>* tw) {
-  for (int m = threadIdx.x; m < N; m += NT) {
-    double s, c;
-    sincospi(-2.0 * (double)m / (double)N, &s, &c);
-    tw[m] = C2<T>{(T)c, (T)s};
+template <typename T, int N> struct TwTable {
+  C2<T> v[N];
+  constexpr TwTable() : v{} {
+    for (int m = 0; m < N; ++m) {
+      // angle = (pi/4) (o + r), r in [0, 1): odd octants are measured from their end
+      const int o = 8 * m / N, rem = 8 * m - o * N;
+      const double x = 0.78539816339744830962 * (double)(o & 1 ? N - rem : rem) / (double)N, x2 = x * x;
+      double c = 1.0, sn = 1.0;
+      for (int k = 20; k >= 2; k -= 2) {
+        c = 1.0 - c * x2 / (double)(k * (k - 1));
+        sn = 1.0 - sn * x2 / (double)(k * (k + 1));
+      }
+      sn *= x;
+      const double cc = (o + 1) & 2 ? sn : c, ss = (o + 1) & 2 ? c : sn;   // octants 1, 2, 5, 6 swap
+      v[m].x = (T)(o >= 2 && o < 6 ? -cc : cc);
+      v[m].y = (T)(o < 4 ? -ss : ss);
+    }
   }
+};
+template <typename T, int N> __device__ const TwTable<T, N> tw_table{};
+
+template <typename T, int N, int NT> __device__ __forceinline__ void build_twiddles(C2<T>* tw) {
+  for (int m = threadIdx.x; m < N; m += NT) tw[m] = tw_table<T, N>.v[m];
 }
 
 // ---------------------------------------------------------------------------

@@ -246,6 +246,7 @@ __device__ static void fin_rest(int op, const Desc& d, SolverState* st, const do
       in->active = si[0] > 0.0 ? 1 : 0;
       in->nb2 = si[0];
       in->dscale = si[0] > 0.0 ? sqrt(si[0] * d.inv_nvox) : 1.0;
+      in->idscale = 1.0 / in->dscale;
       in->rr = si[1];
       in->first = 1;
       in->iters = 0;
@@ -289,6 +290,7 @@ __device__ static void fin_rest(int op, const Desc& d, SolverState* st, const do
         in->tol = inner_target(in->tol0, st->tol, st->res);
         in->nb2 = si[0];
         in->dscale = si[0] > 0.0 ? sqrt(si[0] * d.inv_nvox) : 1.0;
+        in->idscale = 1.0 / in->dscale;
         in->rr = si[1];
         in->first = 1;
         in->iters = 0;

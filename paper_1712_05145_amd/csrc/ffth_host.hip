@@ -392,6 +392,8 @@ Desc base_desc(ffth_plan* P, int l) {
   d.part_i = part_ptr(P, 2 * l + 1);
   d.lam0 = P->lam0;
   d.mu0 = P->mu0;
+  d.gam_h = 0.5 / d.mu0;
+  d.gam_c = (d.lam0 + d.mu0) / (d.mu0 * (d.lam0 + 2.0 * d.mu0));
   d.nc = 6;
   d.inv_nvox = 1.0 / (double)P->nvox;
   d.tau_scale = 1.0;
@@ -411,7 +413,7 @@ SolverState make_state(double tol, int max_iter, double guard_eps, int active) {
   s.active = active;
   s.first = 1;
   s.res = 1.0;
-  s.dscale = 1.0;
+  s.dscale = s.idscale = 1.0;
   return s;
 }
 

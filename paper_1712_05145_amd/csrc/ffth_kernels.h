@@ -266,13 +266,13 @@ template <int R1> __device__ __forceinline__ long tile_row(long base, int rr, lo
 }
 
 // tw1[g R1 + q] = exp(-2 pi i b q / n1) of the block's groups
+// (every n1 with a grouped plan divides 384)
 template <typename T, int R1, int G, int NTB>
 __device__ __forceinline__ void build_group_twiddles(C2<T>* tw1, long g0, int r2) {
+  const int step = 384 / (R1 * r2);
   for (int m = threadIdx.x; m < G * R1; m += NTB) {
     const int b = (int)(g0 + m / R1) % r2, q = m % R1;
-    double s, c;
-    sincospi(-2.0 * (double)(b * q) / (double)(R1 * r2), &s, &c);
-    tw1[m] = C2<T>{(T)c, (T)s};
+    tw1[m] = tw_table<T, 384>.v[b * q * step];
   }
 }
 
@@ -382,7 +382,7 @@ __global__ __launch_bounds__(NTB) void k_xfwd(const Desc* __restrict__ descs, in
   const T* mat = mat_of<T>(d);
   double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0;
   const T beta = (T)d.st->beta;
-  const T ts = d.h16 ? (T)(d.tau_scale / d.st->dscale) : T(1);   // binary16 spectrum scale
+  const T ts = d.h16 ? (T)(d.tau_scale * d.st->idscale) : T(1);   // binary16 spectrum scale
   const bool first = d.st->first != 0;
   // correction fused into the FP64 residual pass (the three-term inner CG
   // leaves none after 0 iterations)
@@ -769,7 +769,7 @@ __device__ __forceinline__ void xcg3_tile(const Desc& d, int b, int nblk, long r
   T* xn = (T*)d.x;    // x_{k-1} in, x_{k+1} out (odd k)
   T* xo = (T*)d.x1;   // x_{k-2} in, x_k out
   const T* mat = mat_of<T>(d);
-  const T ts = d.h16 ? (T)(d.tau_scale / d.st->dscale) : T(1);   // binary16 spectrum scale
+  const T ts = d.h16 ? (T)(d.tau_scale * d.st->idscale) : T(1);   // binary16 spectrum scale
   double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0;
   for (int v = threadIdx.x; v < ROWS * N2; v += NTB) {
     const int rr = v / N2, i2 = v % N2;
@@ -1009,63 +1009,76 @@ __global__ __launch_bounds__(NTB) void k_ypass(const Desc* __restrict__ descs, i
 // z-pass: forward FFT along axis 0, spectral operator, inverse FFT.
 // Block = TK consecutive (i1, k2) columns x 6 components x all i0.
 // ---------------------------------------------------------------------------
+// 1 / x for a sum of squares of wave numbers (exact in T, >= 1).  FP32: the
+// hardware estimate (1 ulp) and one Newton step
+__device__ __forceinline__ float recip(float x) {
+  const float r = __builtin_amdgcn_rcpf(x);
+  return __builtin_fmaf(__builtin_fmaf(-x, r, 1.0f), r, r);
+}
+__device__ __forceinline__ double recip(double x) { return 1.0 / x; }
+
+// With integer wave vector k, |xi| = 2 pi |k|; every operator is a symmetric
+// (or plain) product with w, which needs 1 / |k|^2 only and no square root.
+// (gh, gc): the Green operator's constants of the entry.
 template <typename T>
-__device__ __forceinline__ void spectral_op(int op, T (&in)[6][2], T (&out)[6][2], T k0, T k1, T k2, double lam0,
-                                            double mu0, T scale) {
-  const T kk = k0 * k0 + k1 * k1 + k2 * k2;
-  const T inv = T(1) / sqrt(kk);
-  const T n[3] = {k0 * inv, k1 * inv, k2 * inv};
+__device__ __forceinline__ void spectral_op(int op, T (&in)[6][2], T (&out)[6][2], T k0, T k1, T k2, T gh, T gc,
+                                            T scale) {
+  const T i2 = recip(k0 * k0 + k1 * k1 + k2 * k2);
+  constexpr T I2PI = (T)(0.5 / 3.14159265358979323846);
   if (op == OP_GAMMA) {
-    // eta_hat = -[ (n x v + v x n) / (2 mu0) - c2 (n.v) n x n ],  v = tau_hat n
-    const T c2 = (T)((lam0 + mu0) / (mu0 * (lam0 + 2.0 * mu0)));
-    const T h = (T)(0.5 / mu0);
+    // eta_hat = -[ (n x v + v x n) / (2 mu0) - c2 (n.v) n x n ],  v = tau_hat n:
+    // with v = tau_hat k it is k x w + w x k, w = -h v / |k|^2 + c2 (k.v) k / (2 |k|^4)
+    const T a = -scale * gh * i2, b = T(0.5) * scale * gc * i2 * i2;
 #pragma unroll
     for (int ri = 0; ri < 2; ++ri) {
       const T t0 = in[0][ri], t1 = in[1][ri], t2 = in[2][ri], t3 = in[3][ri], t4 = in[4][ri], t5 = in[5][ri];
-      const T v0 = t0 * n[0] + t5 * n[1] + t4 * n[2];
-      const T v1 = t5 * n[0] + t1 * n[1] + t3 * n[2];
-      const T v2 = t4 * n[0] + t3 * n[1] + t2 * n[2];
-      const T s = (n[0] * v0 + n[1] * v1 + n[2] * v2) * c2;
-      out[0][ri] = -scale * (T(2) * h * n[0] * v0 - s * n[0] * n[0]);
-      out[1][ri] = -scale * (T(2) * h * n[1] * v1 - s * n[1] * n[1]);
-      out[2][ri] = -scale * (T(2) * h * n[2] * v2 - s * n[2] * n[2]);
-      out[3][ri] = -scale * (h * (n[1] * v2 + n[2] * v1) - s * n[1] * n[2]);
-      out[4][ri] = -scale * (h * (n[0] * v2 + n[2] * v0) - s * n[0] * n[2]);
-      out[5][ri] = -scale * (h * (n[0] * v1 + n[1] * v0) - s * n[0] * n[1]);
+      const T v0 = t0 * k0 + t5 * k1 + t4 * k2;
+      const T v1 = t5 * k0 + t1 * k1 + t3 * k2;
+      const T v2 = t4 * k0 + t3 * k1 + t2 * k2;
+      const T s = (k0 * v0 + k1 * v1 + k2 * v2) * b;
+      const T w0 = a * v0 + s * k0, w1 = a * v1 + s * k1, w2 = a * v2 + s * k2;
+      out[0][ri] = T(2) * k0 * w0;
+      out[1][ri] = T(2) * k1 * w1;
+      out[2][ri] = T(2) * k2 * w2;
+      out[3][ri] = k1 * w2 + k2 * w1;
+      out[4][ri] = k0 * w2 + k2 * w0;
+      out[5][ri] = k0 * w1 + k1 * w0;
     }
   } else if (op == OP_THETA) {
-    // theta_hat_ij = (i/|xi|) [ n_i n_j (g.n) - (g_i n_j + n_i g_j) ],  |xi| = 2 pi |k|
-    const T f = scale * inv * (T)(0.5 / 3.14159265358979323846);
-    T w[6][2];
+    // theta_hat_ij = (i/|xi|) [ n_i n_j (g.n) - (g_i n_j + n_i g_j) ] = i (k x w + w x k)_ij,
+    // w = (-g + (g.k) k / (2 |k|^2)) / (2 pi |k|^2)
+    const T f = scale * i2 * I2PI, h = T(0.5) * i2;
+    T u[6][2];
 #pragma unroll
     for (int ri = 0; ri < 2; ++ri) {
       const T g0 = in[0][ri], g1 = in[1][ri], g2 = in[2][ri];
-      const T gn = g0 * n[0] + g1 * n[1] + g2 * n[2];
-      w[0][ri] = n[0] * n[0] * gn - T(2) * g0 * n[0];
-      w[1][ri] = n[1] * n[1] * gn - T(2) * g1 * n[1];
-      w[2][ri] = n[2] * n[2] * gn - T(2) * g2 * n[2];
-      w[3][ri] = n[1] * n[2] * gn - (g1 * n[2] + n[1] * g2);
-      w[4][ri] = n[0] * n[2] * gn - (g0 * n[2] + n[0] * g2);
-      w[5][ri] = n[0] * n[1] * gn - (g0 * n[1] + n[0] * g1);
+      const T s = (g0 * k0 + g1 * k1 + g2 * k2) * h;
+      const T w0 = f * (s * k0 - g0), w1 = f * (s * k1 - g1), w2 = f * (s * k2 - g2);
+      u[0][ri] = T(2) * k0 * w0;
+      u[1][ri] = T(2) * k1 * w1;
+      u[2][ri] = T(2) * k2 * w2;
+      u[3][ri] = k1 * w2 + k2 * w1;
+      u[4][ri] = k0 * w2 + k2 * w0;
+      u[5][ri] = k0 * w1 + k1 * w0;
     }
 #pragma unroll
-    for (int c = 0; c < 6; ++c) {  // multiply by i f
-      out[c][0] = -f * w[c][1];
-      out[c][1] = f * w[c][0];
+    for (int c = 0; c < 6; ++c) {  // multiply by i
+      out[c][0] = -u[c][1];
+      out[c][1] = u[c][0];
     }
-  } else {  // OP_DISP: u_hat = (-i/|xi|) [ 2 eps_hat n - n (n . eps_hat n) ]
-    const T f = scale * inv * (T)(0.5 / 3.14159265358979323846);
+  } else {  // OP_DISP: u_hat = (-i/|xi|) [ 2 eps_hat n - n (n . eps_hat n) ], v = eps_hat k
+    const T f = scale * i2 * I2PI;
     T w[3][2];
 #pragma unroll
     for (int ri = 0; ri < 2; ++ri) {
       const T t0 = in[0][ri], t1 = in[1][ri], t2 = in[2][ri], t3 = in[3][ri], t4 = in[4][ri], t5 = in[5][ri];
-      const T v0 = t0 * n[0] + t5 * n[1] + t4 * n[2];
-      const T v1 = t5 * n[0] + t1 * n[1] + t3 * n[2];
-      const T v2 = t4 * n[0] + t3 * n[1] + t2 * n[2];
-      const T s = n[0] * v0 + n[1] * v1 + n[2] * v2;
-      w[0][ri] = T(2) * v0 - n[0] * s;
-      w[1][ri] = T(2) * v1 - n[1] * s;
-      w[2][ri] = T(2) * v2 - n[2] * s;
+      const T v0 = t0 * k0 + t5 * k1 + t4 * k2;
+      const T v1 = t5 * k0 + t1 * k1 + t3 * k2;
+      const T v2 = t4 * k0 + t3 * k1 + t2 * k2;
+      const T s = (k0 * v0 + k1 * v1 + k2 * v2) * i2;
+      w[0][ri] = T(2) * v0 - k0 * s;
+      w[1][ri] = T(2) * v1 - k1 * s;
+      w[2][ri] = T(2) * v2 - k2 * s;
     }
 #pragma unroll
     for (int c = 0; c < 3; ++c) {  // multiply by -i f
@@ -1077,33 +1090,36 @@ __device__ __forceinline__ void spectral_op(int op, T (&in)[6][2], T (&out)[6][2
 }
 
 // Tile bid (chunk bid / bpc, columns from (bid % bpc) TK) of one load; buf:
-// N0 * 6 TK LDS elements (16-byte aligned), tw: N0.
+// N0 * 6 TK LDS elements, tw: N0.
 // plane: a 2-D grid (axis 0 of length 1).  N0 is then the length of axis 1 (n1
 // is passed as 1), so this pass replaces both y-passes and the z-pass.
-template <typename T, int N0, int TK, int NTB, int V, typename S, int PLAN>
-__device__ __forceinline__ void zpass_tile(const Desc& d, int bid, int op, int n1, int h, double scale, C2<T>* buf,
-                                           C2<T>* tw, bool plane = false) {
+template <typename T, int N0, int TK, int NTB, typename S, int PLAN>
+__device__ __forceinline__ void zpass_tile(const Desc& d, int bid, int op, int n1, int h, FastDiv bpc, FastDiv kcd,
+                                           double scale, C2<T>* buf, C2<T>* tw, bool plane = false) {
+  // (rows are not padded apart: a wave's FFT accesses cover several of them)
   constexpr int W = TK * 6;
   build_twiddles<T, N0, NTB>(tw);
-  // columns (i1, k2 % kc) of one k2-chunk form a [N0][M][6] sub-array
-  const int kc = kchunk(h);
-  const long M = (long)n1 * kc;
-  const int bpc = (int)((M + TK - 1) / TK);            // blocks per chunk
-  const int chunk = bid / bpc;
-  const long m0 = (long)(bid % bpc) * TK;
+  // columns (i1, k2 % kc) of one k2-chunk form a [N0][M][6] sub-array of bpc blocks
+  const int kc = kcd.d, M = n1 * kc;
+  int r;
+  const int chunk = bpc.div(bid, r), m0 = r * TK;
   constexpr bool FULL = std::is_same<S, C2<T>>::value;
   // global accesses move GZ adjacent components (16 bytes in FP32, 8 in
   // binary16); W is even and so is every column's offset, so a group never
   // straddles a column
   constexpr int GZ = sizeof(T) == 4 ? 2 : 1;
-  S* spec = (S*)d.spec + (long)chunk * N0 * M * 6;
+  const int rs = M * 6;   // elements between rows i0
+  const long base = (long)chunk * N0 * rs + m0 * 6;
+  const S* src = (const S*)d.spec + base;
   // binary16 input; the output (after the spectral operator) goes to the FP32 copy
-  C2<T>* dst = (C2<T>*)(FULL ? d.spec : d.spec2) + (long)chunk * N0 * M * 6;
+  C2<T>* dst = (C2<T>*)(FULL ? d.spec : d.spec2) + base;
+  const int wlim = (M - m0) * 6;   // elements of a row inside the chunk (ragged last tile)
   // binary16 storage: the spectral operator also restores the scale of the
   // forward transforms (the descriptor's factor times the right-hand side's
   // RMS replaces 1/N)
   // (2-D: no forward y-pass divided by the axis length)
-  const T sc = FULL ? (T)scale : (T)(d.op_scale * d.st->dscale / (plane ? N0 : 1));
+  const T sc = FULL ? (T)scale : (T)(d.op_scale * d.st->dscale * (plane ? 1.0 / N0 : 1.0));
+  const T gh = (T)d.gam_h, gc = (T)d.gam_c;
   // all of a thread's loads are issued before the first LDS write, so their
   // latencies overlap (the tile's rows are far apart in memory)
   constexpr int NA = N0 * W / GZ, NL = (NA + NTB - 1) / NTB;
@@ -1113,9 +1129,9 @@ __device__ __forceinline__ void zpass_tile(const Desc& d, int bid, int op, int n
     for (int k = 0; k < NL; ++k) {
       const int v = threadIdx.x + k * NTB;
       const int i0 = v / (W / GZ), w = (v % (W / GZ)) * GZ;
-      if ((NA % NTB == 0 || v < NA) && m0 + w / 6 < M) {
-        if constexpr (FULL) load_v<T, GZ>(spec + ((long)i0 * M + m0) * 6 + w, a[k]);
-        else hload_g<T, GZ>(spec + ((long)i0 * M + m0) * 6 + w, a[k]);
+      if ((NA % NTB == 0 || v < NA) && w < wlim) {
+        if constexpr (FULL) load_v<T, GZ>(src + (long)i0 * rs + w, a[k]);
+        else hload_g<T, GZ>(src + (long)i0 * rs + w, a[k]);
       } else {
 #pragma unroll
         for (int q = 0; q < GZ; ++q) a[k][q] = C2<T>{0, 0};
@@ -1132,51 +1148,47 @@ __device__ __forceinline__ void zpass_tile(const Desc& d, int bid, int op, int n
     }
   }
   __syncthreads();
-  if constexpr (N0 > 1) lds_fft<T, N0, W, NTB, W, 1, true, false, -1, V, PLAN>(buf, tw);
+  if constexpr (N0 > 1) lds_fft<T, N0, W, NTB, W, 1, true, false, -1, 1, PLAN>(buf, tw);
+  const int k1b = kcd.div(m0, r), k2b = r;   // first column
   for (int v = threadIdx.x; v < N0 * TK; v += NTB) {
     const int k0 = v / TK, col = v % TK;
-    const long m = m0 + col;
-    if (m >= M) continue;
-    const int k1 = (int)(m / kc), k2 = chunk * kc + (int)(m % kc);
+    if (m0 + col >= M) continue;
+    int k1 = k1b, k2 = k2b + col;
+    if (TK > 1) {
+      for (; k2 >= kc; ++k1) k2 -= kc;
+    }
+    k2 += chunk * kc;
     const bool nyq = ((N0 % 2 == 0) && k0 == N0 / 2) || ((n1 % 2 == 0) && k1 == n1 / 2);
     const int k0s = k0 < (N0 + 1) / 2 ? k0 : k0 - N0;
     const int k1s = k1 < (n1 + 1) / 2 ? k1 : k1 - n1;
     C2<T>* e = buf + k0 * W + col * 6;
     T in[6][2], out[6][2];
 #pragma unroll
-    for (int c = 0; c < 6; c += V) {
-      C2<T> a[V];
-      load_v<T, V>(e + c, a);
-#pragma unroll
-      for (int q = 0; q < V; ++q) {
-        in[c + q][0] = a[q].x;
-        in[c + q][1] = a[q].y;
-      }
+    for (int c = 0; c < 6; ++c) {
+      in[c][0] = e[c].x;
+      in[c][1] = e[c].y;
     }
     if (nyq || (k0s == 0 && k1s == 0 && k2 == 0)) {
 #pragma unroll
       for (int c = 0; c < 6; ++c) out[c][0] = out[c][1] = T(0);
     } else {
-      spectral_op<T>(op, in, out, (T)(plane ? 0 : k0s), (T)(plane ? k0s : k1s), (T)k2, d.lam0, d.mu0, sc);
+      spectral_op<T>(op, in, out, (T)(plane ? 0 : k0s), (T)(plane ? k0s : k1s), (T)k2, gh, gc, sc);
     }
 #pragma unroll
-    for (int c = 0; c < 6; c += V) {
-      C2<T> a[V];
-#pragma unroll
-      for (int q = 0; q < V; ++q) a[q] = C2<T>{out[c + q][0], out[c + q][1]};
-      store_v<T, V>(e + c, a);
-    }
+    for (int c = 0; c < 6; ++c) e[c] = C2<T>{out[c][0], out[c][1]};
   }
   __syncthreads();
-  if constexpr (N0 > 1) lds_fft<T, N0, W, NTB, W, 1, true, false, +1, V, PLAN>(buf, tw);
-  for (int v = threadIdx.x; v < N0 * W / GZ; v += NTB) {
+  if constexpr (N0 > 1) lds_fft<T, N0, W, NTB, W, 1, true, false, +1, 1, PLAN>(buf, tw);
+#pragma unroll
+  for (int k = 0; k < NL; ++k) {
+    const int v = threadIdx.x + k * NTB;
     const int i0 = v / (W / GZ), w = (v % (W / GZ)) * GZ;
-    if (m0 + w / 6 < M) {
+    if ((NA % NTB == 0 || v < NA) && w < wlim) {
       C2<T> a[GZ];
 #pragma unroll
       for (int q = 0; q < GZ; ++q) a[q] = buf[i0 * W + w + q];
       if constexpr (FULL || TK % 4 != 0) {
-        store_v<T, GZ>(dst + ((long)i0 * M + m0) * 6 + w, a);
+        store_v<T, GZ>(dst + (long)i0 * rs + w, a);
       } else {
         // the FP32 copy after the operator goes to its own buffer: streamed
         // with the non-temporal hint, which pays only when every row segment
@@ -1184,7 +1196,7 @@ __device__ __forceinline__ void zpass_tile(const Desc& d, int bid, int op, int n
         static_assert(GZ == 2, "binary16 input implies FP32 pairs");
         typedef float f4 __attribute__((ext_vector_type(4)));
         const f4 o = {a[0].x, a[0].y, a[1].x, a[1].y};
-        __builtin_nontemporal_store(o, (f4*)(dst + ((long)i0 * M + m0) * 6 + w));
+        __builtin_nontemporal_store(o, (f4*)(dst + (long)i0 * rs + w));
       }
     }
   }
@@ -1205,18 +1217,18 @@ __device__ __forceinline__ bool carried_finalize(const Desc& d, int fin, int nbl
   return true;
 }
 
-template <typename T, int N0, int TK = z_cols<T>(N0), int NTB = NT, bool REMAP = true, int V = vec_width<T>(),
-          typename S = C2<T>, int PLAN = 0>
-__global__ __launch_bounds__(NTB) void k_zpass(const Desc* __restrict__ descs, int op, int n1, int h, double scale,
-                                               int plane, int fin, int nblk_f, int nblk_i) {
+template <typename T, int N0, int TK = z_cols<T>(N0), int NTB = NT, typename S = C2<T>, int PLAN = 0>
+__global__ __launch_bounds__(NTB) void k_zpass(const Desc* __restrict__ descs, int op, int n1, int h, FastDiv bpc,
+                                               FastDiv kcd, double scale, int plane, int fin, int nblk_f,
+                                               int nblk_i) {
   __shared__ __attribute__((aligned(16))) C2<T> buf[N0 * TK * 6];
   __shared__ C2<T> tw[N0];
   const Desc& d = descs[blockIdx.y];
   if (!d.st->active) return;
   int bid, nblk;
   if (carried_finalize<NTB>(d, fin, nblk_f, nblk_i, bid, nblk)) return;
-  if (REMAP) bid = xcd_tile(bid, nblk);
-  zpass_tile<T, N0, TK, NTB, V, S, PLAN>(d, bid, op, n1, h, scale, buf, tw, plane != 0);
+  bid = xcd_tile(bid, nblk);
+  zpass_tile<T, N0, TK, NTB, S, PLAN>(d, bid, op, n1, h, bpc, kcd, scale, buf, tw, plane != 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -1234,8 +1246,9 @@ template <typename T> __host__ __device__ constexpr int gz_kc(int n0, int r2) { 
 template <typename T, int N0, int R2, int KC, int NTB, int DIR>
 __device__ __forceinline__ void gz_axis1(C2<T>* buf) {
   constexpr int C = KC * 6, WP = R2 * C + 1;
+  // lanes along i0: WP apart, every bank once
   for (int v = threadIdx.x; v < N0 * C; v += NTB) {
-    C2<T>* e = buf + (v / C) * WP + v % C;
+    C2<T>* e = buf + v % N0 * WP + v / N0;
     C2<T> x[R2];
 #pragma unroll
     for (int b = 0; b < R2; ++b) x[b] = e[b * C];
@@ -1246,19 +1259,29 @@ __device__ __forceinline__ void gz_axis1(C2<T>* buf) {
 }
 
 template <typename T, int N0, int R2, int KC, int NTB, typename S>
-__device__ __forceinline__ void gz_tile(const Desc& d, int bid, int op, int n1, double scale, C2<T>* buf, C2<T>* tw) {
+__device__ __forceinline__ void gz_tile(const Desc& d, int bid, int op, int n1, double scale, int kcs, C2<T>* buf,
+                                        C2<T>* tw) {
   constexpr int W = KC * R2 * 6, WP = W + 1;
   constexpr bool FULL = std::is_same<S, C2<T>>::value;
-  constexpr int GZ = FULL ? (sizeof(T) == 4 ? 2 : 1) : 4;   // 16 bytes per access
+  constexpr int GZ = FULL && sizeof(T) == 8 ? 1 : 2;   // values per access: a segment of the tile holds 6 KC
   build_twiddles<T, N0, NTB>(tw);
-  const int r1 = n1 / R2, chunk = bid / r1, q = bid - chunk * r1;
-  const long rs = (long)n1 * KC * 6;   // elements between rows i0
-  const long base = (long)chunk * N0 * rs + (long)q * W;
+  // blocks of one chunk and q, which share its lines, are neighbours
+  const int r1 = n1 / R2, per = (1 << kcs) / KC;
+  const int kk = bid % per * KC, cq = bid / per, chunk = cq / r1, q = cq - chunk * r1;
+  const int k20 = (chunk << kcs) + kk;
+  const int bs = 6 << kcs;                        // elements between values b
+  const int rs = n1 * bs;                         // and between rows i0
+  const long base = (long)chunk * N0 * rs + (long)q * R2 * bs + kk * 6;
   const S* src = (const S*)d.spec + base;
   C2<T>* dst = (C2<T>*)(FULL ? d.spec : d.spec2) + base;
+  auto at = [&](int v) {   // offset of access v of the tile
+    const int w = v % (W / GZ) * GZ;
+    return (long)(v / (W / GZ)) * rs + w / (KC * 6) * bs + w % (KC * 6);
+  };
   // binary16 storage: the operator restores the scale of the forward
   // transforms (the x-pass divided by R1 only)
   const T sc = FULL ? (T)scale : (T)(d.op_scale * d.st->dscale / R2);
+  const T gh = (T)d.gam_h, gc = (T)d.gam_c;
   constexpr int NA = N0 * W / GZ, NL = (NA + NTB - 1) / NTB;
   {
     C2<T> a[NL][GZ];
@@ -1266,7 +1289,7 @@ __device__ __forceinline__ void gz_tile(const Desc& d, int bid, int op, int n1, 
     for (int k = 0; k < NL; ++k) {
       const int v = threadIdx.x + k * NTB;
       if (NA % NTB == 0 || v < NA) {
-        const S* s = src + (v / (W / GZ)) * rs + (v % (W / GZ)) * GZ;
+        const S* s = src + at(v);
         if constexpr (FULL) load_v<T, GZ>(s, a[k]);
         else hload_g<T, GZ>(s, a[k]);
       } else {
@@ -1288,8 +1311,10 @@ __device__ __forceinline__ void gz_tile(const Desc& d, int bid, int op, int n1, 
   __syncthreads();
   lds_fft<T, N0, W, NTB, WP, 1, true, false, -1>(buf, tw);
   for (int v = threadIdx.x; v < N0 * R2 * KC; v += NTB) {
-    const int k0 = v / (R2 * KC), m = v % (R2 * KC), p = m / KC;
-    const int k1 = q + r1 * p, k2 = chunk * KC + m % KC;
+    const int k0 = v % N0;
+    int m = v / N0;   // one value per wave where N0 is a multiple of it
+    if constexpr (N0 % 64 == 0) m = __builtin_amdgcn_readfirstlane(m);
+    const int p = m / KC, k1 = q + r1 * p, k2 = k20 + m % KC;
     const bool nyq = (N0 % 2 == 0 && k0 == N0 / 2) || (n1 % 2 == 0 && k1 == n1 / 2);
     const int k0s = k0 < (N0 + 1) / 2 ? k0 : k0 - N0;
     const int k1s = k1 < (n1 + 1) / 2 ? k1 : k1 - n1;
@@ -1304,7 +1329,7 @@ __device__ __forceinline__ void gz_tile(const Desc& d, int bid, int op, int n1, 
 #pragma unroll
       for (int c = 0; c < 6; ++c) out[c][0] = out[c][1] = T(0);
     } else {
-      spectral_op<T>(op, in, out, (T)k0s, (T)k1s, (T)k2, d.lam0, d.mu0, sc);
+      spectral_op<T>(op, in, out, (T)k0s, (T)k1s, (T)k2, gh, gc, sc);
     }
 #pragma unroll
     for (int c = 0; c < 6; ++c) e[c] = C2<T>{out[c][0], out[c][1]};
@@ -1319,39 +1344,54 @@ __device__ __forceinline__ void gz_tile(const Desc& d, int bid, int op, int n1, 
     C2<T> a[GS];
 #pragma unroll
     for (int g = 0; g < GS; ++g) a[g] = buf[i0 * WP + w + g];
-    store_v<T, GS>(dst + i0 * rs + w, a);
+    store_v<T, GS>(dst + (long)i0 * rs + w / (KC * 6) * bs + w % (KC * 6), a);
   }
 }
 
 // LDS elements of the tile
 template <typename T> constexpr int gz_elems(int n0, int r2) { return n0 * (gz_kc<T>(n0, r2) * r2 * 6 + 1); }
 
+// FP64: 512 threads for the largest tiles, which leave few blocks per CU.
+// FP32 keeps 256 (N0 = 128, R2 = 8: 146 us, with 512 137): the multi-size
+// launches run the same tile with the same thread count, and the compiler
+// contracts its products the same way only then.
+template <typename T> constexpr int gz_threads(int n0, int r2) {
+  return sizeof(T) == 8 && gz_elems<T>(n0, r2) >= 4096 ? 512 : NT;
+}
+
 template <typename T, int N0, int R2, int NTB, typename S>
-__global__ __launch_bounds__(NTB) void k_gz(const Desc* __restrict__ descs, int op, int n1, double scale, int fin,
-                                            int nblk_f, int nblk_i) {
+__global__ __launch_bounds__(NTB) void k_gz(const Desc* __restrict__ descs, int op, int n1, double scale, int kcs,
+                                            int fin, int nblk_f, int nblk_i) {
   __shared__ __attribute__((aligned(16))) C2<T> buf[gz_elems<T>(N0, R2)];
   __shared__ C2<T> tw[N0];
   const Desc& d = descs[blockIdx.y];
   if (!d.st->active) return;
   int bid, nblk;
   if (carried_finalize<NTB>(d, fin, nblk_f, nblk_i, bid, nblk)) return;
-  gz_tile<T, N0, R2, gz_kc<T>(N0, R2), NTB, S>(d, xcd_tile(bid, nblk), op, n1, scale, buf, tw);
+  gz_tile<T, N0, R2, gz_kc<T>(N0, R2), NTB, S>(d, xcd_tile(bid, nblk), op, n1, scale, kcs, buf, tw);
 }
 
 // Which grids take the grouped passes: axis lengths whose kernels are compiled
-// and whose tiles leave room for three blocks per CU (R2 0: not grouped).
-// FP64 tiles are twice as large: R2 = 4 balances the two passes there.
-constexpr int GROUP_LDS = 56 * 1024;
+// and whose tiles leave room for three blocks per CU (FP64: two).  R2 (0: not
+// grouped) balances the two passes; measured with six loads, us per three-term
+// iteration: FP64 64^3 R2 = 8 138, 4 144; 48^3 4 73, 8 78; 96^3 8 520 (five
+// passes 595).  Longer axes 1 leave no R2 whose tiles fit both passes.
+template <typename T> constexpr int group_lds() { return sizeof(T) == 8 ? 80 * 1024 : 56 * 1024; }
 template <typename T> __host__ __device__ constexpr int group_r2(int n1) {
-  if (sizeof(T) == 8) return n1 >= 8 && n1 <= 64 ? 4 : 0;
+  if (sizeof(T) == 8) return n1 == 64 || n1 == 96 ? 8 : n1 >= 8 && n1 <= 48 ? 4 : 0;
   return n1 == 8 ? 4 : n1 == 16 || n1 == 32 || n1 == 64 || n1 == 128 ? 8 : n1 == 12 || n1 == 24 || n1 == 48 || n1 == 96 ? 6 : 0;
 }
+// log2 of the k2 values per chunk: the x-passes move segments of 6 << kcs
+// values, the z-pass rows of 6 R2 values broken into segments of 6 kc.  Wider
+// chunks speed up the one and slow down the other (128^3, six loads, kcs = 0,
+// 1, 2: x 467, 442, 407 us, z 124, 137, 168; 96^3: 193, 185, 181 and 69, 69, 69).
+__host__ __device__ constexpr int group_kcs(int r2, int h) { return r2 == 6 && h % 4 == 0 ? 2 : 1; }
 template <typename T> constexpr int gx_rows(int n2, int r1) { return group_count(n2, r1) * r1; }
 template <typename T> constexpr bool gx_fits(int n2, int r1) {
-  return gx_rows<T>(n2, r1) * 3 * (n2 + n2 / 16) * 2 * (int)sizeof(T) <= GROUP_LDS;
+  return gx_rows<T>(n2, r1) * 3 * (n2 + n2 / 16) * 2 * (int)sizeof(T) <= group_lds<T>();
 }
 template <typename T> constexpr bool gz_fits(int n0, int r2) {
-  return gz_elems<T>(n0, r2) * 2 * (int)sizeof(T) <= GROUP_LDS;
+  return gz_elems<T>(n0, r2) * 2 * (int)sizeof(T) <= group_lds<T>();
 }
 
 // ---------------------------------------------------------------------------
@@ -1422,15 +1462,15 @@ __global__ __launch_bounds__(MULTI_NT) void k_gz_multi(const Desc* __restrict__ 
   if (di < 0) return;
   const Desc& d = descs[di];
   if (!d.st->active) return;
-  const int n1 = d.n[1];
+  const int n1 = d.n[1], kcs = group_kcs(group_r2<float>(n1), d.n[2] / 2);
   C2<float>* tw = (C2<float>*)lds;   // N0 values, then the tile
   switch (d.n[0]) {
 #define FFTH_MULTI_Z(N)                                                                                               \
   case N:                                                                                                             \
     if (group_r2<float>(n1) == 8)                                                                                     \
-      gz_tile<float, N, 8, gz_kc<float>(N, 8), MULTI_NT, S>(d, bid, op, n1, d.inv_nvox, tw + N, tw);                 \
+      gz_tile<float, N, 8, gz_kc<float>(N, 8), MULTI_NT, S>(d, bid, op, n1, d.inv_nvox, kcs, tw + N, tw);                 \
     else                                                                                                              \
-      gz_tile<float, N, 6, gz_kc<float>(N, 6), MULTI_NT, S>(d, bid, op, n1, d.inv_nvox, tw + N, tw);                 \
+      gz_tile<float, N, 6, gz_kc<float>(N, 6), MULTI_NT, S>(d, bid, op, n1, d.inv_nvox, kcs, tw + N, tw);                 \
     break;
     FFTH_MULTI_SIZES(FFTH_MULTI_Z)
 #undef FFTH_MULTI_Z
@@ -1444,8 +1484,8 @@ __device__ __forceinline__ void multi_x_tile(const Desc& d, int b, C2<float>* ld
   constexpr int ROWS = gx_rows<float>(N, R1);
   const int nb = (d.n[0] * r2 + ROWS / R1 - 1) / (ROWS / R1);
   const long rows = (long)d.n[0] * d.n[1];
-  const int kcs = d.n[0] * r2 * 48 <= 16384 ? 1 : 0;   // gz_kc<float>
-  xcg3_tile<float, N, ISO, ROWS, MULTI_NT, S, 0, R1>(d, b, nb, rows, rows * N, lds + N + ROWS, lds, lds + N, r2, kcs);
+  xcg3_tile<float, N, ISO, ROWS, MULTI_NT, S, 0, R1>(d, b, nb, rows, rows * N, lds + N + ROWS, lds, lds + N, r2,
+                                                       group_kcs(r2, N / 2));
 }
 template <bool ISO, typename S>
 __global__ __launch_bounds__(MULTI_NT) void k_xcg3_multi(const Desc* __restrict__ descs, MultiSegs sg) {

@@ -74,11 +74,12 @@ static void ypass_v(dim3 grid, hipStream_t s, const Desc* d, int dir, int ncols,
                      ntiles);
 }
 template <typename T, int N, int V, typename S = C2<T>>
-static void zpass_v(dim3 grid, hipStream_t s, const Desc* d, int op, int n1, int h, double scale, bool plane, int fin,
-                    int nblk_f, int nblk_i) {
+static void zpass_v(dim3 grid, hipStream_t s, const Desc* d, int op, int n1, int h, double scale, bool plane,
+                    int fin, int nblk_f, int nblk_i) {
   constexpr int TK = ffth::z_cols_v<T>(N, V), TB = ffth::z_threads_v<T>(N, V);
-  hipLaunchKernelGGL((k_zpass<T, N, TK, TB, true, 1, S, ffth::plan_of(V)>), grid, dim3(TB), 0, s, d, op, n1, h,
-                     scale, plane ? 1 : 0, fin, nblk_f, nblk_i);
+  const int kc = kchunk(h), bpc = (int)(((long)n1 * kc + TK - 1) / TK);
+  hipLaunchKernelGGL((k_zpass<T, N, TK, TB, S, ffth::plan_of(V)>), grid, dim3(TB), 0, s, d, op, n1, h,
+                     FastDiv::of(bpc), FastDiv::of(kc), scale, plane ? 1 : 0, fin, nblk_f, nblk_i);
 }
 
 #define FFTH_VARIANTS_S(F, N, S, ...)        \
@@ -161,8 +162,8 @@ template <typename T> hipError_t Launch<T>::ypass(int n1, int v, bool h16, dim3 
 
 #if FFTH_PART == 0
 template <typename T> hipError_t Launch<T>::zpass(int n0, int v, bool h16, dim3 grid, hipStream_t s, const Desc* d,
-                                                 int op, int n1, int h, double scale, bool plane, int fin,
-                                                 int nblk_f, int nblk_i) {
+                                                 int op, int n1, int h, double scale, bool plane,
+                                                 int fin, int nblk_f, int nblk_i) {
 #define FFTH_CASE(N)                                                          \
   if (n0 == N) {                                                              \
     FFTH_VARIANTS_H(zpass_v, N, grid, s, d, op, n1, h, scale, plane, fin, nblk_f, nblk_i)                \

@@ -19,28 +19,29 @@ constexpr bool DBL = sizeof(R) == 8;
 
 #if FFTH_PART == 0
 template <int N, int R2> static void gz_r(dim3 grid, bool h16, hipStream_t s, const Desc* d, int op, int n1,
-                                          double scale, int fin, int nblk_f, int nblk_i) {
+                                          double scale, int kcs, int fin, int nblk_f, int nblk_i) {
   if constexpr (gz_fits<R>(N, R2)) {
+    constexpr int TB = gz_threads<R>(N, R2);
     if constexpr (!DBL) {
       if (h16) {
-        hipLaunchKernelGGL((k_gz<R, N, R2, NT, H2>), grid, dim3(NT), 0, s, d, op, n1, scale, fin, nblk_f, nblk_i);
+        hipLaunchKernelGGL((k_gz<R, N, R2, TB, H2>), grid, dim3(TB), 0, s, d, op, n1, scale, kcs, fin, nblk_f, nblk_i);
         return;
       }
     }
-    hipLaunchKernelGGL((k_gz<R, N, R2, NT, C2<R>>), grid, dim3(NT), 0, s, d, op, n1, scale, fin, nblk_f, nblk_i);
+    hipLaunchKernelGGL((k_gz<R, N, R2, TB, C2<R>>), grid, dim3(TB), 0, s, d, op, n1, scale, kcs, fin, nblk_f, nblk_i);
   }
 }
 template <> hipError_t GLaunch<R>::gz(int n0, const GroupShape& g, bool h16, int nb, hipStream_t s, const Desc* d,
                                       int op, int n1, double scale, int fin, int nblk_f, int nblk_i) {
   const dim3 grid(g.zblocks + (fin >= 0 ? 1 : 0), nb);
   switch (n0) {
-#define FFTH_CASE(N)                                                                          \
-  case N:                                                                                     \
-    if (g.r2 == 4) gz_r<N, 4>(grid, h16, s, d, op, n1, scale, fin, nblk_f, nblk_i);          \
-    if constexpr (!DBL) {                                                                     \
-      if (g.r2 == 6) gz_r<N, 6>(grid, h16, s, d, op, n1, scale, fin, nblk_f, nblk_i);        \
-      if (g.r2 == 8) gz_r<N, 8>(grid, h16, s, d, op, n1, scale, fin, nblk_f, nblk_i);        \
-    }                                                                                         \
+#define FFTH_CASE(N)                                                                                  \
+  case N:                                                                                             \
+    if (g.r2 == 4) gz_r<N, 4>(grid, h16, s, d, op, n1, scale, g.kcs, fin, nblk_f, nblk_i);           \
+    if (g.r2 == 8) gz_r<N, 8>(grid, h16, s, d, op, n1, scale, g.kcs, fin, nblk_f, nblk_i);           \
+    if constexpr (!DBL) {                                                                             \
+      if (g.r2 == 6) gz_r<N, 6>(grid, h16, s, d, op, n1, scale, g.kcs, fin, nblk_f, nblk_i);         \
+    }                                                                                                 \
     return hipGetLastError();
     FFTH_GROUP_N01(FFTH_CASE)
 #undef FFTH_CASE
@@ -71,7 +72,7 @@ template <typename T> static GroupShape shape_of(const int n[3]) {
   g.on = true;
   g.r1 = r1;
   g.r2 = r2;
-  g.kcs = kc == 2 ? 1 : 0;
+  g.kcs = group_kcs(r2, n[2] / 2);
   g.xblocks = (n[0] * r2 + grp - 1) / grp;
   g.zblocks = n[2] / 2 / kc * r1;
   return g;
@@ -80,7 +81,7 @@ GroupShape group_shape(const int n[3], bool dbl) { return dbl ? shape_of<double>
 #endif
 #else
 // kernel launch for (axis-2 length, R1): f(integral constants).  R1 = 3, 6, 12
-// come up with R2 = 4 in FP64 (12, 24, 48 = 4 R1)
+// come up in FP64 (12, 24, 48 = 4 R1, 96 = 8 R1)
 template <int N> struct IC { static constexpr int v = N; };
 template <int N, class F> static bool for_r1(int r1, F&& f) {
   switch (r1) {

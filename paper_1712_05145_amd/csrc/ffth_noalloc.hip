@@ -151,6 +151,8 @@ ffth_status ffth_green_apply_noalloc(const int32_t n[3], double lambda0, double 
   d.nc = 6;
   d.lam0 = lambda0;
   d.mu0 = mu0;
+  d.gam_h = 0.5 / mu0;
+  d.gam_c = (lambda0 + mu0) / (mu0 * (lambda0 + 2.0 * mu0));
   d.inv_nvox = 1.0 / (double)nvox;
   d.tau_scale = 1.0;
   d.op_scale = 1.0 / (double)nvox;
@@ -160,7 +162,7 @@ ffth_status ffth_green_apply_noalloc(const int32_t n[3], double lambda0, double 
   s.first = 1;
   s.max_iter = 1;
   s.res = 1.0;
-  s.dscale = 1.0;
+  s.dscale = s.idscale = 1.0;
   s.gscale = -1.0;
   const int nb = (int)std::min<long>(1024, (nvox + 255) / 256);
   hipLaunchKernelGGL(k_noalloc_setup, dim3(nb), dim3(256), 0, st, d, s, (Desc*)(base + kOffDesc),

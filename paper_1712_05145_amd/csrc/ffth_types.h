@@ -26,6 +26,7 @@ struct SolverState {
   int32_t proj;      // FP32 projection passes (outer state only)
   double omega;      // BiCGSTAB: omega of the last iteration
   double dscale;     // inner state: RMS of the inner right-hand side (binary16 spectrum scale)
+  double idscale;    // its reciprocal
   int32_t pending;   // BiCGSTAB: x += alpha p + omega s of the last iteration not applied yet
   int32_t xpend;     // three-term CG: stopped after an even iteration, x of the last one not formed yet
   double tol0;       // inner state: the tightest reduction asked of one inner solve
@@ -70,6 +71,7 @@ struct Desc {
   SolverState* st;         // gating state
   SolverState* st2;        // secondary state (outer -> inner set-up)
   double lam0, mu0;        // reference medium of this entry's problem
+  double gam_h, gam_c;     // Green operator: 1 / (2 mu0), (lam0 + mu0) / (mu0 (lam0 + 2 mu0))
   double E[6];             // macroscopic strain, tensor components
   double G[18];            // order-1 gradient load G[J*3 + j]
   double H[54];            // order-2 load H[J*9 + j*3 + m] = d^2 E_J / dY_j dY_m
@@ -84,6 +86,27 @@ struct Desc {
   int32_t n[3];            // grid of this entry (multi-size launches)
   int32_t nblk_multi;      // partial-sum blocks of its multi-size fused pass (finalize with nblk_i < 0)
   int32_t x_zero;          // the iterate x is zero (first residual sweep of a solve): not read
+};
+
+// Division of block numbers by a launch constant: quotient and remainder in a
+// few scalar instructions (floor(2^32 / d) is at most one quotient short).
+struct FastDiv {
+  int32_t d;
+  uint32_t inv;
+#ifdef __HIPCC__
+  __host__ __device__ static FastDiv of(int d) {
+    return FastDiv{d, d > 1 ? (uint32_t)(0x100000000ull / (uint32_t)d) : 0xffffffffu};
+  }
+  __device__ __forceinline__ int div(int x, int& rem) const {
+    int q = (int)__umulhi((unsigned)x, inv);
+    rem = x - q * d;
+    if (rem >= d) {
+      rem -= d;
+      ++q;
+    }
+    return q;
+  }
+#endif
 };
 
 // x-pass (forward) modes

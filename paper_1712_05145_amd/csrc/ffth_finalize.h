@@ -283,6 +283,7 @@ __device__ static void fin_rest(int op, const Desc& d, SolverState* st, const do
       }
       if (!st->active) {
         in->active = 0;
+        in->xpend = 0;
       } else if (op == FIN_OUTER_P) {
         in->active = 0;  // the projection pass sets the inner solve up
       } else {

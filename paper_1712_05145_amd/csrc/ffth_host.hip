@@ -38,6 +38,7 @@ constexpr int NRED_ = NRED;
 constexpr int MS_BLOCKS_MAX = 1024;   // blocks of the pointwise reduction kernels
 constexpr int NT = 256;              // threads per block of the pointwise kernels
 constexpr size_t ALIGN = 256;
+constexpr int NDISP = 24;            // displacement transforms of an order-2 right-hand side (6 + 18)
 
 size_t al(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
@@ -73,7 +74,7 @@ Layout make_layout(const int n[3], int nph, int nloads, int order, const ffth_op
   Layout L{};
   const long nvox = (long)n[0] * n[1] * n[2];
   const int prec = o.precision, scheme = o.scheme;
-  L.ndesc = 7 * nloads + 8;
+  L.ndesc = 7 * nloads + NDISP;
   L.nstate = 3 * nloads + 1;
   L.nblk = std::max((int)((long)n[0] * n[1]), ms_blocks(nvox));   // x-pass blocks of any variant (>= 1 row)
   // per-load FP32 / FP64 field counts
@@ -270,7 +271,8 @@ struct ffth_plan {
   GroupShape grp[2];      // grouped passes, FP32/FP64 (off: the plan runs the five classical passes)
   bool plane = false;     // 2-D grid whose axis-1 transforms and operator are one pass
   int bw[2] = {0, 0};     // loads per launch of the iteration passes, FP32/FP64 (0: all at once)
-  std::vector<Desc> h_desc;
+  Desc* h_desc = nullptr;             // pinned, ndesc descriptors
+  bool descs_queued = false, states_queued = false;   // uploads that may still read h_desc / h_state
   // kernel timing (diagnostics): events bracket every launch when enabled
   bool prof = false;
   struct Rec { int cat, units; hipEvent_t a, b; };
@@ -321,11 +323,17 @@ SolverState* st_inner(ffth_plan* P, int l) { return P->d_state + P->nloads + l; 
 SolverState* st_post(ffth_plan* P, int l) { return P->d_state + 2 * P->nloads + l; }
 
 // Descriptor slots (roles x nloads).
-enum Role { R_MAIN = 0, R_MAIN_DELTA = 1, R_INNER = 2, R_POST = 3, R_THETA = 4, R_UTIL = 5, R_PROJ = 6 };
+// R_FIRST: the first pass of a solve, on the zero iterate; R_DELTA1: the first
+// sweep of a mixed solve that adds a correction.  They take the slots of the
+// theta and utility transforms, which no solve runs.
+enum Role {
+  R_MAIN = 0, R_MAIN_DELTA = 1, R_INNER = 2, R_POST = 3, R_THETA = 4, R_UTIL = 5, R_PROJ = 6,
+  R_FIRST = R_THETA, R_DELTA1 = R_UTIL
+};
 int desc_slot(ffth_plan* P, Role r, int l) { return (int)r * P->nloads + l; }
 const Desc* dptr(ffth_plan* P, Role r) { return P->d_desc + desc_slot(P, r, 0); }
-// the 6 order-1 displacement descriptors live after the role blocks
-int util6_slot(ffth_plan* P, int J) { return 7 * P->nloads + J; }
+// the displacement descriptors of orders 1 and 2 live after the role blocks
+int disp_slot(ffth_plan* P, int J) { return 7 * P->nloads + J; }
 
 // ---- kernel timing ---------------------------------------------------------
 enum Cat {
@@ -417,27 +425,41 @@ SolverState make_state(double tol, int max_iter, double guard_eps, int active) {
   return s;
 }
 
-ffth_status upload_descs(ffth_plan* P) {
-  HIPCHK(hipMemcpyAsync(P->d_desc, P->h_desc.data(), P->h_desc.size() * sizeof(Desc), hipMemcpyHostToDevice,
-                        P->stream));
+// Uploads are queued from pinned memory and not waited for; the host waits
+// only before it writes what a queued upload may still read.
+ffth_status stream_sync(ffth_plan* P) {
   HIPCHK(hipStreamSynchronize(P->stream));
+  P->descs_queued = P->states_queued = false;
+  return FFTH_OK;
+}
+
+// before the first write to h_desc after upload_descs
+ffth_status descs_writable(ffth_plan* P) { return P->descs_queued ? stream_sync(P) : FFTH_OK; }
+
+ffth_status upload_descs(ffth_plan* P) {
+  HIPCHK(hipMemcpyAsync(P->d_desc, P->h_desc, P->L.ndesc * sizeof(Desc), hipMemcpyHostToDevice, P->stream));
+  P->descs_queued = true;
   return FFTH_OK;
 }
 
 ffth_status upload_states(ffth_plan* P, const std::vector<SolverState>& s, int first_slot) {
-  HIPCHK(hipMemcpyAsync(P->d_state + first_slot, s.data(), s.size() * sizeof(SolverState), hipMemcpyHostToDevice,
-                        P->stream));
-  HIPCHK(hipStreamSynchronize(P->stream));
-  std::memcpy(P->h_state + first_slot, s.data(), s.size() * sizeof(SolverState));  // keep the mirror current
+  if (P->states_queued) {
+    const ffth_status st = stream_sync(P);
+    if (st != FFTH_OK) return st;
+  }
+  std::memcpy(P->h_state + first_slot, s.data(), s.size() * sizeof(SolverState));
+  HIPCHK(hipMemcpyAsync(P->d_state + first_slot, P->h_state + first_slot, s.size() * sizeof(SolverState),
+                        hipMemcpyHostToDevice, P->stream));
+  P->states_queued = true;
   return FFTH_OK;
 }
 
 ffth_status read_states(ffth_plan* P) {
   HIPCHK(hipMemcpyAsync(P->h_state, P->d_state, P->L.nstate * sizeof(SolverState), hipMemcpyDeviceToHost,
                         P->stream));
-  HIPCHK(hipStreamSynchronize(P->stream));
-  prof_flush(P);
-  return FFTH_OK;
+  const ffth_status st = stream_sync(P);
+  if (st == FFTH_OK) prof_flush(P);
+  return st;
 }
 
 // ---- pass launchers -------------------------------------------------------
@@ -776,6 +798,7 @@ ffth_status autotune(ffth_plan* P) {
   if (mixed || (o.precision == FFTH_FP64 && P->L.nf64 >= 2)) {   // FP64 passes
     const bool cg3 = o.scheme == FFTH_CG3;
     const int xf = mixed ? XF_LS : cg3 ? XF_R3 : XF_CG, xi = mixed ? XI_RESID : XI_CG;
+    if ((s = descs_writable(P)) != FFTH_OK) return s;
     for (int l = 0; l < nt; ++l) {
       Desc d = base_desc(P, l);
       d.st = P->d_state + 3 * P->nloads;
@@ -796,7 +819,7 @@ ffth_status autotune(ffth_plan* P) {
     if ((s = upload_descs(P)) != FFTH_OK) return s;
     tune_prec<double>(P, dd, nt, xf, xi, cg3, false);
   }
-  HIPCHK(hipStreamSynchronize(P->stream));
+  if ((s = stream_sync(P)) != FFTH_OK) return s;
   HIPCHK(hipGetLastError());
   std::array<int, 10> val;
   for (int i = 0; i < 8; ++i) val[i] = P->var[i / 2][i % 2];
@@ -831,6 +854,10 @@ bool any_active(ffth_plan* P, int first, int count) {
   return false;
 }
 
+// Loads so small that launches and host waits bound a solve (up to 64^3 x 8 voxels
+// in all: an iteration takes less than about 100 us).
+bool launch_bound(const ffth_plan* P, int nl) { return P->nvox * nl <= 1L << 21; }
+
 // Launch set: the descriptors of role r for the loads whose state (slot
 // state_base + l) was active at the last read-back, copied contiguously into
 // compact region `region` so that grids span active loads only.  Loads that
@@ -840,6 +867,14 @@ struct DescSet {
   int n;
 };
 DescSet active_set(ffth_plan* P, Role r, int state_base, int nl, int region) {
+  // all of them, or launches so small that the blocks of stopped loads cost
+  // less than an upload: the descriptors already on the device
+  bool all = launch_bound(P, nl);
+  if (!all) {
+    all = true;
+    for (int l = 0; l < nl; ++l) all = all && P->h_state[state_base + l].active;
+  }
+  if (all) return DescSet{dptr(P, r), any_active(P, state_base, nl) ? nl : 0};
   Desc* stage = P->h_cdesc + (size_t)region * P->nloads;
   int k = 0;
   for (int l = 0; l < nl; ++l)
@@ -874,7 +909,7 @@ template <typename T> ffth_status bicg_iter(ffth_plan* P, const Desc* d, int nb)
 }
 
 // Iterate a plain (single precision level) scheme on descriptors d with
-// states in slots [0, nl).  The iterate must hold zero on entry.
+// states in slots [0, nl).
 template <typename T> ffth_status run_cg3(ffth_plan* P, int nl);
 
 template <typename T> ffth_status run_plain(ffth_plan* P, const Desc* d, int nl) {
@@ -883,7 +918,7 @@ template <typename T> ffth_status run_plain(ffth_plan* P, const Desc* d, int nl)
   DescSet as;
   if (o.scheme == FFTH_CG3) return run_cg3<T>(P, nl);
   // pass 0: x = b = -Gamma0 * P_rhs, ||b||, zero right-hand-side guard
-  if ((s = apply<T>(P, d, nl, XF_LS, OP_GAMMA, XI_BS, FIN_LS_FIRST)) != FFTH_OK) return s;
+  if ((s = apply<T>(P, dptr(P, R_FIRST), nl, XF_LS, OP_GAMMA, XI_BS, FIN_LS_FIRST)) != FFTH_OK) return s;
   if (o.scheme != FFTH_BASIC) {
     // r0 = b - A b = LS(x) - x
     const int fin_op = o.scheme == FFTH_CG ? FIN_RESID_INIT : FIN_BI_INIT;
@@ -920,7 +955,7 @@ template <typename T> ffth_status run_cg3(ffth_plan* P, int nl) {
   const ffth_opts& o = P->opts;
   ffth_status s;
   DescSet as;
-  if ((s = apply<T>(P, dptr(P, R_MAIN_DELTA), nl, XF_LS, OP_GAMMA, XI_BS, FIN_LS_FIRST)) != FFTH_OK) return s;
+  if ((s = apply<T>(P, dptr(P, R_FIRST), nl, XF_LS, OP_GAMMA, XI_BS, FIN_LS_FIRST)) != FFTH_OK) return s;
   if ((s = read_states(P)) != FFTH_OK) return s;
   if ((as = active_set(P, R_MAIN, 0, nl, 0)).n < 0) return FFTH_ERR_DEVICE;
   if ((s = cg3_start<T>(P, as.d, as.n, false)) != FFTH_OK) return s;
@@ -1060,14 +1095,13 @@ ffth_status group_issue(std::vector<Job*>& jobs, Stage& st, int* kin_out, InnerS
   }
   int from[4], cnt[4] = {0, 0, 0, 0}, nFresh = 0;
   int kin = o.check_every;
-  const Role role[3] = {R_MAIN, R_MAIN_DELTA, R_PROJ};
   for (int ph = PH_A0; ph <= PH_PROJ; ++ph) {
     from[ph] = st.cursor;
-    for (Job* J : jobs)
-      if (J->phase == ph) cnt[ph] += stage_append(st, *J, role[ph], 0);
+    for (Job* J : jobs) {
+      const Role role = ph == PH_A0 ? R_FIRST : ph == PH_PROJ ? R_PROJ : J->sweeps == 1 ? R_DELTA1 : R_MAIN_DELTA;
+      if (J->phase == ph) cnt[ph] += stage_append(st, *J, role, 0);
+    }
   }
-  // the first sweep of a solve runs on the zero iterate: its passes skip reading it
-  for (int i = 0; i < cnt[PH_A0]; ++i) st.h[from[PH_A0] + i].x_zero = 1;
   // inner loads: those whose solve starts this round first (they take the start pass)
   from[3] = st.cursor;
   for (int pass = 0; pass < 2; ++pass) {
@@ -1181,20 +1215,67 @@ ffth_status group_advance(std::vector<Job*>& jobs, int kin) {
   return FFTH_OK;
 }
 
+// The same phases for one plan.  Every load takes part in a phase while its
+// state on the device says so; the host only has to know when to stop.  Small
+// solves, which launches and host waits bound, therefore queue a sweep, the
+// projection, the start of the inner solve and its first iterations in one go
+// wherever the sweep is not expected to be the last: its predecessor asked for
+// a reduction that leaves the residual above the tolerance.
 ffth_status run_mixed(ffth_plan* P, int nl) {
-  Job J;
-  J.P = P;
-  J.nl = nl;
-  std::vector<Job*> jobs{&J};
+  const ffth_opts& o = P->opts;
+  const bool cg = o.scheme == FFTH_CG, chain = launch_bound(P, nl);
+  const size_t bytes = (size_t)P->nvox * 6 * sizeof(float);
+  int sweeps = 0, inner_total = 0;
+  bool last = false;   // inner budget spent: the next sweep is the final one
   ffth_status s;
-  while (J.phase != PH_DONE) {
-    Stage st{P->d_cdesc, P->h_cdesc, 4 * P->nloads, 0};
-    int kin = 0;
-    if ((s = group_issue(jobs, st, &kin)) != FFTH_OK) return s;
-    HIPCHK(hipStreamSynchronize(P->stream));
-    if ((s = group_advance(jobs, kin)) != FFTH_OK) return s;
+  DescSet ds;
+  for (;;) {
+    if (sweeps > 0 && cg) {
+      // inner solves that ended after an even iteration owe their last x,
+      // which the sweep adds (the kernel knows which)
+      ProfScope ps(P, C_POINT, nl);
+      HIPCHK(Launch<float>::cg3_finish(dim3(ms_blocks(P->nvox), nl), P->stream, dptr(P, R_INNER), 6L * P->nvox));
+    }
+    bool expect_end = sweeps > 0;
+    for (int l = 0; l < nl && expect_end; ++l)
+      if (P->h_state[l].active) expect_end = P->h_state[l].res * P->h_state[P->nloads + l].tol <= o.tol;
+    ds = active_set(P, sweeps == 0 ? R_FIRST : sweeps == 1 ? R_DELTA1 : R_MAIN_DELTA, 0, nl, 0);
+    if (ds.n < 0) return FFTH_ERR_DEVICE;
+    if ((s = apply<double>(P, ds.d, ds.n, XF_LS, OP_GAMMA, XI_RESID, sweeps == 0 ? FIN_OUTER : FIN_OUTER_P)) != FFTH_OK)
+      return s;
+    ++sweeps;
+    const bool final_sweep = last || sweeps >= o.max_outer;
+    if (!chain || final_sweep || expect_end) {
+      if ((s = read_states(P)) != FFTH_OK) return s;
+      if (final_sweep || !any_active(P, 0, nl)) return FFTH_OK;
+    }
+    if (sweeps > 1) {
+      if ((ds = active_set(P, R_PROJ, 0, nl, 1)).n < 0) return FFTH_ERR_DEVICE;
+      if ((s = apply<float>(P, ds.d, ds.n, XF_C0, OP_GAMMA, XI_PROJ, FIN_PROJ)) != FFTH_OK) return s;
+    }
+    // inner solve of the loads that go on
+    if ((ds = active_set(P, R_INNER, 0, nl, 2)).n < 0) return FFTH_ERR_DEVICE;
+    if (cg) {   // x_0 = 0 is implicit in the three-term CG
+      if ((s = cg3_start<float>(P, ds.d, ds.n, P->h16)) != FFTH_OK) return s;
+    } else {    // Basic Scheme: x_0 = b
+      for (int l = 0; l < nl; ++l)
+        HIPCHK(hipMemcpyAsync(f32_ptr(P, l, 0), f32_ptr(P, l, 1), bytes, hipMemcpyDeviceToDevice, P->stream));
+    }
+    do {
+      const int kin = std::min(o.check_every, std::max(1, o.max_iter - inner_total));
+      if (cg) {
+        if ((s = cg3_iters<float>(P, ds.d, ds.n, kin, P->h16)) != FFTH_OK) return s;
+      } else {
+        for (int j = 0; j < kin; ++j)
+          if ((s = apply<float>(P, ds.d, ds.n, XF_MATVEC, OP_GAMMA, XI_BS_INNER, FIN_BS)) != FFTH_OK) return s;
+      }
+      inner_total += kin;
+      if (inner_total >= o.max_iter) last = true;
+      if ((s = read_states(P)) != FFTH_OK) return s;
+      if (!any_active(P, 0, nl)) return FFTH_OK;   // a sweep queued with these iterations stopped every load
+      if ((ds = active_set(P, R_INNER, P->nloads, nl, 2)).n < 0) return FFTH_ERR_DEVICE;
+    } while (any_active(P, P->nloads, nl) && !last);
   }
-  return FFTH_OK;
 }
 
 ffth_status check_plan(ffth_plan* P, int nloads) {
@@ -1278,8 +1359,13 @@ void build_solve_descs(ffth_plan* P, int nl, const double* E, double* eps, bool 
       pr.r = f64_ptr(P, l, 0);
       pr.out = f32_ptr(P, l, 1);
     }
-    if (o.scheme == FFTH_CG3) md.x = m.r;   // b = -Gamma0 * P_rhs goes to the residual slot (r_0 = b)
+    Desc fi = m;
+    fi.x_zero = X_ZERO;
+    if (o.scheme == FFTH_CG3) fi.x = m.r;   // b = -Gamma0 * P_rhs goes to the residual slot (r_0 = b)
+    P->h_desc[desc_slot(P, R_FIRST, l)] = fi;
     P->h_desc[desc_slot(P, R_MAIN_DELTA, l)] = md;
+    md.x_zero = X_INIT;
+    P->h_desc[desc_slot(P, R_DELTA1, l)] = md;
     P->h_desc[desc_slot(P, R_PROJ, l)] = pr;
     Desc in = base_desc(P, l);
     in.st = st_inner(P, l);
@@ -1306,9 +1392,7 @@ void build_solve_descs(ffth_plan* P, int nl, const double* E, double* eps, bool 
   }
 }
 
-// Run the solve for nl loads whose descriptors are built, then fill results.
-// Upload the iteration states and zero the iterate of nl loads whose
-// descriptors are built (keep_gscale: order-1 guard scales from the builder).
+// Upload the iteration states of nl loads whose descriptors are built (keep_gscale: order-1 guard scales from the builder).
 ffth_status solve_begin(ffth_plan* P, int nl, bool keep_gscale) {
   const ffth_opts& o = P->opts;
   ffth_status s;
@@ -1326,24 +1410,17 @@ ffth_status solve_begin(ffth_plan* P, int nl, bool keep_gscale) {
     for (int l = 0; l < nl; ++l) sts[l].gscale = P->h_state[2 * P->nloads + l].gscale;
   }
   if ((s = upload_states(P, sts, 0)) != FFTH_OK) return s;
-  // zero the iterate (three-term CG: the residual slot, which the first pass
-  // reads as its iterate and overwrites with b)
-  for (int l = 0; l < nl; ++l) {
-    const Desc& m = P->h_desc[desc_slot(P, o.scheme == FFTH_CG3 ? R_MAIN_DELTA : R_MAIN, l)];
-    const size_t bytes = (size_t)P->nvox * 6 * (o.precision == FFTH_FP32 ? sizeof(float) : sizeof(double));
-    HIPCHK(hipMemsetAsync(m.x, 0, bytes, P->stream));
-  }
   return FFTH_OK;
 }
 
-// After the iteration: exact zero for guarded loads, volume averages, results.
+// After the iteration (the states have just been read): exact zero for guarded loads, volume averages, results.
 ffth_status solve_finish(ffth_plan* P, int nl, double* eps, ffth_result* res, double t0, const double* gmean) {
   const ffth_opts& o = P->opts;
   ffth_status s;
-  // zero-rhs guard: eps = 0 exactly
-  if ((s = read_states(P)) != FFTH_OK) return s;
+  // zero-rhs guard: eps = 0 exactly; mixed solves that ended with their first
+  // sweep never stored their iterate, which is zero
   for (int l = 0; l < nl; ++l)
-    if (P->h_state[l].flag == FLAG_ZERO_RHS) {
+    if (P->h_state[l].flag == FLAG_ZERO_RHS || (o.precision == FFTH_MIXED && P->h_state[l].iters <= 1)) {
       const Desc& m = P->h_desc[desc_slot(P, R_MAIN, l)];
       const size_t bytes = (size_t)P->nvox * 6 * (o.precision == FFTH_FP32 ? sizeof(float) : sizeof(double));
       HIPCHK(hipMemsetAsync(m.x, 0, bytes, P->stream));
@@ -1430,11 +1507,26 @@ void host_put(ffth_plan* P, void* q, size_t bytes) {
   else (void)hipHostFree(q);
 }
 
+// One pinned allocation (each costs tens of microseconds): state mirror,
+// staging of compacted descriptors, descriptors.
+size_t host_bytes(const ffth_plan* P) {
+  return al(P->L.nstate * sizeof(SolverState)) + (4 * (size_t)P->nloads + P->L.ndesc) * sizeof(Desc);
+}
+
+bool alloc_host_bufs(ffth_plan* P) {
+  char* h = (char*)host_get(P, host_bytes(P));
+  if (!h) return false;
+  P->h_state = (SolverState*)h;
+  P->h_cdesc = (Desc*)(h + al(P->L.nstate * sizeof(SolverState)));
+  P->h_desc = P->h_cdesc + 4 * (size_t)P->nloads;
+  std::memset(P->h_desc, 0, P->L.ndesc * sizeof(Desc));
+  return true;
+}
+
 void free_host_bufs(ffth_plan* P) {
-  host_put(P, P->h_state, P->L.nstate * sizeof(SolverState));
-  host_put(P, P->h_cdesc, 4 * (size_t)P->nloads * sizeof(Desc));
+  host_put(P, P->h_state, host_bytes(P));
   P->h_state = nullptr;
-  P->h_cdesc = nullptr;
+  P->h_cdesc = P->h_desc = nullptr;
 }
 
 ffth_status plan_create(ffth_plan** out, const ffth_problem* p, const ffth_opts* o, int32_t nloads, int32_t order,
@@ -1557,13 +1649,9 @@ ffth_status plan_create(ffth_plan** out, const ffth_problem* p, const ffth_opts*
   P->d_cdesc = (Desc*)(P->ws + L.cdesc);
   set_passes(P, false);
   set_blocks(P);
-  P->h_desc.assign(L.ndesc, Desc{});
   P->hpool = pool;
-  P->h_state = (SolverState*)host_get(P, L.nstate * sizeof(SolverState));
-  P->h_cdesc = (Desc*)host_get(P, 4 * (size_t)nloads * sizeof(Desc));
-  if (!P->h_state || !P->h_cdesc) {
+  if (!alloc_host_bufs(P)) {
     g_last_error = "hipHostMalloc failed";
-    free_host_bufs(P);
     delete P;
     return FFTH_ERR_DEVICE;
   }
@@ -1673,6 +1761,7 @@ ffth_status ffth_solve_order0(ffth_plan* P, int32_t nloads, const double* E, dou
     return FFTH_ERR_INVALID;
   }
   const double t0 = now_s();
+  if ((s = descs_writable(P)) != FFTH_OK) return s;
   build_solve_descs(P, nloads, E, eps, false);
   if ((s = upload_descs(P)) != FFTH_OK) return s;
   return solve_common(P, nloads, eps, res, t0, nullptr);
@@ -1686,6 +1775,7 @@ namespace {
 ffth_status build_rhs(ffth_plan* P, int order, int nl, const double* eps, const double* G, double* const* Pout,
                       std::vector<double>& gmean) {
   ffth_status s;
+  if ((s = descs_writable(P)) != FFTH_OK) return s;
   for (int l = 0; l < nl; ++l) {
     Desc d = base_desc(P, l);
     d.st = st_post(P, l);
@@ -1728,45 +1818,42 @@ ffth_status build_rhs(ffth_plan* P, int order, int nl, const double* eps, const 
   return FFTH_OK;
 }
 
-ffth_status make_x1_block(ffth_plan* P, const double* eps0, double* out, int count);
+// Displacements of `count` strain fields [count][6][N] into out [count][3][N].
+struct DispJob {
+  const double* eps;
+  double* out;
+  int count;
+};
 
-// Displacements of `count` strain fields [count][6][N] into out [count][3][N]
-// (order-0 correctors -> X1, order-1 unit-gradient solutions -> X2).
-ffth_status make_disp(ffth_plan* P, const double* eps0, double* out, int count) {
+// Displacement transforms (forward, displacement operator, inverse) of the
+// order-0 correctors (-> X1) and, for order 2, of the 18 order-1 unit-gradient
+// solutions (-> X2).  As many fields share a launch as spectra fit into the
+// plan's spectrum and iterate regions, which are contiguous and idle before the
+// solve (one load of a mixed plan: 4 fields instead of 1; 64^3, 24 fields:
+// 1.29 -> 0.6 ms); all groups are queued back to back.  The transforms' block
+// sums are not used and share one array.
+ffth_status make_disp(ffth_plan* P, std::initializer_list<DispJob> jobs) {
   ffth_status s;
-  for (int base = 0; base < count; base += 6) {
-    const int k = std::min(6, count - base);
-    if ((s = make_x1_block(P, eps0 + (size_t)base * 6 * P->nvox, out + (size_t)base * 3 * P->nvox, k)) != FFTH_OK)
-      return s;
-  }
-  return FFTH_OK;
-}
-
-ffth_status make_x1(ffth_plan* P, const double* eps0) { return make_disp(P, eps0, X1field(P), 6); }
-
-ffth_status make_x1_block(ffth_plan* P, const double* eps0, double* out, int count) {
-  // Displacement transforms (forward, displacement operator, inverse) of
-  // `count` <= 6 strain fields: as many fields per launch as the plan has
-  // load spectra (each field in its own spectrum region and partial sums),
-  // all groups queued back to back without waiting for the device.
-  ffth_status s;
-  const int k = std::max(1, std::min(count, P->nloads));
-  for (int J = 0; J < count; ++J) {
-    const int l = J % k;
-    Desc d = base_desc(P, l);
-    d.st = P->d_state + 3 * P->nloads;
-    d.io = (void*)(eps0 + (size_t)J * 6 * P->nvox);
-    d.out = out + (size_t)J * 3 * P->nvox;
-    d.nc = 6;
-    d.nc_out = 3;
-    P->h_desc[util6_slot(P, J)] = d;
-  }
+  if ((s = descs_writable(P)) != FFTH_OK) return s;
+  const int room = (int)std::min<size_t>(NDISP, (P->L.P - P->L.spec) / P->L.spec_stride);
+  int n = 0;
+  for (const DispJob& j : jobs)
+    for (int J = 0; J < j.count; ++J, ++n) {
+      Desc d = base_desc(P, 0);
+      d.spec = spec_ptr(P, n % room);
+      d.st = P->d_state + 3 * P->nloads;
+      d.io = (void*)(j.eps + (size_t)J * 6 * P->nvox);
+      d.out = j.out + (size_t)J * 3 * P->nvox;
+      d.nc = 6;
+      d.nc_out = 3;
+      P->h_desc[disp_slot(P, n)] = d;
+    }
   if ((s = upload_descs(P)) != FFTH_OK) return s;
   std::vector<SolverState> u(1, make_state(0, 1, 0, 1));
   if ((s = upload_states(P, u, 3 * P->nloads)) != FFTH_OK) return s;
-  for (int J0 = 0; J0 < count; J0 += k) {
-    const int nb = std::min(k, count - J0);
-    const Desc* d = P->d_desc + util6_slot(P, J0);
+  for (int J0 = 0; J0 < n; J0 += room) {
+    const int nb = std::min(room, n - J0);
+    const Desc* d = P->d_desc + disp_slot(P, J0);
     if ((s = xfwd<double>(P, d, nb, XF_COPY)) != FFTH_OK) return s;
     if ((s = spectral<double>(P, d, nb, OP_DISP)) != FFTH_OK) return s;
     if ((s = xinv<double>(P, d, nb, XI_STORE)) != FFTH_OK) return s;
@@ -1790,11 +1877,12 @@ ffth_status ffth_solve_order1(ffth_plan* P, const double* eps0_six, int32_t nloa
     return FFTH_ERR_INVALID;
   }
   const double t0 = now_s();
-  if ((s = make_x1(P, eps0_six)) != FFTH_OK) return s;
+  if ((s = make_disp(P, {{eps0_six, X1field(P), 6}})) != FFTH_OK) return s;
   std::vector<double*> pout(nloads);
   for (int l = 0; l < nloads; ++l) pout[l] = Pfield(P, l);
   std::vector<double> gmean;
   if ((s = build_rhs(P, 1, nloads, eps0_six, G, pout.data(), gmean)) != FFTH_OK) return s;
+  if ((s = descs_writable(P)) != FFTH_OK) return s;
   build_solve_descs(P, nloads, nullptr, eps, true);
   if ((s = upload_descs(P)) != FFTH_OK) return s;
   return solve_common(P, nloads, eps, res, t0, gmean.data());
@@ -1814,12 +1902,12 @@ ffth_status ffth_solve_order2(ffth_plan* P, const double* eps0_six, const double
     return FFTH_ERR_INVALID;
   }
   const double t0 = now_s();
-  if ((s = make_x1(P, eps0_six)) != FFTH_OK) return s;
-  if ((s = make_disp(P, eps1_18, X2field(P), 18)) != FFTH_OK) return s;
+  if ((s = make_disp(P, {{eps0_six, X1field(P), 6}, {eps1_18, X2field(P), 18}})) != FFTH_OK) return s;
   std::vector<double*> pout(nloads);
   for (int l = 0; l < nloads; ++l) pout[l] = Pfield(P, l);
   std::vector<double> gmean;
   if ((s = build_rhs(P, 2, nloads, eps1_18, H, pout.data(), gmean)) != FFTH_OK) return s;
+  if ((s = descs_writable(P)) != FFTH_OK) return s;
   build_solve_descs(P, nloads, nullptr, eps, true);
   if ((s = upload_descs(P)) != FFTH_OK) return s;
   return solve_common(P, nloads, eps, res, t0, gmean.data());
@@ -1838,15 +1926,13 @@ ffth_status ffth_order2_rhs(ffth_plan* P, const double* eps0_six, const double* 
     g_last_error = "null argument";
     return FFTH_ERR_INVALID;
   }
-  if ((s = make_x1(P, eps0_six)) != FFTH_OK) return s;
-  if ((s = make_disp(P, eps1_18, X2field(P), 18)) != FFTH_OK) return s;
+  if ((s = make_disp(P, {{eps0_six, X1field(P), 6}, {eps1_18, X2field(P), 18}})) != FFTH_OK) return s;
   std::vector<double> gm;
   double* po[1] = {Pout};
   if ((s = build_rhs(P, 2, 1, eps1_18, H, po, gm)) != FFTH_OK) return s;
   if (g_mean)
     for (int c = 0; c < 3; ++c) g_mean[c] = gm[c];
-  HIPCHK(hipStreamSynchronize(P->stream));
-  return FFTH_OK;
+  return stream_sync(P);
 }
 
 ffth_status ffth_green_apply(ffth_plan* P, const double* tau, double* eta, int32_t precision) {
@@ -1862,11 +1948,8 @@ ffth_status ffth_green_apply(ffth_plan* P, const double* tau, double* eta, int32
   d.io = (void*)tau;
   d.out = eta;
   d.nc = 6;
-  P->h_desc[desc_slot(P, R_UTIL, 0)] = d;
-  if ((s = upload_descs(P)) != FFTH_OK) return s;
-  std::vector<SolverState> u(1, make_state(0, 1, 0, 1));
-  if ((s = upload_states(P, u, 3 * P->nloads)) != FFTH_OK) return s;
   const Desc* dd = dptr(P, R_UTIL);
+  HIPCHK(launch_setup(P->stream, d, make_state(0, 1, 0, 1), (Desc*)dd, d.st));
   if (precision == FFTH_FP64) {
     if ((s = xfwd<double>(P, dd, 1, XF_COPY)) != FFTH_OK) return s;
     if ((s = spectral<double>(P, dd, 1, OP_GAMMA)) != FFTH_OK) return s;
@@ -1876,8 +1959,7 @@ ffth_status ffth_green_apply(ffth_plan* P, const double* tau, double* eta, int32
     if ((s = spectral<float>(P, dd, 1, OP_GAMMA)) != FFTH_OK) return s;
     if ((s = xinv<float>(P, dd, 1, XI_STORE)) != FFTH_OK) return s;
   }
-  HIPCHK(hipStreamSynchronize(P->stream));
-  return FFTH_OK;
+  return stream_sync(P);
 }
 
 ffth_status ffth_displacement(ffth_plan* P, const double* eps, double* u) {
@@ -1894,16 +1976,12 @@ ffth_status ffth_displacement(ffth_plan* P, const double* eps, double* u) {
   d.out = u;
   d.nc = 6;
   d.nc_out = 3;
-  P->h_desc[desc_slot(P, R_UTIL, 0)] = d;
-  if ((s = upload_descs(P)) != FFTH_OK) return s;
-  std::vector<SolverState> st(1, make_state(0, 1, 0, 1));
-  if ((s = upload_states(P, st, 3 * P->nloads)) != FFTH_OK) return s;
   const Desc* dd = dptr(P, R_UTIL);
+  HIPCHK(launch_setup(P->stream, d, make_state(0, 1, 0, 1), (Desc*)dd, d.st));
   if ((s = xfwd<double>(P, dd, 1, XF_COPY)) != FFTH_OK) return s;
   if ((s = spectral<double>(P, dd, 1, OP_DISP)) != FFTH_OK) return s;
   if ((s = xinv<double>(P, dd, 1, XI_STORE)) != FFTH_OK) return s;
-  HIPCHK(hipStreamSynchronize(P->stream));
-  return FFTH_OK;
+  return stream_sync(P);
 }
 
 ffth_status ffth_order1_rhs(ffth_plan* P, const double* eps0_six, const double* G, double* Pout, double* g_mean) {
@@ -1918,14 +1996,13 @@ ffth_status ffth_order1_rhs(ffth_plan* P, const double* eps0_six, const double* 
     g_last_error = "null argument";
     return FFTH_ERR_INVALID;
   }
-  if ((s = make_x1(P, eps0_six)) != FFTH_OK) return s;
+  if ((s = make_disp(P, {{eps0_six, X1field(P), 6}})) != FFTH_OK) return s;
   std::vector<double> gm;
   double* po[1] = {Pout};
   if ((s = build_rhs(P, 1, 1, eps0_six, G, po, gm)) != FFTH_OK) return s;
   if (g_mean)
     for (int c = 0; c < 3; ++c) g_mean[c] = gm[c];
-  HIPCHK(hipStreamSynchronize(P->stream));
-  return FFTH_OK;
+  return stream_sync(P);
 }
 
 ffth_status ffth_profile_enable(ffth_plan* P, int32_t on) {
@@ -2138,7 +2215,7 @@ ffth_status admit(ffth_server* S) {
     r->t_start = now_s();
     build_solve_descs(r->P, r->nl, r->E.data(), r->eps, false);
     if ((st = upload_descs(r->P)) != FFTH_OK || (st = solve_begin(r->P, r->nl, false)) != FFTH_OK ||
-        (st = hip_ok(hipStreamSynchronize(S->admit_stream), "sync") ? FFTH_OK : FFTH_ERR_DEVICE) != FFTH_OK) {
+        (st = stream_sync(r->P)) != FFTH_OK) {
       finish_request(S, r, st);
       continue;
     }

@@ -397,16 +397,21 @@ __global__ __launch_bounds__(NTB) void k_xfwd(const Desc* __restrict__ descs, in
       const int ph = d.phase[vox];
       if (mode == XF_LS) {
         T x[6] = {0, 0, 0, 0, 0, 0};
-        T* xp = d.x_zero ? nullptr : (T*)d.x;
+        T* xp = d.x_zero == X_ZERO ? nullptr : (T*)d.x;
         if (xp) {
+          if (d.x_zero == X_READ) {
 #pragma unroll
-          for (int c = 0; c < 6; ++c) x[c] = xp[c * nvox + vox];
+            for (int c = 0; c < 6; ++c) x[c] = xp[c * nvox + vox];
+          }
           if (dl) {
 #pragma unroll
             for (int c = 0; c < 6; ++c) {
               x[c] += (T)dl[c * nvox + vox];
               xp[c * nvox + vox] = x[c];
             }
+          } else if (d.x_zero == X_INIT) {
+#pragma unroll
+            for (int c = 0; c < 6; ++c) xp[c * nvox + vox] = T(0);
           }
         }
         T pr[6];
@@ -598,7 +603,7 @@ __global__ __launch_bounds__(NTB) void k_xinv(const Desc* __restrict__ descs, in
       T* xp = (T*)d.x;
       T df[6];
 #pragma unroll
-      for (int c = 0; c < 6; ++c) df[c] = eta[c] - xp[c * nvox + vox];
+      for (int c = 0; c < 6; ++c) df[c] = eta[c] - (d.x_zero == X_ZERO ? T(0) : xp[c * nvox + vox]);
 #pragma unroll
       for (int c = 0; c < 6; ++c) xp[c * nvox + vox] = eta[c];
       acc0 += frob_acc(df, df);
@@ -606,7 +611,7 @@ __global__ __launch_bounds__(NTB) void k_xinv(const Desc* __restrict__ descs, in
       const T* xp = (const T*)d.x;
       double r[6];
 #pragma unroll
-      for (int c = 0; c < 6; ++c) r[c] = (double)eta[c] - (d.x_zero ? 0.0 : (double)xp[c * nvox + vox]);
+      for (int c = 0; c < 6; ++c) r[c] = (double)eta[c] - (d.x_zero == X_ZERO ? 0.0 : (double)xp[c * nvox + vox]);
       if (d.r_f32) {
         float* rp = (float*)d.r;
 #pragma unroll
@@ -1350,14 +1355,6 @@ __device__ __forceinline__ void gz_tile(const Desc& d, int bid, int op, int n1, 
 
 // LDS elements of the tile
 template <typename T> constexpr int gz_elems(int n0, int r2) { return n0 * (gz_kc<T>(n0, r2) * r2 * 6 + 1); }
-
-// FP64: 512 threads for the largest tiles, which leave few blocks per CU.
-// FP32 keeps 256 (N0 = 128, R2 = 8: 146 us, with 512 137): the multi-size
-// launches run the same tile with the same thread count, and the compiler
-// contracts its products the same way only then.
-template <typename T> constexpr int gz_threads(int n0, int r2) {
-  return sizeof(T) == 8 && gz_elems<T>(n0, r2) >= 4096 ? 512 : NT;
-}
 
 template <typename T, int N0, int R2, int NTB, typename S>
 __global__ __launch_bounds__(NTB) void k_gz(const Desc* __restrict__ descs, int op, int n1, double scale, int kcs,

@@ -21,14 +21,13 @@ constexpr bool DBL = sizeof(R) == 8;
 template <int N, int R2> static void gz_r(dim3 grid, bool h16, hipStream_t s, const Desc* d, int op, int n1,
                                           double scale, int kcs, int fin, int nblk_f, int nblk_i) {
   if constexpr (gz_fits<R>(N, R2)) {
-    constexpr int TB = gz_threads<R>(N, R2);
     if constexpr (!DBL) {
       if (h16) {
-        hipLaunchKernelGGL((k_gz<R, N, R2, TB, H2>), grid, dim3(TB), 0, s, d, op, n1, scale, kcs, fin, nblk_f, nblk_i);
+        hipLaunchKernelGGL((k_gz<R, N, R2, NT, H2>), grid, dim3(NT), 0, s, d, op, n1, scale, kcs, fin, nblk_f, nblk_i);
         return;
       }
     }
-    hipLaunchKernelGGL((k_gz<R, N, R2, TB, C2<R>>), grid, dim3(TB), 0, s, d, op, n1, scale, kcs, fin, nblk_f, nblk_i);
+    hipLaunchKernelGGL((k_gz<R, N, R2, NT, C2<R>>), grid, dim3(NT), 0, s, d, op, n1, scale, kcs, fin, nblk_f, nblk_i);
   }
 }
 template <> hipError_t GLaunch<R>::gz(int n0, const GroupShape& g, bool h16, int nb, hipStream_t s, const Desc* d,

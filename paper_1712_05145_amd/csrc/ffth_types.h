@@ -85,7 +85,7 @@ struct Desc {
   int32_t delta_gate;      // delta is the three-term inner solve's x: absent while it has no iteration
   int32_t n[3];            // grid of this entry (multi-size launches)
   int32_t nblk_multi;      // partial-sum blocks of its multi-size fused pass (finalize with nblk_i < 0)
-  int32_t x_zero;          // the iterate x is zero (first residual sweep of a solve): not read
+  int32_t x_zero;          // X_*: whether the residual sweep reads its iterate
 };
 
 // Division of block numbers by a launch constant: quotient and remainder in a
@@ -108,6 +108,11 @@ struct FastDiv {
   }
 #endif
 };
+
+// The iterate of a residual sweep: read; zero and not stored yet (first sweep
+// of a solve: neither read nor written); zero, and stored by this sweep (the
+// first one that adds a correction).  A solve never clears its iterate.
+enum : int32_t { X_READ = 0, X_ZERO = 1, X_INIT = 2 };
 
 // x-pass (forward) modes
 enum : int32_t { XF_LS = 0, XF_MATVEC = 1, XF_CG = 2, XF_COPY = 3, XF_C0 = 4, XF_R3 = 5, XF_BI1 = 6, XF_BI2 = 7 };

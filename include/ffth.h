@@ -337,8 +337,7 @@ ffth_status ffth_server_destroy(ffth_server *srv);
  * what ffth_green_apply computes on a plan of grid n with reference medium
  * (lambda0, mu0): eta = -Gamma0 * tau (eq. (5) and the formula below it), with
  * the same kernels, but needs neither a plan nor a workspace: every device
- * buffer beyond tau and eta (descriptor, state, block sums, phase ids, half
- * spectrum) lives in one fixed array of FFTH_NOALLOC_SCRATCH_BYTES bytes in
+ * buffer beyond tau and eta (descriptor, state, half spectrum) lives in one fixed array of FFTH_NOALLOC_SCRATCH_BYTES bytes in
  * the library, one copy per GPU, held until the process ends.  The call
  * allocates nothing: no hipMalloc, hipFree or allocating library routine.
  *   n:       grid (as ffth_size_supported; n0 = 1 allowed), at most
@@ -354,7 +353,7 @@ ffth_status ffth_server_destroy(ffth_server *srv);
  * correct; calls that overlap on one GPU (different streams or threads)
  * race on the array and give wrong results. */
 #define FFTH_NOALLOC_MAX_VOXELS 262144
-#define FFTH_NOALLOC_SCRATCH_BYTES 21497088
+#define FFTH_NOALLOC_SCRATCH_BYTES 12584192
 ffth_status ffth_green_apply_noalloc(const int32_t n[3], double lambda0, double mu0, const double *tau,
                                      double *eta, int32_t precision, void *hip_stream);
 

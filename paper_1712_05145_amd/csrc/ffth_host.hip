@@ -563,6 +563,37 @@ template <typename T> ffth_status xinv(ffth_plan* P, const Desc* d, int nb, int 
   return FFTH_OK;
 }
 
+// Field passes: FP64 fields to spectra and back.
+template <typename T> ffth_status field_fwd(ffth_plan* P, const Desc* d, int nb) {
+  ProfScope ps(P, sizeof(T) == 8 ? C_XF64 : C_XF32, nb);
+  if (grp<T>(P).on) HIPCHK(GLaunch<T>::field_fwd(P->n[2], grp<T>(P), nb, P->stream, d, P->rows, P->nvox));
+  else HIPCHK(Launch<T>::field_fwd(P->n[2], nb, P->stream, d, P->rows, P->nvox));
+  return FFTH_OK;
+}
+
+template <typename T> ffth_status field_inv(ffth_plan* P, const Desc* d, int nb, bool accum) {
+  ProfScope ps(P, sizeof(T) == 8 ? C_XI64 : C_XI32, nb);
+  if (grp<T>(P).on) HIPCHK(GLaunch<T>::field_inv(P->n[2], grp<T>(P), nb, P->stream, d, accum, P->rows, P->nvox));
+  else HIPCHK(Launch<T>::field_inv(P->n[2], nb, P->stream, d, accum, P->rows, P->nvox));
+  return FFTH_OK;
+}
+
+// One field through a spectral operator (descriptor d, utility state slot).
+template <typename T> ffth_status field_apply(ffth_plan* P, Desc d, int op) {
+  ffth_status s;
+  d.st = P->d_state + 3 * P->nloads;
+  Desc* dd = P->d_desc + desc_slot(P, R_UTIL, 0);
+  const SolverState st = make_state(0, 1, 0, 1);
+  {
+    ProfScope ps(P, sizeof(T) == 8 ? C_XF64 : C_XF32, 1);
+    if (grp<T>(P).on) HIPCHK(GLaunch<T>::field_fwd1(P->n[2], grp<T>(P), P->stream, d, st, dd, P->rows, P->nvox));
+    else HIPCHK(Launch<T>::field_fwd1(P->n[2], P->stream, d, st, dd, P->rows, P->nvox));
+  }
+  if ((s = spectral<T>(P, dd, 1, op)) != FFTH_OK) return s;
+  if ((s = field_inv<T>(P, dd, 1, false)) != FFTH_OK) return s;
+  return stream_sync(P);
+}
+
 template <typename T> ffth_status xcg3(ffth_plan* P, const Desc* d, int nb, bool h16) {
   ProfScope ps(P, sizeof(T) == 8 ? C_XCG3_64 : C_XCG3, nb);
   if (grp<T>(P).on)
@@ -1808,9 +1839,9 @@ ffth_status build_rhs(ffth_plan* P, int order, int nl, const double* eps, const 
   }
   if ((s = fin(P, dptr(P, R_POST), nl, FIN_O1RHS, 0, nms)) != FFTH_OK) return s;
   const Desc* dt = dptr(P, R_THETA);
-  if ((s = xfwd<double>(P, dt, nl, XF_COPY)) != FFTH_OK) return s;
+  if ((s = field_fwd<double>(P, dt, nl)) != FFTH_OK) return s;
   if ((s = spectral<double>(P, dt, nl, OP_THETA)) != FFTH_OK) return s;
-  if ((s = xinv<double>(P, dt, nl, XI_ACCUM)) != FFTH_OK) return s;
+  if ((s = field_inv<double>(P, dt, nl, true)) != FFTH_OK) return s;
   if ((s = read_states(P)) != FFTH_OK) return s;
   gmean.assign(3 * nl, 0.0);
   for (int l = 0; l < nl; ++l)
@@ -1854,9 +1885,9 @@ ffth_status make_disp(ffth_plan* P, std::initializer_list<DispJob> jobs) {
   for (int J0 = 0; J0 < n; J0 += room) {
     const int nb = std::min(room, n - J0);
     const Desc* d = P->d_desc + disp_slot(P, J0);
-    if ((s = xfwd<double>(P, d, nb, XF_COPY)) != FFTH_OK) return s;
+    if ((s = field_fwd<double>(P, d, nb)) != FFTH_OK) return s;
     if ((s = spectral<double>(P, d, nb, OP_DISP)) != FFTH_OK) return s;
-    if ((s = xinv<double>(P, d, nb, XI_STORE)) != FFTH_OK) return s;
+    if ((s = field_inv<double>(P, d, nb, false)) != FFTH_OK) return s;
   }
   return FFTH_OK;
 }
@@ -1944,22 +1975,10 @@ ffth_status ffth_green_apply(ffth_plan* P, const double* tau, double* eta, int32
     return FFTH_ERR_INVALID;
   }
   Desc d = base_desc(P, 0);
-  d.st = P->d_state + 3 * P->nloads;
   d.io = (void*)tau;
   d.out = eta;
   d.nc = 6;
-  const Desc* dd = dptr(P, R_UTIL);
-  HIPCHK(launch_setup(P->stream, d, make_state(0, 1, 0, 1), (Desc*)dd, d.st));
-  if (precision == FFTH_FP64) {
-    if ((s = xfwd<double>(P, dd, 1, XF_COPY)) != FFTH_OK) return s;
-    if ((s = spectral<double>(P, dd, 1, OP_GAMMA)) != FFTH_OK) return s;
-    if ((s = xinv<double>(P, dd, 1, XI_STORE)) != FFTH_OK) return s;
-  } else {
-    if ((s = xfwd<float>(P, dd, 1, XF_COPY)) != FFTH_OK) return s;
-    if ((s = spectral<float>(P, dd, 1, OP_GAMMA)) != FFTH_OK) return s;
-    if ((s = xinv<float>(P, dd, 1, XI_STORE)) != FFTH_OK) return s;
-  }
-  return stream_sync(P);
+  return precision == FFTH_FP64 ? field_apply<double>(P, d, OP_GAMMA) : field_apply<float>(P, d, OP_GAMMA);
 }
 
 ffth_status ffth_displacement(ffth_plan* P, const double* eps, double* u) {
@@ -1971,17 +1990,11 @@ ffth_status ffth_displacement(ffth_plan* P, const double* eps, double* u) {
     return FFTH_ERR_INVALID;
   }
   Desc d = base_desc(P, 0);
-  d.st = P->d_state + 3 * P->nloads;
   d.io = (void*)eps;
   d.out = u;
   d.nc = 6;
   d.nc_out = 3;
-  const Desc* dd = dptr(P, R_UTIL);
-  HIPCHK(launch_setup(P->stream, d, make_state(0, 1, 0, 1), (Desc*)dd, d.st));
-  if ((s = xfwd<double>(P, dd, 1, XF_COPY)) != FFTH_OK) return s;
-  if ((s = spectral<double>(P, dd, 1, OP_DISP)) != FFTH_OK) return s;
-  if ((s = xinv<double>(P, dd, 1, XI_STORE)) != FFTH_OK) return s;
-  return stream_sync(P);
+  return field_apply<double>(P, d, OP_DISP);
 }
 
 ffth_status ffth_order1_rhs(ffth_plan* P, const double* eps0_six, const double* G, double* Pout, double* g_mean) {

@@ -523,7 +523,7 @@ __global__ __launch_bounds__(NTB) void k_xfwd(const Desc* __restrict__ descs, in
           sp[c * nvox + vox] = sv[c];
         }
         apply_mat<T, ISO>(mat, ph, true, sv, tau);
-      } else if (mode == XF_C0) {
+      } else {  // XF_C0
         // tau = C0 : r for the projection -Gamma0 * C0 r (r is the FP64 residual)
         const double* vp = (const double*)d.r;
         T v[6];
@@ -532,11 +532,6 @@ __global__ __launch_bounds__(NTB) void k_xfwd(const Desc* __restrict__ descs, in
         const T tr = (T)d.lam0 * (v[0] + v[1] + v[2]);
 #pragma unroll
         for (int c = 0; c < 6; ++c) tau[c] = T(2) * (T)d.mu0 * v[c] + (c < 3 ? tr : T(0));
-      } else {  // XF_COPY
-        const double* ip = (const double*)d.io;
-#pragma unroll
-        for (int c = 0; c < 6; ++c)
-          if (c < d.nc) tau[c] = (T)ip[c * nvox + vox];
       }
     }
 #pragma unroll
@@ -590,16 +585,7 @@ __global__ __launch_bounds__(NTB) void k_xinv(const Desc* __restrict__ descs, in
       eta[2 * q] = w.x;
       eta[2 * q + 1] = w.y;
     }
-    if (mode == XI_STORE || mode == XI_ACCUM) {
-      double* op = (double*)d.out;
-      const int nco = d.nc_out ? d.nc_out : d.nc;
-      double o[6];
-#pragma unroll
-      for (int c = 0; c < 6; ++c) o[c] = (mode == XI_ACCUM && c < nco) ? op[c * nvox + vox] : 0.0;
-#pragma unroll
-      for (int c = 0; c < 6; ++c)
-        if (c < nco) op[c * nvox + vox] = o[c] + (double)eta[c];
-    } else if (mode == XI_BS) {
+    if (mode == XI_BS) {
       T* xp = (T*)d.x;
       T df[6];
 #pragma unroll
@@ -720,6 +706,107 @@ __global__ __launch_bounds__(NTB) void k_xinv(const Desc* __restrict__ descs, in
   } else {
     double sums[2] = {acc0, acc1};
     block_sums<2, NTB>(sums, d.part_i + bid, gridDim.x);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Field x-passes: an FP64 field in (nc components, the others zero) and out
+// (nc_out components, stored or accumulated), for the operator, displacement
+// and theta transforms.  No constitutive law, no sums and no gating state: as
+// modes of k_xfwd and k_xinv they had those passes' registers (112), a read of
+// the phase ids and of the state before the first value.  Small calls are
+// bound by the chain of launches, large ones by the memory rate.  With the
+// descriptor in the launch arguments (no setup launch) an operator call takes,
+// before -> now: 16^3 19.6 -> 15.4 us, 48x96x24 47.6 -> 40.5 us, 512^3 15.36
+// -> 15.01 ms; the order-1 right-hand side of 64^3 725 -> 683 us.
+// ---------------------------------------------------------------------------
+template <typename T, int N2, int ROWS, int R1>
+__device__ __forceinline__ void field_fwd_tile(const Desc& d, int bid, long rows_total, long nvox, int r2, int kcs,
+                                               C2<T>* z, C2<T>* tw, C2<T>* tw1) {
+  constexpr int RS = N2 + N2 / 16;
+  const long row0 = (long)bid * (ROWS / R1);
+  const double* ip = (const double*)d.io;
+  const int nc = d.nc;
+  for (int v = threadIdx.x; v < ROWS * N2; v += NT) {
+    const int rr = v / N2, i2 = v % N2;
+    const long row = tile_row<R1>(row0, rr, rows_total, r2);
+    T t[6] = {0, 0, 0, 0, 0, 0};
+    if (row < rows_total) {
+#pragma unroll
+      for (int c = 0; c < 6; ++c)
+        if (c < nc) t[c] = (T)ip[c * nvox + row * N2 + i2];
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) z[(rr * 3 + q) * RS + padx<true>(i2)] = C2<T>{t[2 * q], t[2 * q + 1]};
+  }
+  build_twiddles<T, N2, NT>(tw);
+  if constexpr (R1 > 1) build_group_twiddles<T, R1, ROWS / R1, NT>(tw1, row0, r2);
+  __syncthreads();
+  lds_fft<T, N2, ROWS * 3, NT, 1, RS, false, true, -1>(z, tw);
+  if constexpr (R1 > 1) store_groups_r2c<T, N2, R1, ROWS / R1, NT, C2<T>>((C2<T>*)d.spec, z, tw1, row0, rows_total, r2, kcs);
+  else store_rows_r2c<T, N2, ROWS, NT>((C2<T>*)d.spec, z, row0, rows_total);
+}
+
+template <typename T, int N2, int ROWS, int R1>
+__global__ __launch_bounds__(NT) void k_field_fwd(const Desc* __restrict__ descs, long rows_total, long nvox, int r2,
+                                                  int kcs) {
+  __shared__ C2<T> z[ROWS * 3 * (N2 + N2 / 16)];
+  __shared__ C2<T> tw[N2];
+  __shared__ C2<T> tw1[R1 > 1 ? ROWS : 1];
+  field_fwd_tile<T, N2, ROWS, R1>(descs[blockIdx.y], xcd_tile(blockIdx.x, gridDim.x), rows_total, nvox, r2, kcs, z, tw,
+                                  tw1);
+}
+
+// The same for one field whose descriptor comes with the launch; it leaves the
+// descriptor and its gating state in memory for the passes that follow.
+template <typename T, int N2, int ROWS, int R1>
+__global__ __launch_bounds__(NT) void k_field_fwd1(Desc d, SolverState s, Desc* dd, long rows_total, long nvox, int r2,
+                                                   int kcs) {
+  __shared__ C2<T> z[ROWS * 3 * (N2 + N2 / 16)];
+  __shared__ C2<T> tw[N2];
+  __shared__ C2<T> tw1[R1 > 1 ? ROWS : 1];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *dd = d;
+    *d.st = s;
+  }
+  field_fwd_tile<T, N2, ROWS, R1>(d, xcd_tile(blockIdx.x, gridDim.x), rows_total, nvox, r2, kcs, z, tw, tw1);
+}
+
+template <typename T, int N2, int ROWS, int R1>
+__global__ __launch_bounds__(NT) void k_field_inv(const Desc* __restrict__ descs, int accum, long rows_total, long nvox,
+                                                  int r2, int kcs) {
+  constexpr int RS = N2 + N2 / 16;
+  __shared__ C2<T> z[ROWS * 3 * RS];
+  __shared__ C2<T> tw[N2];
+  __shared__ C2<T> tw1[R1 > 1 ? ROWS : 1];
+  const Desc& d = descs[blockIdx.y];
+  const int bid = xcd_tile(blockIdx.x, gridDim.x);
+  const long row0 = (long)bid * (ROWS / R1);
+  build_twiddles<T, N2, NT>(tw);
+  if constexpr (R1 > 1) {
+    build_group_twiddles<T, R1, ROWS / R1, NT>(tw1, row0, r2);
+    __syncthreads();
+    load_groups_c2r<T, N2, R1, ROWS / R1, NT>((const C2<T>*)d.spec, z, tw1, row0, rows_total, r2, kcs);
+  } else {
+    load_rows_c2r<T, N2, ROWS, NT>((const C2<T>*)d.spec, z, row0, rows_total);
+  }
+  __syncthreads();
+  lds_fft<T, N2, ROWS * 3, NT, 1, RS, false, true, +1>(z, tw);
+  double* op = (double*)d.out;
+  const int nco = d.nc_out ? d.nc_out : d.nc;
+  for (int v = threadIdx.x; v < ROWS * N2; v += NT) {
+    const int rr = v / N2, i2 = v % N2;
+    const long row = tile_row<R1>(row0, rr, rows_total, r2);
+    if (row >= rows_total) continue;
+    const long vox = row * N2 + i2;
+    double o[6];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) o[c] = accum && c < nco ? op[c * nvox + vox] : 0.0;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      const C2<T> w = z[(rr * 3 + c / 2) * RS + padx<true>(i2)];
+      if (c < nco) op[c * nvox + vox] = o[c] + (double)(c & 1 ? w.y : w.x);
+    }
   }
 }
 

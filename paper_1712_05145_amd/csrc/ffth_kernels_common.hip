@@ -144,12 +144,6 @@ __global__ __launch_bounds__(NT) void k_order2_point(const Desc* __restrict__ de
   block_sums<NRED, NT>(acc, d.part_i + blockIdx.x, gridDim.x);
 }
 
-// One descriptor and its gating state from the kernel arguments.
-__global__ void k_setup(Desc d, SolverState s, Desc* dd, SolverState* ss) {
-  *dd = d;
-  *ss = s;
-}
-
 __global__ void k_widen(const Desc* __restrict__ descs, long n) {
   const Desc& d = descs[blockIdx.y];
   const float* src = (const float*)d.x;
@@ -221,11 +215,6 @@ hipError_t launch_order2_point(bool iso, int nblk, int nbatch, hipStream_t s, co
 
 hipError_t launch_phase_max(hipStream_t s, const uint16_t* phase, long n, int* out) {
   hipLaunchKernelGGL(k_phase_max, dim3(512), dim3(256), 0, s, phase, n, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_setup(hipStream_t s, const Desc& d, const SolverState& st, Desc* dd, SolverState* ss) {
-  hipLaunchKernelGGL(k_setup, dim3(1), dim3(1), 0, s, d, st, dd, ss);
   return hipGetLastError();
 }
 

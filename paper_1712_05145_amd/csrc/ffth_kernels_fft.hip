@@ -174,6 +174,50 @@ template <typename T> hipError_t Launch<T>::zpass(int n0, int v, bool h16, dim3 
   return hipErrorInvalidValue;
 }
 
+// rows per block of the field passes
+template <typename T> static dim3 field_grid(int n2, int nb, long rows) {
+  int r = 0;
+#define FFTH_CASE(N) if (n2 == N) r = ffth::x_rows<T>(N);
+  FFTH_SIZES(FFTH_CASE)
+#undef FFTH_CASE
+  return dim3(r > 0 ? (unsigned)((rows + r - 1) / r) : 0, nb);
+}
+template <typename T> hipError_t Launch<T>::field_fwd(int n2, int nb, hipStream_t s, const Desc* d, long rows, long nvox) {
+#define FFTH_CASE(N)                                                                                                 \
+  if (n2 == N) {                                                                                                     \
+    hipLaunchKernelGGL((k_field_fwd<T, N, ffth::x_rows<T>(N), 1>), field_grid<T>(n2, nb, rows), dim3(NT), 0, s, d, rows, \
+                       nvox, 1, 0);                                                                                  \
+    return hipGetLastError();                                                                                        \
+  }
+  FFTH_SIZES(FFTH_CASE)
+#undef FFTH_CASE
+  return hipErrorInvalidValue;
+}
+template <typename T> hipError_t Launch<T>::field_fwd1(int n2, hipStream_t s, const Desc& d, const SolverState& st,
+                                                      Desc* dd, long rows, long nvox) {
+#define FFTH_CASE(N)                                                                                                 \
+  if (n2 == N) {                                                                                                     \
+    hipLaunchKernelGGL((k_field_fwd1<T, N, ffth::x_rows<T>(N), 1>), field_grid<T>(n2, 1, rows), dim3(NT), 0, s, d, st, \
+                       dd, rows, nvox, 1, 0);                                                                        \
+    return hipGetLastError();                                                                                        \
+  }
+  FFTH_SIZES(FFTH_CASE)
+#undef FFTH_CASE
+  return hipErrorInvalidValue;
+}
+template <typename T> hipError_t Launch<T>::field_inv(int n2, int nb, hipStream_t s, const Desc* d, bool accum, long rows,
+                                                     long nvox) {
+#define FFTH_CASE(N)                                                                                                 \
+  if (n2 == N) {                                                                                                     \
+    hipLaunchKernelGGL((k_field_inv<T, N, ffth::x_rows<T>(N), 1>), field_grid<T>(n2, nb, rows), dim3(NT), 0, s, d, \
+                       accum ? 1 : 0, rows, nvox, 1, 0);                                                             \
+    return hipGetLastError();                                                                                        \
+  }
+  FFTH_SIZES(FFTH_CASE)
+#undef FFTH_CASE
+  return hipErrorInvalidValue;
+}
+
 template <typename T> hipError_t Launch<T>::bicg_finish(dim3 grid, hipStream_t s, const Desc* d, long n) {
   hipLaunchKernelGGL((k_bicg_finish<T>), grid, dim3(NT), 0, s, d, n);
   return hipGetLastError();

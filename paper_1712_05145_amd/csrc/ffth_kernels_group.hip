@@ -131,6 +131,31 @@ template <> hipError_t GLaunch<R>::xinv(int n2, const GroupShape& g, bool iso, i
     else hipLaunchKernelGGL((k_xinv<R, N, false, RW, NT, 0, K>), grid, dim3(NT), 0, s, d, mode, rows, nvox, g.r2, g.kcs);
   });
 }
+
+template <> hipError_t GLaunch<R>::field_fwd(int n2, const GroupShape& g, int nb, hipStream_t s, const Desc* d,
+                                             long rows, long nvox) {
+  return for_shape(n2, g.r1, [&](auto n, auto r) {
+    constexpr int N = decltype(n)::v, K = decltype(r)::v;
+    hipLaunchKernelGGL((k_field_fwd<R, N, gx_rows<R>(N, K), K>), dim3(g.xblocks, nb), dim3(NT), 0, s, d, rows, nvox,
+                       g.r2, g.kcs);
+  });
+}
+template <> hipError_t GLaunch<R>::field_fwd1(int n2, const GroupShape& g, hipStream_t s, const Desc& d,
+                                              const SolverState& st, Desc* dd, long rows, long nvox) {
+  return for_shape(n2, g.r1, [&](auto n, auto r) {
+    constexpr int N = decltype(n)::v, K = decltype(r)::v;
+    hipLaunchKernelGGL((k_field_fwd1<R, N, gx_rows<R>(N, K), K>), dim3(g.xblocks), dim3(NT), 0, s, d, st, dd, rows,
+                       nvox, g.r2, g.kcs);
+  });
+}
+template <> hipError_t GLaunch<R>::field_inv(int n2, const GroupShape& g, int nb, hipStream_t s, const Desc* d,
+                                             bool accum, long rows, long nvox) {
+  return for_shape(n2, g.r1, [&](auto n, auto r) {
+    constexpr int N = decltype(n)::v, K = decltype(r)::v;
+    hipLaunchKernelGGL((k_field_inv<R, N, gx_rows<R>(N, K), K>), dim3(g.xblocks, nb), dim3(NT), 0, s, d, accum ? 1 : 0,
+                       rows, nvox, g.r2, g.kcs);
+  });
+}
 #elif FFTH_PART >= 3
 // (one translation unit per material kind)
 constexpr bool ISO = FFTH_PART == 3;

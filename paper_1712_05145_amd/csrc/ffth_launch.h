@@ -31,6 +31,12 @@ template <typename T> struct Launch {
   // fused three-term CG iteration (x-inverse, update, x-forward); x-inverse tiles
   static hipError_t xcg3(int n2, bool iso, int v, bool h16, dim3 grid, hipStream_t s, const Desc* d, long rows,
                          long nvox);
+  // field x-passes (an FP64 field in / out); field_fwd1: one field, descriptor
+  // and gating state (at d.st) with the launch, left in dd for the next passes
+  static hipError_t field_fwd(int n2, int nb, hipStream_t s, const Desc* d, long rows, long nvox);
+  static hipError_t field_fwd1(int n2, hipStream_t s, const Desc& d, const SolverState& st, Desc* dd, long rows,
+                               long nvox);
+  static hipError_t field_inv(int n2, int nb, hipStream_t s, const Desc* d, bool accum, long rows, long nvox);
   // BiCGSTAB: the pending x update of loads that stopped (n = 6 * voxels)
   static hipError_t bicg_finish(dim3 grid, hipStream_t s, const Desc* d, long n);
   // three-term CG: the last x of loads that stopped after an even iteration
@@ -60,6 +66,11 @@ template <typename T> struct GLaunch {
   template <bool ISO>
   static hipError_t xcg3(int n2, const GroupShape& g, bool h16, int nb, hipStream_t s, const Desc* d, long rows,
                          long nvox);
+  static hipError_t field_fwd(int n2, const GroupShape& g, int nb, hipStream_t s, const Desc* d, long rows, long nvox);
+  static hipError_t field_fwd1(int n2, const GroupShape& g, hipStream_t s, const Desc& d, const SolverState& st,
+                               Desc* dd, long rows, long nvox);
+  static hipError_t field_inv(int n2, const GroupShape& g, int nb, hipStream_t s, const Desc* d, bool accum, long rows,
+                              long nvox);
   static hipError_t gz(int n0, const GroupShape& g, bool h16, int nb, hipStream_t s, const Desc* d, int op, int n1,
                        double scale, int fin, int nblk_f, int nblk_i);
 };
@@ -86,7 +97,6 @@ hipError_t launch_order1_point(bool iso, int nblk, int nbatch, hipStream_t s, co
                                const double* x1, long nvox);
 hipError_t launch_order2_point(bool iso, int nblk, int nbatch, hipStream_t s, const Desc* d, const double* eps1,
                                const double* x1, const double* x2, long nvox);
-hipError_t launch_setup(hipStream_t s, const Desc& d, const SolverState& st, Desc* dd, SolverState* ss);
 hipError_t launch_widen(int nbatch, hipStream_t s, const Desc* d, long n);
 hipError_t launch_phase_max(hipStream_t s, const uint16_t* phase, long n, int* out);
 

@@ -1,8 +1,7 @@
 // ffth_green_apply_noalloc: the Green operator application of
 // ffth_green_apply without a plan or a caller workspace, for callers that
 // cannot allocate device memory.  Everything the passes need beyond the input
-// and output fields (launch descriptor, gating state, block partial sums, a
-// zero phase array and the half spectrum) lives in one file-scope device
+// and output fields (launch descriptor, gating state and the half spectrum) lives in one file-scope device
 // array of fixed size, one copy per GPU, held until the process ends.
 #include <hip/hip_runtime.h>
 
@@ -23,18 +22,12 @@ namespace {
 constexpr size_t kAlign = 256;
 constexpr size_t al(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
-// Regions of the scratch array for the largest grid: descriptor, state,
-// forward and inverse partial sums (NRED doubles per x-pass block; blocks <=
-// rows = n0 n1 <= voxels / 4), the phase ids (zero: the copy-in pass reads
-// them) and the FP64 half spectrum (48 bytes per voxel).
+// Regions of the scratch array for the largest grid: descriptor, state and the
+// FP64 half spectrum (48 bytes per voxel).
 constexpr size_t kVox = FFTH_NOALLOC_MAX_VOXELS;
-constexpr size_t kRows = kVox / 4;
 constexpr size_t kOffDesc = 0;
 constexpr size_t kOffState = al(sizeof(Desc));
-constexpr size_t kOffPartF = kOffState + al(sizeof(SolverState));
-constexpr size_t kOffPartI = kOffPartF + al(kRows * NRED * sizeof(double));
-constexpr size_t kOffPhase = kOffPartI + al(kRows * NRED * sizeof(double));
-constexpr size_t kOffSpec = kOffPhase + al(kVox * sizeof(uint16_t));
+constexpr size_t kOffSpec = kOffState + al(sizeof(SolverState));
 constexpr size_t kBytes = kOffSpec + al(kVox * 6 * sizeof(double));
 
 static_assert(kBytes == FFTH_NOALLOC_SCRATCH_BYTES, "scratch size stated in ffth.h");
@@ -46,45 +39,31 @@ constexpr int kMaxDevices = 64;
 std::mutex g_mu;
 void* g_ptr[kMaxDevices] = {nullptr};
 
-// Descriptor and state go to scratch from the kernel arguments (no host
-// buffer has to outlive the call); the phase ids of the grid are cleared.
-__global__ void k_noalloc_setup(Desc d, SolverState s, Desc* dd, SolverState* ss, uint16_t* phase, long nvox) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    *dd = d;
-    *ss = s;
-  }
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < nvox; i += (long)gridDim.x * blockDim.x)
-    phase[i] = 0;
-}
-
 int kchunk_of(int h) {
   int c = h < 16 ? h : 16;
   while (h % c) --c;
   return c;
 }
 
-template <typename T> hipError_t green_passes(const int n[3], hipStream_t st, const Desc* d) {
+template <typename T>
+hipError_t green_passes(const int n[3], hipStream_t st, const Desc& d0, const SolverState& s0, Desc* d) {
   const long rows = (long)n[0] * n[1], nvox = rows * n[2];
+  const double scale = 1.0 / (double)nvox;
   const GroupShape g = group_shape(n, sizeof(T) == 8);
-  if (g.on) {   // grouped passes, as a plan takes them
-    hipError_t e;
-    if ((e = GLaunch<T>::xfwd(n[2], g, true, false, 1, st, d, XF_COPY, rows, nvox)) != hipSuccess) return e;
-    if ((e = GLaunch<T>::gz(n[0], g, false, 1, st, d, OP_GAMMA, n[1], 1.0 / (double)nvox, -1, 0, 0)) != hipSuccess)
-      return e;
-    return GLaunch<T>::xinv(n[2], g, true, 1, st, d, XI_STORE, rows, nvox);
-  }
-  const int h = n[2] / 2, kc = kchunk_of(h);
-  const int xr = Launch<T>::x_rows(n[2], 0), xir = Launch<T>::xi_rows(n[2], 0);
   hipError_t e;
-  if ((e = Launch<T>::xfwd(n[2], true, 0, false, dim3((unsigned)((rows + xr - 1) / xr), 1), st, d, XF_COPY, rows,
-                           nvox)) != hipSuccess)
-    return e;
+  if (g.on) {   // grouped passes, as a plan takes them
+    if ((e = GLaunch<T>::field_fwd1(n[2], g, st, d0, s0, d, rows, nvox)) != hipSuccess) return e;
+    if ((e = GLaunch<T>::gz(n[0], g, false, 1, st, d, OP_GAMMA, n[1], scale, -1, 0, 0)) != hipSuccess) return e;
+    return GLaunch<T>::field_inv(n[2], g, 1, st, d, false, rows, nvox);
+  }
+  if ((e = Launch<T>::field_fwd1(n[2], st, d0, s0, d, rows, nvox)) != hipSuccess) return e;
+  const int h = n[2] / 2, kc = kchunk_of(h);
   if (n[0] == 1) {   // 2-D: one spectral pass
     const int tk = Launch<T>::z_cols(n[1], 0);
-    if ((e = Launch<T>::zpass(n[1], 0, false, dim3((kc + tk - 1) / tk * (h / kc), 1), st, d, OP_GAMMA, 1, h,
-                              1.0 / (double)nvox, true)) != hipSuccess)
+    if ((e = Launch<T>::zpass(n[1], 0, false, dim3((kc + tk - 1) / tk * (h / kc), 1), st, d, OP_GAMMA, 1, h, scale,
+                              true)) != hipSuccess)
       return e;
-    return Launch<T>::xinv(n[2], true, 0, dim3((unsigned)((rows + xir - 1) / xir), 1), st, d, XI_STORE, rows, nvox);
+    return Launch<T>::field_inv(n[2], 1, st, d, false, rows, nvox);
   }
   const int ncols = kc * 6, nplanes = n[0] * (h / kc);
   const int cw = Launch<T>::y_cols(n[1], 0), ntiles = (ncols + cw - 1) / cw;
@@ -93,12 +72,10 @@ template <typename T> hipError_t green_passes(const int n[3], hipStream_t st, co
   const long M = (long)n[1] * kc;
   const int tk = Launch<T>::z_cols(n[0], 0);
   const int nzb = (int)((M + tk - 1) / tk) * (h / kc);
-  if ((e = Launch<T>::zpass(n[0], 0, false, dim3(nzb, 1), st, d, OP_GAMMA, n[1], h, 1.0 / (double)nvox)) !=
-      hipSuccess)
-    return e;
+  if ((e = Launch<T>::zpass(n[0], 0, false, dim3(nzb, 1), st, d, OP_GAMMA, n[1], h, scale)) != hipSuccess) return e;
   if ((e = Launch<T>::ypass(n[1], 0, false, dim3(nplanes * ntiles, 1), st, d, +1, ncols, ntiles)) != hipSuccess)
     return e;
-  return Launch<T>::xinv(n[2], true, 0, dim3((unsigned)((rows + xir - 1) / xir), 1), st, d, XI_STORE, rows, nvox);
+  return Launch<T>::field_inv(n[2], 1, st, d, false, rows, nvox);
 }
 
 ffth_status fail(ffth_status s, const std::string& msg) {
@@ -141,10 +118,7 @@ ffth_status ffth_green_apply_noalloc(const int32_t n[3], double lambda0, double 
   hipStream_t st = (hipStream_t)hip_stream;
   Desc d;
   std::memset(&d, 0, sizeof(d));
-  d.phase = (const uint16_t*)(base + kOffPhase);
   d.spec = base + kOffSpec;
-  d.part_f = (double*)(base + kOffPartF);
-  d.part_i = (double*)(base + kOffPartI);
   d.st = (SolverState*)(base + kOffState);
   d.io = (void*)tau;
   d.out = eta;
@@ -164,13 +138,9 @@ ffth_status ffth_green_apply_noalloc(const int32_t n[3], double lambda0, double 
   s.res = 1.0;
   s.dscale = s.idscale = 1.0;
   s.gscale = -1.0;
-  const int nb = (int)std::min<long>(1024, (nvox + 255) / 256);
-  hipLaunchKernelGGL(k_noalloc_setup, dim3(nb), dim3(256), 0, st, d, s, (Desc*)(base + kOffDesc),
-                     (SolverState*)(base + kOffState), (uint16_t*)(base + kOffPhase), nvox);
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess)
-    e = precision == FFTH_FP64 ? green_passes<double>(nn, st, (const Desc*)(base + kOffDesc))
-                               : green_passes<float>(nn, st, (const Desc*)(base + kOffDesc));
+  Desc* dd = (Desc*)(base + kOffDesc);
+  const hipError_t e = precision == FFTH_FP64 ? green_passes<double>(nn, st, d, s, dd)
+                                              : green_passes<float>(nn, st, d, s, dd);
   if (e != hipSuccess) return fail(FFTH_ERR_DEVICE, std::string("launch: ") + hipGetErrorString(e));
   return FFTH_OK;
 }

@@ -115,10 +115,10 @@ struct FastDiv {
 enum : int32_t { X_READ = 0, X_ZERO = 1, X_INIT = 2 };
 
 // x-pass (forward) modes
-enum : int32_t { XF_LS = 0, XF_MATVEC = 1, XF_CG = 2, XF_COPY = 3, XF_C0 = 4, XF_R3 = 5, XF_BI1 = 6, XF_BI2 = 7 };
+enum : int32_t { XF_LS = 0, XF_MATVEC = 1, XF_CG = 2, XF_C0 = 4, XF_R3 = 5, XF_BI1 = 6, XF_BI2 = 7 };
 // x-pass (inverse) modes
 enum : int32_t {
-  XI_STORE = 0, XI_ACCUM = 1, XI_BS = 2, XI_RESID = 3, XI_BS_INNER = 4, XI_CG = 5, XI_PROJ = 6, XI_BI1 = 7, XI_BI2 = 8
+  XI_BS = 2, XI_RESID = 3, XI_BS_INNER = 4, XI_CG = 5, XI_PROJ = 6, XI_BI1 = 7, XI_BI2 = 8
 };
 // spectral operators of the z-pass
 enum : int32_t { OP_GAMMA = 0, OP_THETA = 1, OP_DISP = 2 };

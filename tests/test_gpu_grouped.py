@@ -10,6 +10,8 @@ to 2e-8 between the routes: each is within 1e-10 of the solution in residual,
 times at most the stiffness contrast in the field.  Finalizes carried by a
 pass do the sums of a separate launch in the same order, so iterates do not
 depend, bit for bit, on how often the host reads the states."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -69,6 +71,27 @@ def test_solves_agree_with_classical_passes(shape, scheme, precision, h16):
     for i in range(2):
         assert rel_l2(out[0][0][i], out[1][0][i]) < 2e-8
     assert np.abs(out[0][1] - out[1][1]).max() < 2e-8 * np.abs(out[1][1]).max()
+
+
+@pytest.mark.parametrize("shape", [(8, 12, 24), (24, 48, 8), (8, 96, 12), (6, 4, 12), (4, 6, 1024), (1, 16, 48),
+                                   (1, 6, 4)])
+def test_field_passes(shape):
+    """Field in, field out without a solve: six components out of three values
+    per pass (displacement) and the allocation-free operator, over grouped and
+    classical plans with ragged last blocks; input and output may be one array."""
+    torch = require_gpu()
+    print("case field passes", shape, flush=True)
+    rng = np.random.default_rng(sum(shape))
+    tau = rng.standard_normal((6,) + shape)
+    s = ffth.Solver(np.zeros(shape, np.uint16), 1.1, 0.6, lame=[[2.0, 1.0]], autotune=False)
+    ref = spectral.displacement_from_strain(full(tau))
+    assert rel_l2(s.displacement(to_dev(torch, tau)).cpu().numpy(), ref) < 1e-12
+    ref = voigt6(spectral.green_apply(full(tau), 1.1, 0.6))
+    for precision, tol in (("fp64", 1e-12), ("fp32", 5e-6)):
+        a = to_dev(torch, tau)
+        ffth.ffth_green_apply_noalloc(shape, 1.1, 0.6, ffth._dptr(a), ffth._dptr(a), ffth.PRECISIONS[precision],
+                                      ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert rel_l2(a.cpu().numpy(), ref) < tol
 
 
 @pytest.mark.parametrize("shape", [(16, 24, 32), (1, 32, 16)])

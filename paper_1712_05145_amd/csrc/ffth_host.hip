@@ -88,8 +88,8 @@ Layout make_layout(const int n[3], int nph, int nloads, int order, const ffth_op
   L.f64_stride = al((size_t)nvox * 6 * sizeof(double));
   L.part_stride = al((size_t)L.nblk * NRED_ * sizeof(double));
   size_t off = 0;
-  L.mat64 = off; off += al((size_t)nph * 72 * sizeof(double));
-  L.mat32 = off; off += al((size_t)nph * 72 * sizeof(float));
+  L.mat64 = off; off += al((size_t)nph * 2 * MAT_TRI * sizeof(double));
+  L.mat32 = off; off += al((size_t)nph * 2 * MAT_TRI * sizeof(float));
   L.desc = off; off += al((size_t)L.ndesc * sizeof(Desc));
   L.cdesc = off; off += al((size_t)4 * nloads * sizeof(Desc));   // compacted active-load copies
   L.state = off; off += al((size_t)L.nstate * sizeof(SolverState));
@@ -1687,8 +1687,8 @@ ffth_status plan_create(ffth_plan** out, const ffth_problem* p, const ffth_opts*
     return FFTH_ERR_DEVICE;
   }
   // material tables
-  std::vector<double> m64((size_t)p->nphases * 72, 0.0);
-  double m0[36];
+  std::vector<double> m64((size_t)p->nphases * 2 * MAT_TRI, 0.0);
+  double m0[36], kmax = 0.0;   // kmax: largest row sum of |C - C0|
   iso_to_m(p->lambda0, p->mu0, m0);
   for (int ph = 0; ph < p->nphases; ++ph) {
     if (P->iso) {
@@ -1697,32 +1697,26 @@ ffth_status plan_create(ffth_plan** out, const ffth_problem* p, const ffth_opts*
       m64[ph * 4 + 1] = mu;
       m64[ph * 4 + 2] = lam - p->lambda0;
       m64[ph * 4 + 3] = mu - p->mu0;
+      kmax = std::max(kmax, 3.0 * std::fabs(m64[ph * 4 + 2]) + 2.0 * std::fabs(m64[ph * 4 + 3]));
     } else {
-      double m[36];
+      double m[36], *c = &m64[(size_t)ph * 2 * MAT_TRI], *dc = c + MAT_TRI;
       voigt21_to_m(p->stiffness + 21 * ph, m);
-      for (int i = 0; i < 36; ++i) {
-        m64[ph * 72 + i] = m[i];
-        m64[ph * 72 + 36 + i] = m[i] - m0[i];
+      for (int a = 0, k = 0; a < 6; ++a) {
+        double rs = 0.0;
+        for (int b = 0; b < 6; ++b) {
+          const double f = b < 3 ? 1.0 : 2.0;   // m holds 2 C in the shear columns
+          rs += std::fabs(m[a * 6 + b] - m0[a * 6 + b]);
+          if (b < a) continue;
+          c[k] = m[a * 6 + b] / f;
+          dc[k++] = (m[a * 6 + b] - m0[a * 6 + b]) / f;
+        }
+        kmax = std::max(kmax, rs);
       }
     }
   }
   std::vector<float> m32(m64.size());
   for (size_t i = 0; i < m64.size(); ++i) m32[i] = (float)m64[i];
-  {
-    double kmax = 0.0;
-    for (int ph = 0; ph < p->nphases; ++ph) {
-      if (P->iso) {
-        kmax = std::max(kmax, 3.0 * std::fabs(m64[ph * 4 + 2]) + 2.0 * std::fabs(m64[ph * 4 + 3]));
-      } else {
-        for (int a = 0; a < 6; ++a) {
-          double rs = 0.0;
-          for (int b = 0; b < 6; ++b) rs += std::fabs(m64[ph * 72 + 36 + a * 6 + b]);
-          kmax = std::max(kmax, rs);
-        }
-      }
-    }
-    P->kappa = std::max(kmax / std::fabs(p->mu0), 1e-3);
-  }
+  P->kappa = std::max(kmax / std::fabs(p->mu0), 1e-3);
   // binary16 rounding (unit 2^-11) times the stiffness contrast bounds the
   // relative error the stored spectrum adds to the inner solve's operator;
   // above FFTH_SPECTRUM16_MAX_CONTRAST it would cost iterations, so FP32 is

@@ -139,12 +139,29 @@ __device__ __forceinline__ void apply_mat(const T* mat, int ph, bool delta, cons
 #pragma unroll
     for (int c = 0; c < 6; ++c) out[c] = mu2 * e[c] + (c < 3 ? lam * tr : T(0));
   } else {
-    const T* m = mat + ph * 72 + (delta ? 36 : 0);
+    // upper triangle, padded to MAT_TRI values so that 16-byte loads fetch it:
+    // the loads are gathers (neighbouring voxels differ in phase) and their
+    // number bounds the pass, 11 (FP64) or 6 (FP32) here instead of 36
+    constexpr int Q = 16 / (int)sizeof(T);
+    struct alignas(16) Quad { T v[Q]; };
+    const Quad* q = (const Quad*)(mat + ph * (2 * MAT_TRI) + (delta ? MAT_TRI : 0));
+    T m[(21 + Q - 1) / Q * Q];
+#pragma unroll
+    for (int i = 0; i < (21 + Q - 1) / Q; ++i) {
+      const Quad w = q[i];
+#pragma unroll
+      for (int j = 0; j < Q; ++j) m[i * Q + j] = w.v[j];
+    }
+    // engineering shear strains; factors of two are exact
+    const T g[6] = {e[0], e[1], e[2], T(2) * e[3], T(2) * e[4], T(2) * e[5]};
 #pragma unroll
     for (int a = 0; a < 6; ++a) {
       T s = 0;
 #pragma unroll
-      for (int b = 0; b < 6; ++b) s += m[a * 6 + b] * e[b];
+      for (int b = 0; b < 6; ++b) {
+        const int lo = a < b ? a : b, hi = a < b ? b : a;
+        s += m[lo * (11 - lo) / 2 + hi] * g[b];
+      }
       out[a] = s;
     }
   }

@@ -46,9 +46,12 @@ enum : int32_t { FLAG_RUNNING = 0, FLAG_CONVERGED = 1, FLAG_DIVERGED = 2, FLAG_Z
 // Everything a kernel needs about one batch entry (one load case of one
 // RVE).  Kernels index an array of these with blockIdx.y (blockIdx.x for the
 // one-block-per-entry kernels).
+// general phases: the 21 upper entries of a symmetric 6 x 6 matrix, row by row, padded
+constexpr int MAT_TRI = 24;
+
 struct Desc {
   const uint16_t* phase;   // [N] phase ids
-  const double* mat64;     // per phase: iso (lam, mu, lam-lam0, mu-mu0) or gen (M[36], M-M0[36])
+  const double* mat64;     // per phase: iso (lam, mu, lam-lam0, mu-mu0) or gen (upper triangles of C and C-C0, MAT_TRI each)
   const float* mat32;
   void* x;                 // iterate (compute precision)
   void* r;                 // residual (compute precision, or FP32 when r_f32)

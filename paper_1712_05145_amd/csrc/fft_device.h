@@ -229,8 +229,11 @@ template <typename T, int N> struct TwTable {
 };
 template <typename T, int N> __device__ const TwTable<T, N> tw_table{};
 
+// entries of the table that the stages read: radices 2, 4, 8 and 16 use powers
+// w^r with r <= R / 2 only
+constexpr int tw_len(int n) { return (n & (n - 1)) == 0 && n > 1 ? n / 2 : n; }
 template <typename T, int N, int NT> __device__ __forceinline__ void build_twiddles(C2<T>* tw) {
-  for (int m = threadIdx.x; m < N; m += NT) tw[m] = tw_table<T, N>.v[m];
+  for (int m = threadIdx.x; m < tw_len(N); m += NT) tw[m] = tw_table<T, N>.v[m];
 }
 
 // ---------------------------------------------------------------------------

@@ -246,16 +246,15 @@ __device__ __forceinline__ void load_rows_c2r(const S* spec, C2<T>* z, long row0
   C2<T> a[NL], b[NL];
 #pragma unroll
   for (int i = 0; i < NL; ++i) {
-    const int v = threadIdx.x + i * NTB;
+    const int u = threadIdx.x + i * NTB;
+    const int v = NA % NTB == 0 || u < NA ? u : 0;
     const int rr = v / (H * 3), rem = v % (H * 3);
     const int k = rem / 3, q = rem % 3;
-    const long row = row0 + rr;
-    a[i] = b[i] = C2<T>{0, 0};
-    if ((NA % NTB == 0 || v < NA) && row < rows_total) {
-      const S* s = spec + spec_at(row, k, 2 * q, rows_total, kchunk(H));
-      a[i] = sload<T>(s);
-      b[i] = sload<T>(s + 1);
-    }
+    // rows past the end are never used: they repeat the first
+    const long row = row0 + rr < rows_total ? row0 + rr : row0;
+    const S* s = spec + spec_at(row, k, 2 * q, rows_total, kchunk(H));
+    a[i] = sload<T>(s);
+    b[i] = sload<T>(s + 1);
   }
 #pragma unroll
   for (int i = 0; i < NL; ++i) {
@@ -1027,21 +1026,28 @@ __global__ __launch_bounds__(NT) void k_bicg_finish(const Desc* __restrict__ des
 // Binary16 tile transfers, G columns per access (ncols and c0 multiples of G,
 // so a group is either all inside or all outside the plane).
 // Tile loads of the y-pass: all of a thread's global loads are issued before
-// its first LDS write, so their latencies overlap.
+// its first LDS write, so their latencies overlap.  In FP32 places outside the
+// plane load its first column instead of being skipped (their columns are not
+// stored): around a skipped load the compiler waits for each binary16 value in
+// turn (256^3, both directions, per load: 210 -> 193 us).  FP64 skips them, its
+// loads then leave one by one: 512^3 2.53 ms a pass, else 3.59 ms.
 template <typename T, int N1, int CW, int NTB, int G, typename S>
 __device__ __forceinline__ void y_tile_load(const S* base, int ncols, int c0, C2<T>* buf) {
   constexpr int NA = N1 * CW / G, NL = (NA + NTB - 1) / NTB;
   C2<T> a[NL][G];
 #pragma unroll
   for (int k = 0; k < NL; ++k) {
-    const int v = threadIdx.x + k * NTB;
+    const int u = threadIdx.x + k * NTB;
+    const int v = NA % NTB == 0 || u < NA ? u : 0;
     const int i1 = v / (CW / G), col = (v % (CW / G)) * G;
-    if ((NA % NTB == 0 || v < NA) && c0 + col < ncols) {
-      if constexpr (std::is_same<S, H2>::value) hload_g<T, G>(base + (long)i1 * ncols + col, a[k]);
-      else load_v<T, G>(base + (long)i1 * ncols + col, a[k]);
+    const S* s = base + (long)i1 * ncols;
+    if constexpr (sizeof(T) == 8) {
+      a[k][0] = C2<T>{0, 0};
+      if ((NA % NTB == 0 || u < NA) && c0 + col < ncols) a[k][0] = s[col];
+    } else if constexpr (std::is_same<S, H2>::value) {
+      hload_g<T, G>(s + (c0 + col < ncols ? col : 0), a[k]);
     } else {
-#pragma unroll
-      for (int q = 0; q < G; ++q) a[k][q] = C2<T>{0, 0};
+      load_v<T, G>(s + (c0 + col < ncols ? col : 0), a[k]);
     }
   }
 #pragma unroll
@@ -1245,20 +1251,28 @@ __device__ __forceinline__ void zpass_tile(const Desc& d, int bid, int op, int n
   const T sc = FULL ? (T)scale : (T)(d.op_scale * d.st->dscale * (plane ? 1.0 / N0 : 1.0));
   const T gh = (T)d.gam_h, gc = (T)d.gam_c;
   // all of a thread's loads are issued before the first LDS write, so their
-  // latencies overlap (the tile's rows are far apart in memory)
+  // latencies overlap (the tile's rows are far apart in memory).  Columns
+  // outside the chunk load its first one in FP32: skipped instead, they made
+  // the compiler wait for each binary16 value in turn (256^3, three loads: 569
+  // -> 442 us).  FP64 skips them: its loads then leave one by one, and the
+  // narrow rows of long axes (96 bytes) come faster (512^3 operator 14.1 ms,
+  // else 15.7)
   constexpr int NA = N0 * W / GZ, NL = (NA + NTB - 1) / NTB;
   {
     C2<T> a[NL][GZ];
 #pragma unroll
     for (int k = 0; k < NL; ++k) {
-      const int v = threadIdx.x + k * NTB;
+      const int u = threadIdx.x + k * NTB;
+      const int v = NA % NTB == 0 || u < NA ? u : 0;
       const int i0 = v / (W / GZ), w = (v % (W / GZ)) * GZ;
-      if ((NA % NTB == 0 || v < NA) && w < wlim) {
-        if constexpr (FULL) load_v<T, GZ>(src + (long)i0 * rs + w, a[k]);
-        else hload_g<T, GZ>(src + (long)i0 * rs + w, a[k]);
+      const S* s = src + (long)i0 * rs;
+      if constexpr (sizeof(T) == 8) {
+        a[k][0] = C2<T>{0, 0};
+        if ((NA % NTB == 0 || u < NA) && w < wlim) a[k][0] = s[w];
+      } else if constexpr (FULL) {
+        load_v<T, GZ>(s + (w < wlim ? w : 0), a[k]);
       } else {
-#pragma unroll
-        for (int q = 0; q < GZ; ++q) a[k][q] = C2<T>{0, 0};
+        hload_g<T, GZ>(s + (w < wlim ? w : 0), a[k]);
       }
     }
 #pragma unroll
@@ -1411,15 +1425,10 @@ __device__ __forceinline__ void gz_tile(const Desc& d, int bid, int op, int n1, 
     C2<T> a[NL][GZ];
 #pragma unroll
     for (int k = 0; k < NL; ++k) {
-      const int v = threadIdx.x + k * NTB;
-      if (NA % NTB == 0 || v < NA) {
-        const S* s = src + at(v);
-        if constexpr (FULL) load_v<T, GZ>(s, a[k]);
-        else hload_g<T, GZ>(s, a[k]);
-      } else {
-#pragma unroll
-        for (int g = 0; g < GZ; ++g) a[k][g] = C2<T>{0, 0};
-      }
+      const int u = threadIdx.x + k * NTB;
+      const S* s = src + at(NA % NTB == 0 || u < NA ? u : 0);
+      if constexpr (FULL) load_v<T, GZ>(s, a[k]);
+      else hload_g<T, GZ>(s, a[k]);
     }
 #pragma unroll
     for (int k = 0; k < NL; ++k) {

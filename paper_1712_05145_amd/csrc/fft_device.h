@@ -119,6 +119,22 @@ template <int DIR, typename T> __device__ __forceinline__ C2<T> w16(int m) {
   return C2<T>{c[m & 15], DIR > 0 ? s : -s};
 }
 
+// exp(DIR * 2 pi i * m / 32) for m in [0, 32)
+#define FFTH_C32_1 0.98078528040323044913
+#define FFTH_S32_1 0.19509032201612826785
+#define FFTH_C32_3 0.83146961230254523708
+#define FFTH_S32_3 0.55557023301960222474
+template <int DIR, typename T> __device__ __forceinline__ C2<T> w32(int m) {
+  if (m % 2 == 0) return w16<DIR, T>(m / 2);
+  const T q[8] = {T(FFTH_C32_1), T(FFTH_C32_3), T(FFTH_S32_3), T(FFTH_S32_1), T(-FFTH_S32_1), T(-FFTH_S32_3),
+                  T(-FFTH_C32_3), T(-FFTH_C32_1)};   // cos(2 pi (2 j + 1) / 32)
+  const int j = m / 2;                               // m in [0, 32): cos changes sign at 16
+  const T c = j < 8 ? q[j] : -q[j - 8];
+  const int jj = (j + 12) & 15;                      // sin(a) = cos(a - pi/2): 8 steps of pi/16 back
+  const T sn = jj < 8 ? q[jj] : -q[jj - 8];
+  return C2<T>{c, DIR > 0 ? sn : -sn};
+}
+
 // exp(DIR * 2 pi i * m / 12) for m in [0, 12)
 template <int DIR, typename T> __device__ __forceinline__ C2<T> w12(int m) {
   const T c[12] = {T(1), T(FFTH_S3), T(0.5), T(0), T(-0.5), T(-FFTH_S3), T(-1), T(-FFTH_S3), T(-0.5), T(0), T(0.5),
@@ -177,6 +193,27 @@ template <int R, int DIR, typename T> __device__ __forceinline__ void dft(C2<T>*
       a[k2] = b0;
       a[k2 + 4] = b1;
       a[k2 + 8] = b2;
+    }
+  } else if constexpr (R == 32) {
+    // 32 = 4 x 8: Y_s = DFT8(a[4m+s]); X[k2 + 8 k1] = sum_s w4^{k1 s} w32^{k2 s} Y_s[k2]
+    C2<T> y[4][8];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+#pragma unroll
+      for (int m = 0; m < 8; ++m) y[s][m] = a[4 * m + s];
+      dft<8, DIR>(y[s]);
+#pragma unroll
+      for (int k = 1; k < 8; ++k)
+        if (s) y[s][k] = s * k == 8 ? mul_i<DIR>(y[s][k]) : cmul(y[s][k], w32<DIR, T>(s * k));
+    }
+#pragma unroll
+    for (int k2 = 0; k2 < 8; ++k2) {
+      C2<T> b0 = y[0][k2], b1 = y[1][k2], b2 = y[2][k2], b3 = y[3][k2];
+      dft4<DIR>(b0, b1, b2, b3);
+      a[k2] = b0;
+      a[k2 + 8] = b1;
+      a[k2 + 16] = b2;
+      a[k2 + 24] = b3;
     }
   } else if constexpr (R == 16) {
     // 16 = 4 x 4: Y_s = DFT4(a[4m+s]); twiddle w16^{k2 s}; X[k2 + 4 k1] = DFT4_s

@@ -296,13 +296,13 @@ template <int R1> __device__ __forceinline__ long tile_row(long base, int rr, lo
 }
 
 // tw1[g R1 + q] = exp(-2 pi i b q / n1) of the block's groups
-// (every n1 with a grouped plan divides 384)
+// (every n1 with a grouped plan divides 768)
 template <typename T, int R1, int G, int NTB>
 __device__ __forceinline__ void build_group_twiddles(C2<T>* tw1, long g0, int r2) {
-  const int step = 384 / (R1 * r2);
+  const int step = 768 / (R1 * r2);
   for (int m = threadIdx.x; m < G * R1; m += NTB) {
     const int b = (int)(g0 + m / R1) % r2, q = m % R1;
-    tw1[m] = tw_table<T, 384>.v[b * q * step];
+    tw1[m] = tw_table<T, 768>.v[b * q * step];
   }
 }
 
@@ -1498,13 +1498,30 @@ __global__ __launch_bounds__(NTB) void k_gz(const Desc* __restrict__ descs, int 
 
 // Which grids take the grouped passes: axis lengths whose kernels are compiled
 // and whose tiles leave room for three blocks per CU (FP64: two).  R2 (0: not
-// grouped) balances the two passes; measured with six loads, us per three-term
-// iteration: FP64 64^3 R2 = 8 138, 4 144; 48^3 4 73, 8 78; 96^3 8 520 (five
-// passes 595).  Longer axes 1 leave no R2 whose tiles fit both passes.
+// grouped) balances the two passes; measured, us per three-term iteration:
+// FP64 six loads 64^3 R2 = 8 138, 4 144; 48^3 4 73, 8 78; 96^3 8 520 (five
+// passes 595).  Axes of 256 (FP32 six loads, FP64 three; grouped against five
+// passes): FP32 64x256x128 623, 730; 128x256x64 683, 746; 256x64x64 306, 356;
+// 256x128x64 690, 772; 256x16x96 138, 192; FP64 48x256x64 250, 284; 256x16x64
+// 93, 170; 64x128x64 161, 205.  At 256^3 no R2 has tiles that fit both passes.
 template <typename T> constexpr int group_lds() { return sizeof(T) == 8 ? 80 * 1024 : 56 * 1024; }
+// the preferred R2 of axis 1, and a second choice where its tile does not fit
 template <typename T> __host__ __device__ constexpr int group_r2(int n1) {
-  if (sizeof(T) == 8) return n1 == 64 || n1 == 96 ? 8 : n1 >= 8 && n1 <= 48 ? 4 : 0;
-  return n1 == 8 ? 4 : n1 == 16 || n1 == 32 || n1 == 64 || n1 == 128 ? 8 : n1 == 12 || n1 == 24 || n1 == 48 || n1 == 96 ? 6 : 0;
+  if (sizeof(T) == 8) return n1 == 64 || n1 == 96 || n1 == 128 ? 8 : n1 >= 8 && n1 <= 48 ? 4 : n1 == 256 ? 16 : 0;
+  return n1 == 8 ? 4 : n1 == 16 || n1 == 32 || n1 == 64 || n1 == 128 ? 8
+         : n1 == 12 || n1 == 24 || n1 == 48 || n1 == 96 ? 6 : n1 == 256 ? 16 : 0;
+}
+template <typename T> constexpr int group_r2b(int n1) {
+  if (sizeof(T) == 8) return n1 == 64 ? 4 : n1 >= 8 && n1 <= 32 ? 2 : 0;
+  return n1 == 256 ? 8 : n1 == 16 || n1 == 32 || n1 == 64 || n1 == 128 ? 4 : 0;
+}
+// With R1 >= 16 rows per group a block has few items in its spectrum transfers
+// on short axes 2, and the fused pass loses more than the y-passes cost (five
+// passes the second figure, FP32 six loads: 64x256x16 121, 111; 128x256x32 384,
+// 354; 256x64x32 179, 193) unless the grid is small enough to be bound by its
+// launches (64x128x16 70, 79; 16x256x8 33, 43)
+constexpr bool group_pays(int r1, int n2, long nvox) {
+  return r1 < 16 || n2 >= 2 * r1 || (r1 == 16 && nvox <= 1 << 17);
 }
 // log2 of the k2 values per chunk: the x-passes move segments of 6 << kcs
 // values, the z-pass rows of 6 R2 values broken into segments of 6 kc.  Wider

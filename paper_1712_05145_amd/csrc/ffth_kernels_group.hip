@@ -8,9 +8,8 @@
 #error "compile with -DFFTH_REAL=float|double and -DFFTH_PART=0..4"
 #endif
 
-// axis lengths of the grouped passes: axes 0 and 1, axis 2
-#define FFTH_GROUP_N01(X) X(8) X(12) X(16) X(24) X(32) X(48) X(64) X(96) X(128)
-#define FFTH_GROUP_N2(X) FFTH_GROUP_N01(X) X(256)
+// axis lengths of the grouped passes
+#define FFTH_GROUP_N(X) X(8) X(12) X(16) X(24) X(32) X(48) X(64) X(96) X(128) X(256)
 
 namespace ffth {
 
@@ -38,57 +37,61 @@ template <> hipError_t GLaunch<R>::gz(int n0, const GroupShape& g, bool h16, int
   case N:                                                                                             \
     if (g.r2 == 4) gz_r<N, 4>(grid, h16, s, d, op, n1, scale, g.kcs, fin, nblk_f, nblk_i);           \
     if (g.r2 == 8) gz_r<N, 8>(grid, h16, s, d, op, n1, scale, g.kcs, fin, nblk_f, nblk_i);           \
-    if constexpr (!DBL) {                                                                             \
+    if (g.r2 == 16) gz_r<N, 16>(grid, h16, s, d, op, n1, scale, g.kcs, fin, nblk_f, nblk_i);         \
+    if constexpr (DBL) {                                                                              \
+      if (g.r2 == 2) gz_r<N, 2>(grid, h16, s, d, op, n1, scale, g.kcs, fin, nblk_f, nblk_i);         \
+    } else {                                                                                          \
       if (g.r2 == 6) gz_r<N, 6>(grid, h16, s, d, op, n1, scale, g.kcs, fin, nblk_f, nblk_i);         \
     }                                                                                                 \
     return hipGetLastError();
-    FFTH_GROUP_N01(FFTH_CASE)
+    FFTH_GROUP_N(FFTH_CASE)
 #undef FFTH_CASE
   }
   return hipErrorInvalidValue;
 }
 
-static bool n01_compiled(int n) {
-#define FFTH_CASE(N) if (n == N) return true;
-  FFTH_GROUP_N01(FFTH_CASE)
-#undef FFTH_CASE
-  return false;
-}
-static bool n2_compiled(int n) {
-#define FFTH_CASE(N) if (n == N) return true;
-  FFTH_GROUP_N2(FFTH_CASE)
-#undef FFTH_CASE
-  return false;
-}
 #ifdef FFTH_GROUP_RULE   // defined for one of the two precisions
+static bool compiled(int n) {
+#define FFTH_CASE(N) if (n == N) return true;
+  FFTH_GROUP_N(FFTH_CASE)
+#undef FFTH_CASE
+  return false;
+}
 template <typename T> static GroupShape shape_of(const int n[3]) {
   GroupShape g;
-  const int r2 = group_r2<T>(n[1]);
-  if (!n01_compiled(n[0]) || !n01_compiled(n[1]) || !n2_compiled(n[2]) || r2 == 0) return g;
-  const int r1 = n[1] / r2;
-  if (!gx_fits<T>(n[2], r1) || !gz_fits<T>(n[0], r2)) return g;
-  const int kc = gz_kc<T>(n[0], r2), grp = group_count(n[2], r1);
-  g.on = true;
-  g.r1 = r1;
-  g.r2 = r2;
-  g.kcs = group_kcs(r2, n[2] / 2);
-  g.xblocks = (n[0] * r2 + grp - 1) / grp;
-  g.zblocks = n[2] / 2 / kc * r1;
+  if (!compiled(n[0]) || !compiled(n[1]) || !compiled(n[2])) return g;
+  for (int r2 : {group_r2<T>(n[1]), group_r2b<T>(n[1])}) {
+    const int r1 = r2 > 0 ? n[1] / r2 : 0;
+    if (r2 == 0 || !gx_fits<T>(n[2], r1) || !gz_fits<T>(n[0], r2)) continue;
+    // (grids of the multi-size launches are grouped in FP32, whatever their axis 2)
+    const bool multi = sizeof(T) == 4 && multi_size(n[0]) && multi_size(n[1]) && multi_size(n[2]);
+    if (!multi && !group_pays(r1, n[2], (long)n[0] * n[1] * n[2])) continue;
+    const int grp = group_count(n[2], r1);
+    g.on = true;
+    g.r1 = r1;
+    g.r2 = r2;
+    g.kcs = group_kcs(r2, n[2] / 2);
+    g.xblocks = (n[0] * r2 + grp - 1) / grp;
+    g.zblocks = n[2] / 2 / gz_kc<T>(n[0], r2) * r1;
+    return g;
+  }
   return g;
 }
 GroupShape group_shape(const int n[3], bool dbl) { return dbl ? shape_of<double>(n) : shape_of<float>(n); }
 #endif
 #else
 // kernel launch for (axis-2 length, R1): f(integral constants).  R1 = 3, 6, 12
-// come up in FP64 (12, 24, 48 = 4 R1, 96 = 8 R1)
+// come up in FP64 (12, 24, 48 = 4 R1, 96 = 8 R1), R1 = 32 in FP32
 template <int N> struct IC { static constexpr int v = N; };
 template <int N, class F> static bool for_r1(int r1, F&& f) {
   switch (r1) {
 #define FFTH_R1(K) case K: if constexpr (gx_fits<R>(N, K)) { f(IC<N>(), IC<K>()); return true; } break;
+#define FFTH_R1F(K) case K: if constexpr (!DBL && gx_fits<R>(N, K)) { f(IC<N>(), IC<K>()); return true; } break;
 #define FFTH_R1D(K) case K: if constexpr (DBL && gx_fits<R>(N, K)) { f(IC<N>(), IC<K>()); return true; } break;
     FFTH_R1(2) FFTH_R1(4) FFTH_R1(8) FFTH_R1(16)
-    FFTH_R1D(3) FFTH_R1D(6) FFTH_R1D(12)
+    FFTH_R1D(3) FFTH_R1D(6) FFTH_R1D(12) FFTH_R1F(32)
 #undef FFTH_R1
+#undef FFTH_R1F
 #undef FFTH_R1D
   }
   return false;
@@ -97,7 +100,7 @@ template <class F> static hipError_t for_shape(int n2, int r1, F&& f) {
   bool ok = false;
   switch (n2) {
 #define FFTH_CASE(N) case N: ok = for_r1<N>(r1, f); break;
-    FFTH_GROUP_N2(FFTH_CASE)
+    FFTH_GROUP_N(FFTH_CASE)
 #undef FFTH_CASE
   }
   return ok ? hipGetLastError() : hipErrorInvalidValue;

@@ -26,7 +26,10 @@ pytestmark = pytest.mark.gpu
 # blocks with a ragged last group, and lengths just outside the rule
 SHAPES = [(8, 8, 8), (12, 12, 24), (8, 16, 12), (24, 24, 8), (8, 32, 16), (12, 48, 8), (16, 64, 8), (8, 96, 12),
           (8, 128, 8), (128, 8, 8), (96, 12, 16), (128, 24, 12), (8, 16, 256), (8, 64, 256), (12, 12, 128),
-          (64, 32, 96), (1, 12, 16), (1, 48, 96), (1, 256, 8)]
+          (64, 32, 96), (1, 12, 16), (1, 48, 96), (1, 256, 8),
+          # axes of 256, both choices of the split, and lengths the rule leaves out
+          (8, 256, 8), (64, 256, 32), (96, 256, 64), (64, 256, 16), (256, 8, 12), (256, 32, 8), (256, 64, 32),
+          (256, 128, 64), (256, 24, 16), (48, 256, 96), (128, 64, 96), (64, 128, 64)]
 
 
 @pytest.mark.parametrize("shape", SHAPES)
@@ -45,7 +48,8 @@ def test_green_operator_every_split(shape):
         assert rel_l2(got, ref) < tol, (precision, rel_l2(got, ref))
 
 
-@pytest.mark.parametrize("shape", [(8, 12, 16), (24, 16, 8), (16, 48, 32), (12, 128, 16), (1, 24, 32)])
+@pytest.mark.parametrize("shape", [(8, 12, 16), (24, 16, 8), (16, 48, 32), (12, 128, 16), (1, 24, 32), (8, 256, 16),
+                                   (256, 16, 8)])
 @pytest.mark.parametrize("scheme,precision,h16", [("cg", "mixed", False), ("cg", "mixed", "force"),
                                                   ("basic", "mixed", False), ("cg", "fp64", False),
                                                   ("cg3", "fp64", False), ("bicgstab", "fp64", False)])

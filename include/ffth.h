@@ -110,7 +110,8 @@ typedef struct {
                                  fields, one FP32 operator application)                */
   int32_t check_every;        /* iterations between host reads of the convergence flags */
   int32_t autotune;           /* 1: time the compiled tile shapes of every pass at plan
-                                 creation (grids >= 64^3) and keep the fastest          */
+                                 creation (grids >= 64^3) and keep the fastest (grouped
+                                 passes, below, have one shape each)                    */
   int32_t spectrum16;         /* MIXED CG: 1 keeps the FP32 inner solve's spectrum in
                                  binary16 from the forward transforms up to the Green
                                  operator (FP32 arithmetic, scaled into range; FP32
@@ -257,17 +258,21 @@ ffth_status ffth_profile_read(ffth_plan *plan, int32_t category, int64_t *launch
                               double *ms);
 const char *ffth_profile_name(int32_t category);
 /* Tile variant chosen per pass: out[2*pass + prec], pass 0..3 = x-forward, y,
- * z, x-inverse; prec 0 = FP32, 1 = FP64 (variant 0 = the default shape). */
+ * z, x-inverse; prec 0 = FP32, 1 = FP64 (variant 0 = the default shape).
+ * Most grids with axes up to 256 run grouped passes in one or both precisions
+ * (axis 1 split between the x-passes and the z-pass, no y-passes: three passes
+ * per operator application instead of five); those have one shape and read 0. */
 ffth_status ffth_tile_variants(ffth_plan *plan, int32_t out[8]);
 /* Pin the tile variants (same layout; each in [0, 6): 0..3 tile shapes with
  * the default radix order, 4 and 5 the default tile with the radix orders
  * 4-2-3-5-8-16 and 8-4-2-3-5-16); results of every variant agree to
- * rounding.  INVALID for a value out of range. */
+ * rounding.  A plan with pinned variants runs the five classical passes.
+ * INVALID for a value out of range. */
 ffth_status ffth_set_tile_variants(ffth_plan *plan, const int32_t in[8]);
 /* Loads per launch of the iteration passes, out[prec] (0 = FP32, 1 = FP64):
  * 0 = every load of the iteration in one launch per pass; k > 0 = the loads
  * are taken k at a time, each group through all of the iteration's passes
- * (y, z, y and the x-passes) before the next (load-major order), and the
+ * before the next (load-major order), and the
  * scalars of all of them finalized together.  Chosen by the autotuner like
  * the tile variants (0 unless a smaller width is measured faster). */
 ffth_status ffth_launch_loads(ffth_plan *plan, int32_t out[2]);
@@ -322,7 +327,7 @@ ffth_status ffth_cancel(ffth_server *srv, uint64_t request_id);
  * iterations of the running requests whose grids have all three axis lengths
  * in {16, 24, 32, 48, 64, 96, 128} run as one launch per pass across the grid
  * sizes that share a stream (more grids than streams; per material kind and
- * spectrum precision), each load with the default tile shape of its lengths
+ * spectrum precision), each load with the grouped passes' tiles of its lengths
  * (a grid alone on its stream keeps the per-size kernels, with the same
  * tiles); such requests' plans are not autotuned, so their results equal the
  * plan path's with autotuning off, bit for bit.

@@ -1,6 +1,6 @@
 // HIP kernels of one iteration of the Moulinec-Suquet Basic Scheme / its CG
-// form (Algorithm 1 and eq. (6) of arXiv:1712.05145), organised as five
-// HBM-streaming passes over a half spectrum (k2 < n2/2, six interleaved
+// form (Algorithm 1 and eq. (6) of arXiv:1712.05145), organised as five (the
+// classical) or three (the grouped, below) passes over a half spectrum (k2 < n2/2, six interleaved
 // components) stored k2-chunked as [k2 / KC][n0][n1][k2 % KC][6] complex,
 // KC = kchunk(n2/2) (at most 16): every z-column then strides KC*6*n1
 // complex values between rows instead of a whole plane:
@@ -15,6 +15,12 @@
 //   y-pass (inverse)
 //   x-pass (inverse)   complex-to-real FFT fused with the Basic Scheme / CG
 //                      update and the residual reductions
+//
+// 2-D grids (n0 = 1) have no y-passes: the z-pass transforms axis 1.  Grouped
+// passes split axis 1 between the x-passes and the z-pass (k_gz) and need no
+// y-passes either.  The three-term CG joins the inverse x-pass of an iteration
+// and the forward one of the next (k_xcg3); the field passes (k_field_*) serve
+// operator calls without a solve.
 //
 // All FFTs run in LDS (mixed-radix Stockham, fft_device.h).  Block tile
 // sizes are compile-time functions of the axis length and precision.
@@ -122,8 +128,8 @@ template <typename T> constexpr int vec_width() { return 1; }
 
 // ---------------------------------------------------------------------------
 // Constitutive law helpers.  Tensor-component vectors (11,22,33,23,13,12).
-// Isotropic table row: (lam, mu, lam - lam0, mu - mu0).  Generic table row:
-// M (36, maps tensor components to stress) followed by M - M0 (36).
+// Isotropic table row: (lam, mu, lam - lam0, mu - mu0).  Generic table row: the
+// upper triangles of C and of C - C0, MAT_TRI values each.
 // ---------------------------------------------------------------------------
 template <typename T> __device__ __forceinline__ const T* mat_of(const Desc& d);
 template <> __device__ __forceinline__ const float* mat_of<float>(const Desc& d) { return d.mat32; }
@@ -142,6 +148,7 @@ __device__ __forceinline__ void apply_mat(const T* mat, int ph, bool delta, cons
     // upper triangle, padded to MAT_TRI values so that 16-byte loads fetch it:
     // the loads are gathers (neighbouring voxels differ in phase) and their
     // number bounds the pass, 11 (FP64) or 6 (FP32) here instead of 36
+    // (48x24x96 BiCGSTAB solve, two loads: 7.76 -> 7.59 ms)
     constexpr int Q = 16 / (int)sizeof(T);
     struct alignas(16) Quad { T v[Q]; };
     const Quad* q = (const Quad*)(mat + ph * (2 * MAT_TRI) + (delta ? MAT_TRI : 0));
@@ -747,8 +754,9 @@ __global__ __launch_bounds__(NTB) void k_xinv(const Desc* __restrict__ descs, in
 // the phase ids and of the state before the first value.  Small calls are
 // bound by the chain of launches, large ones by the memory rate.  With the
 // descriptor in the launch arguments (no setup launch) an operator call takes,
-// before -> now: 16^3 19.6 -> 15.4 us, 48x96x24 47.6 -> 40.5 us, 512^3 15.36
-// -> 15.01 ms; the order-1 right-hand side of 64^3 725 -> 683 us.
+// before -> now: 16^3 19.6 -> 15.6 us, 48x96x24 47.6 -> 41.0 us, 512^3 15.36
+// -> 14.05 ms (forward pass 2.4 ms, 5.4 TB/s, inverse 2.6 ms, 5.0 TB/s); two
+// order-2 right-hand sides of 64^3 725 -> 683 us.
 // ---------------------------------------------------------------------------
 template <typename T, int N2, int ROWS, int R1>
 __device__ __forceinline__ void field_fwd_tile(const Desc& d, int bid, long rows_total, long nvox, int r2, int kcs,
@@ -1376,6 +1384,9 @@ __global__ __launch_bounds__(NTB) void k_zpass(const Desc* __restrict__ descs, i
 // q, every b and i0; a row of the tile, [b][k2][6], is contiguous.  Rows are
 // an odd number of elements apart (WP): the passes along a column and the
 // operator's threads then spread over the banks.
+// Bound by vector instructions and LDS traffic more than by memory (128^3, FP32,
+// launches of 2.9 loads on average: 74 us, two y-passes and a z-pass before 139;
+// the fused pass rose from 164 to 189).
 // ---------------------------------------------------------------------------
 template <typename T> __host__ __device__ constexpr int gz_kc(int n0, int r2) { return n0 * r2 * 6 * 2 * (int)sizeof(T) <= 16384 ? 2 : 1; }
 

@@ -760,9 +760,9 @@ __global__ __launch_bounds__(NTB) void k_xinv(const Desc* __restrict__ descs, in
 // the phase ids and of the state before the first value.  Small calls are
 // bound by the chain of launches, large ones by the memory rate.  With the
 // descriptor in the launch arguments (no setup launch) an operator call takes,
-// before -> now: 16^3 19.6 -> 15.6 us, 48x96x24 47.6 -> 41.0 us, 512^3 15.36
-// -> 14.05 ms (forward pass 2.4 ms, 5.4 TB/s, inverse 2.6 ms, 5.0 TB/s); two
-// order-2 right-hand sides of 64^3 725 -> 683 us.
+// before -> now: 16^3 19.6 -> 15.6 us, 48x96x24 47.6 -> 41.0 us; the forward
+// pass of 512^3 3.1 -> 2.4 ms (5.4 TB/s), the inverse 3.6 -> 2.6 (5.0 TB/s);
+// two order-2 right-hand sides of 64^3 725 -> 683 us.
 // ---------------------------------------------------------------------------
 template <typename T, int N2, int ROWS, int R1>
 __device__ __forceinline__ void field_fwd_tile(const Desc& d, int bid, long rows_total, long nvox, int r2, int kcs,
@@ -1269,8 +1269,8 @@ __device__ __forceinline__ void zpass_tile(const Desc& d, int bid, int op, int n
   // outside the chunk load its first one in FP32: skipped instead, they made
   // the compiler wait for each binary16 value in turn (256^3, three loads: 569
   // -> 442 us).  FP64 skips them: its loads then leave one by one, and the
-  // narrow rows of long axes (96 bytes) come faster (512^3 operator 14.1 ms,
-  // else 15.7)
+  // narrow rows of long axes (96 bytes) come faster (512^3 with 256 threads 3.9
+  // ms, all at once about 6)
   constexpr int NA = N0 * W / GZ, NL = (NA + NTB - 1) / NTB;
   {
     C2<T> a[NL][GZ];

@@ -70,6 +70,15 @@ template <int NTF> __device__ __forceinline__ double strided_sum(const double* _
   return ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
 }
 
+// The gating flag of a load.  A pass that carries a finalize reads it in every
+// block while the finalize's block may clear it, so both sides are atomic.
+__device__ __forceinline__ bool flag_read(const SolverState* st) {
+  return __hip_atomic_load(&st->active, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+}
+__device__ __forceinline__ void flag_clear(SolverState* st) {
+  __hip_atomic_store(&st->active, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Scalars of one iteration (the ops a pass may carry).
 __device__ static void fin_iter(int op, SolverState* st, const double* sf, const double* si) {
   switch (op) {
@@ -77,7 +86,7 @@ __device__ static void fin_iter(int op, SolverState* st, const double* sf, const
       const double pq = sf[0];
       if (!(pq > 0.0) || !(st->rr == st->rr)) {
         st->flag = FLAG_DIVERGED;
-        st->active = 0;
+        flag_clear(st);
       } else {
         st->alpha = st->rr / pq;
       }
@@ -87,7 +96,7 @@ __device__ static void fin_iter(int op, SolverState* st, const double* sf, const
       // three-term CG: rho_0 = <r,r>_C0, mu_0 = <r,Ar>_C0, gamma_0 = rho_0 / mu_0, omega_0 = 1
       if (!(sf[1] > 0.0) || !(sf[0] > 0.0)) {
         st->flag = sf[0] > 0.0 ? FLAG_DIVERGED : FLAG_CONVERGED;
-        st->active = 0;
+        flag_clear(st);
         break;
       }
       st->rr = sf[0];
@@ -116,19 +125,19 @@ __device__ static void fin_iter(int op, SolverState* st, const double* sf, const
       // which k_cg3_finish forms x_{k+1} when k was even
       if (st->res < st->tol) {
         st->flag = FLAG_CONVERGED;
-        st->active = 0;
+        flag_clear(st);
       } else if (!(si[1] > 0.0) || !(om == om) || !(fabs(om) < 1e6) || !(st->res == st->res) || st->res > 1e6) {
         st->flag = FLAG_DIVERGED;
-        st->active = 0;
+        flag_clear(st);
       } else if (st->total >= st->max_iter) {
         // iteration budget (over all solves sharing the state: the mixed
         // scheme's inner solves count together) spent; flag stays RUNNING
-        st->active = 0;
+        flag_clear(st);
       } else if (st->iters - st->best_it >= CG3_STALL && !(st->res < st->best_res)) {
         // no new smallest residual for CG3_STALL iterations: the rounding
         // floor of this precision; flag stays RUNNING
         st->stalled = 1;
-        st->active = 0;
+        flag_clear(st);
       } else {
         st->rr = si[0];
         st->alpha_prev = st->alpha;
@@ -141,7 +150,7 @@ __device__ static void fin_iter(int op, SolverState* st, const double* sf, const
         st->best_it = st->iters;
       }
       // x is formed on odd iterations: after an even last one (iters odd) it is owed
-      if (!st->active) st->xpend = st->iters & 1;
+      if (!flag_read(st)) st->xpend = st->iters & 1;
       break;
     }
   }
@@ -312,31 +321,35 @@ __device__ static void fin_rest(int op, const Desc& d, SolverState* st, const do
 }
 
 // Sums of the block partials of one batch entry and its scalar update, by a
-// block of NTF threads.  Only the slots the op reads are summed, four at a
-// time (red: NTF / 64 x 4 doubles of LDS).  ITER: only the ops of fin_iter.
-template <int NTF, bool ITER>
+// block of NTB threads, the first NTF of which sum (the others only meet its
+// barriers).  Only the slots the op reads are summed, four at a time (red:
+// NTF / 64 x 4 doubles of LDS).  ITER: only the ops of fin_iter.  The block is
+// the only writer of the state while it runs.
+template <int NTF, bool ITER, int NTB = NTF>
 __device__ __forceinline__ void finalize_entry(const Desc& d, int op, int nblk_f, int nblk_i) {
   constexpr int NW = NTF / 64;
   __shared__ double red[NW][4];
   __shared__ double sums[2 * NRED];
   SolverState* st = d.st;
-  if (!st->active) return;
+  if (!flag_read(st)) return;
   if (nblk_i < 0) nblk_i = d.nblk_multi;   // multi-size launch: each entry's own block count
   int nf, ni;
   fin_slots(op, nf, ni);
   const int ns = nf + ni, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   for (int k0 = 0; k0 < ns; k0 += 4) {
-    double a[4];
+    if (NTB == NTF || w < NW) {
+      double a[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int k = k0 + u, n = k < nf ? nblk_f : nblk_i;
-      const double* p = k < nf ? d.part_f + (long)k * nblk_f : d.part_i + (long)(k - nf) * nblk_i;
-      a[u] = k < ns ? strided_sum<NTF>(p, n) : 0.0;
-    }
+      for (int u = 0; u < 4; ++u) {
+        const int k = k0 + u, n = k < nf ? nblk_f : nblk_i;
+        const double* p = k < nf ? d.part_f + (long)k * nblk_f : d.part_i + (long)(k - nf) * nblk_i;
+        a[u] = k < ns ? strided_sum<NTF>(p, n) : 0.0;
+      }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (k0 + u < ns) a[u] = wave_sum(a[u]);
-      if (lane == 0) red[w][u] = a[u];
+      for (int u = 0; u < 4; ++u) {
+        if (k0 + u < ns) a[u] = wave_sum(a[u]);
+        if (lane == 0) red[w][u] = a[u];
+      }
     }
     __syncthreads();
     if (threadIdx.x < 4 && k0 + (int)threadIdx.x < ns) {

@@ -1357,7 +1357,9 @@ __device__ __forceinline__ void zpass_tile(const Desc& d, int bid, int op, int n
 // fin >= 0 (z-passes of 2-D grids, grouped z-passes): the first block of every
 // entry does that finalize instead of a tile.  The operator needs none of the
 // scalars a finalize sets; blocks that still see a load active which it stops
-// write a spectrum that nothing reads.
+// write a spectrum that nothing reads.  The flag can change while the launch
+// runs, so each block reads it once for all of its waves (block_active): waves
+// that read it by themselves could part ways ahead of the tile's barriers.
 template <int NTB>
 __device__ __forceinline__ bool carried_finalize(const Desc& d, int fin, int nblk_f, int nblk_i, int& bid, int& nblk) {
   bid = blockIdx.x;
@@ -1365,8 +1367,16 @@ __device__ __forceinline__ bool carried_finalize(const Desc& d, int fin, int nbl
   if (fin < 0) return false;
   --nblk;
   if (bid-- > 0) return false;
-  if (threadIdx.x < 256) finalize_entry<256, true>(d, fin, nblk_f, nblk_i);   // whole waves leave
+  finalize_entry<256, true, NTB>(d, fin, nblk_f, nblk_i);
   return true;
+}
+
+__device__ __forceinline__ bool block_active(const Desc& d, int fin) {
+  if (fin < 0) return d.st->active != 0;   // nothing writes the state in this launch
+  __shared__ int act;
+  if (threadIdx.x == 0) act = flag_read(d.st);
+  __syncthreads();
+  return act != 0;
 }
 
 template <typename T, int N0, int TK = z_cols<T>(N0), int NTB = NT, typename S = C2<T>, int PLAN = 0>
@@ -1376,9 +1386,8 @@ __global__ __launch_bounds__(NTB) void k_zpass(const Desc* __restrict__ descs, i
   __shared__ __attribute__((aligned(16))) C2<T> buf[N0 * TK * 6];
   __shared__ C2<T> tw[tw_len(N0)];
   const Desc& d = descs[blockIdx.y];
-  if (!d.st->active) return;
   int bid, nblk;
-  if (carried_finalize<NTB>(d, fin, nblk_f, nblk_i, bid, nblk)) return;
+  if (carried_finalize<NTB>(d, fin, nblk_f, nblk_i, bid, nblk) || !block_active(d, fin)) return;
   bid = xcd_tile(bid, nblk);
   zpass_tile<T, N0, TK, NTB, S, PLAN>(d, bid, op, n1, h, bpc, kcd, scale, buf, tw, plane != 0);
 }
@@ -1507,9 +1516,8 @@ __global__ __launch_bounds__(NTB) void k_gz(const Desc* __restrict__ descs, int 
   __shared__ __attribute__((aligned(16))) C2<T> buf[gz_elems<T>(N0, R2)];
   __shared__ C2<T> tw[tw_len(N0)];
   const Desc& d = descs[blockIdx.y];
-  if (!d.st->active) return;
   int bid, nblk;
-  if (carried_finalize<NTB>(d, fin, nblk_f, nblk_i, bid, nblk)) return;
+  if (carried_finalize<NTB>(d, fin, nblk_f, nblk_i, bid, nblk) || !block_active(d, fin)) return;
   gz_tile<T, N0, R2, gz_kc<T>(N0, R2), NTB, S>(d, xcd_tile(bid, nblk), op, n1, scale, kcs, buf, tw);
 }
 
@@ -1620,7 +1628,7 @@ __global__ __launch_bounds__(MULTI_NT) void k_gz_multi(const Desc* __restrict__ 
   const int di = multi_block(sg, bid);
   if (di < 0) return;
   const Desc& d = descs[di];
-  if (!d.st->active) return;
+  if (!block_active(d, fin)) return;
   const int n1 = d.n[1], kcs = group_kcs(group_r2<float>(n1), d.n[2] / 2);
   C2<float>* tw = (C2<float>*)lds;   // N0 values, then the tile
   switch (d.n[0]) {

@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "unit_root.h"
+
 namespace ffth {
 
 template <typename T> struct C2 { T x, y; };
@@ -241,26 +243,17 @@ template <int R, int DIR, typename T> __device__ __forceinline__ void dft(C2<T>*
 
 // ---------------------------------------------------------------------------
 // Twiddle tables w[m] = exp(-2 pi i m / N), m in [0, N): computed at compile
-// time (Taylor series in the first octant, FP64, then rounded to T) and copied
-// to LDS by every block.  Evaluating sincospi in the block cost each wave
+// time (unit_root.h, then rounded to T) and copied to LDS by every block.  Evaluating sincospi in the block cost each wave
 // about 90 of the 790 vector instructions of the 128-point fused pass.
 // ---------------------------------------------------------------------------
 template <typename T, int N> struct TwTable {
   C2<T> v[N];
   constexpr TwTable() : v{} {
     for (int m = 0; m < N; ++m) {
-      // angle = (pi/4) (o + r), r in [0, 1): odd octants are measured from their end
-      const int o = 8 * m / N, rem = 8 * m - o * N;
-      const double x = 0.78539816339744830962 * (double)(o & 1 ? N - rem : rem) / (double)N, x2 = x * x;
-      double c = 1.0, sn = 1.0;
-      for (int k = 20; k >= 2; k -= 2) {
-        c = 1.0 - c * x2 / (double)(k * (k - 1));
-        sn = 1.0 - sn * x2 / (double)(k * (k + 1));
-      }
-      sn *= x;
-      const double cc = (o + 1) & 2 ? sn : c, ss = (o + 1) & 2 ? c : sn;   // octants 1, 2, 5, 6 swap
-      v[m].x = (T)(o >= 2 && o < 6 ? -cc : cc);
-      v[m].y = (T)(o < 4 ? -ss : ss);
+      double c = 0.0, sn = 0.0;
+      unit_root(m, N, c, sn);
+      v[m].x = (T)c;
+      v[m].y = (T)-sn;
     }
   }
 };

@@ -401,7 +401,7 @@ Desc base_desc(ffth_plan* P, int l) {
   d.lam0 = P->lam0;
   d.mu0 = P->mu0;
   d.gam_h = 0.5 / d.mu0;
-  d.gam_c = (d.lam0 + d.mu0) / (d.mu0 * (d.lam0 + 2.0 * d.mu0));
+  d.gam_r = (d.lam0 + d.mu0) / (d.lam0 + 2.0 * d.mu0);
   d.nc = 6;
   d.inv_nvox = 1.0 / (double)P->nvox;
   d.tau_scale = 1.0;

@@ -126,7 +126,7 @@ ffth_status ffth_green_apply_noalloc(const int32_t n[3], double lambda0, double 
   d.lam0 = lambda0;
   d.mu0 = mu0;
   d.gam_h = 0.5 / mu0;
-  d.gam_c = (lambda0 + mu0) / (mu0 * (lambda0 + 2.0 * mu0));
+  d.gam_r = (lambda0 + mu0) / (lambda0 + 2.0 * mu0);
   d.inv_nvox = 1.0 / (double)nvox;
   d.tau_scale = 1.0;
   d.op_scale = 1.0 / (double)nvox;

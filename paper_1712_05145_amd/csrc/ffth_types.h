@@ -74,7 +74,7 @@ struct Desc {
   SolverState* st;         // gating state
   SolverState* st2;        // secondary state (outer -> inner set-up)
   double lam0, mu0;        // reference medium of this entry's problem
-  double gam_h, gam_c;     // Green operator: 1 / (2 mu0), (lam0 + mu0) / (mu0 (lam0 + 2 mu0))
+  double gam_h, gam_r;     // Green operator: 1 / (2 mu0), (lam0 + mu0) / (lam0 + 2 mu0)
   double E[6];             // macroscopic strain, tensor components
   double G[18];            // order-1 gradient load G[J*3 + j]
   double H[54];            // order-2 load H[J*9 + j*3 + m] = d^2 E_J / dY_j dY_m

@@ -266,7 +266,11 @@ ffth_status ffth_tile_variants(ffth_plan *plan, int32_t out[8]);
 /* Pin the tile variants (same layout; each in [0, 6): 0..3 tile shapes with
  * the default radix order, 4 and 5 the default tile with the radix orders
  * 4-2-3-5-8-16 and 8-4-2-3-5-16); results of every variant agree to
- * rounding.  A plan with pinned variants runs the five classical passes.
+ * rounding.  A precision with a variant other than 0 runs the classical passes
+ * with these tiles; with all of its variants 0 it runs the passes the plan was
+ * created with (grouped where the grid has them).  A 2-D grid keeps its single
+ * spectral pass, in the z variant's shape, unless a y variant is not 0.  So
+ * writing back what ffth_tile_variants returned changes nothing.
  * INVALID for a value out of range. */
 ffth_status ffth_set_tile_variants(ffth_plan *plan, const int32_t in[8]);
 /* Loads per launch of the iteration passes, out[prec] (0 = FP32, 1 = FP64):

@@ -285,12 +285,20 @@ struct ffth_plan {
 
 namespace {
 
-// Passes of the plan.  Grouped where the grid allows it (group_shape), in
-// each precision by itself; 2-D grids take the one-pass spectral step.  Pinned
-// tile shapes are those of the classical passes, which such a plan then runs.
-void set_passes(ffth_plan* P, bool pinned) {
-  for (int pi = 0; pi < 2; ++pi) P->grp[pi] = pinned ? GroupShape{} : group_shape(P->n, pi == 1);
-  P->plane = !pinned && P->n[0] == 1;
+enum Pass { PS_XF = 0, PS_Y = 1, PS_Z = 2, PS_XI = 3 };
+
+// Passes of the plan, from its tile variants.  Grouped where the grid allows
+// it (group_shape) and every variant of the precision is 0, in each precision
+// by itself; 2-D grids take the one-pass spectral step while no y-pass shape is
+// asked for.  Variants that are not 0 are shapes of the classical passes.  So
+// the variants that a plan reports always stand for the passes that it runs.
+void set_passes(ffth_plan* P) {
+  for (int pi = 0; pi < 2; ++pi) {
+    bool pinned = false;
+    for (int pass = 0; pass < 4; ++pass) pinned = pinned || P->var[pass][pi] != 0;
+    P->grp[pi] = pinned ? GroupShape{} : group_shape(P->n, pi == 1);
+  }
+  P->plane = P->n[0] == 1 && P->var[PS_Y][0] == 0 && P->var[PS_Y][1] == 0;
 }
 
 void set_blocks(ffth_plan* P) {
@@ -464,7 +472,6 @@ ffth_status read_states(ffth_plan* P) {
 
 // ---- pass launchers -------------------------------------------------------
 
-enum Pass { PS_XF = 0, PS_Y = 1, PS_Z = 2, PS_XI = 3 };
 template <typename T> int pv(ffth_plan* P, Pass ps) { return P->var[ps][sizeof(T) == 8 ? 1 : 0]; }
 
 template <typename T> int xblocks(ffth_plan* P) { return sizeof(T) == 8 ? P->nx64 : P->nx32; }
@@ -1678,7 +1685,7 @@ ffth_status plan_create(ffth_plan** out, const ffth_problem* p, const ffth_opts*
   P->d_desc = (Desc*)(P->ws + L.desc);
   P->d_state = (SolverState*)(P->ws + L.state);
   P->d_cdesc = (Desc*)(P->ws + L.cdesc);
-  set_passes(P, false);
+  set_passes(P);
   set_blocks(P);
   P->hpool = pool;
   if (!alloc_host_bufs(P)) {
@@ -2051,7 +2058,7 @@ ffth_status ffth_set_tile_variants(ffth_plan* P, const int32_t in[8]) {
     }
   }
   for (int i = 0; i < 8; ++i) P->var[i / 2][i % 2] = in[i];
-  set_passes(P, true);
+  set_passes(P);
   set_blocks(P);
   return FFTH_OK;
 }

@@ -386,7 +386,8 @@ class Solver:
 
     @property
     def tile_variants(self):
-        """Tile variant per pass: [xf32, xf64, y32, y64, z32, z64, xi32, xi64]."""
+        """Tile variant per pass: [xf32, xf64, y32, y64, z32, z64, xi32, xi64];
+        all 0 in a precision: the passes the plan was created with (ffth.h)."""
         return ffth_tile_variants(self.plan)
 
     @tile_variants.setter

@@ -1033,7 +1033,8 @@ template <typename T> ffth_status run_cg3(ffth_plan* P, int nl) {
 //   PROJ  split r with P = Gamma0 C0: compatible part -> FP32 inner right-hand
 //         side, the rest (minus the incompatible round-off of x) applied to x
 //   INNER up to check_every FP32 CG / Basic Scheme iterations
-// Outer states sit in slots [0, nl), inner states in [nl, 2nl) of each plan.
+// The states of load l sit in slots l (outer) and nloads + l (inner) of its
+// plan, which may hold more loads than the job solves.
 enum Phase { PH_A0 = 0, PH_A, PH_PROJ, PH_INNER, PH_DONE };
 
 struct Job {
@@ -1145,7 +1146,7 @@ ffth_status group_issue(std::vector<Job*>& jobs, Stage& st, int* kin_out, InnerS
   for (int pass = 0; pass < 2; ++pass) {
     for (Job* J : jobs) {
       if (J->phase != PH_INNER || J->fresh != (pass == 0)) continue;
-      cnt[3] += stage_append(st, *J, R_INNER, J->nl);
+      cnt[3] += stage_append(st, *J, R_INNER, J->P->nloads);
       if (pass == 0) nFresh = cnt[3];
       kin = std::min(kin, std::max(1, o.max_iter - J->inner_total));
     }
@@ -1170,7 +1171,7 @@ ffth_status group_issue(std::vector<Job*>& jobs, Stage& st, int* kin_out, InnerS
     for (Job* J : jobs) {
       if (J->phase != PH_A) continue;
       for (int l = 0; l < J->nl; ++l)
-        if (J->P->h_state[J->nl + l].xpend) {
+        if (J->P->h_state[J->P->nloads + l].xpend) {
           if (st.cursor >= st.cap) {
             g_last_error = "descriptor staging area too small for the round";
             return FFTH_ERR_INVALID;
@@ -1246,7 +1247,7 @@ ffth_status group_advance(std::vector<Job*>& jobs, int kin) {
       case PH_INNER:
         J->inner_total += kin;
         if (J->inner_total >= o.max_iter) J->last = true;
-        if (!any_active(P, J->nl, J->nl) || J->last) J->phase = PH_A;
+        if (!any_active(P, P->nloads, J->nl) || J->last) J->phase = PH_A;
         break;
     }
   }

@@ -1567,6 +1567,51 @@ template <typename T> constexpr bool gz_fits(int n0, int r2) {
   return gz_elems<T>(n0, r2) * 2 * (int)sizeof(T) <= group_lds<T>();
 }
 
+// axis lengths of the grouped passes
+#define FFTH_GROUP_N(X) X(8) X(12) X(16) X(24) X(32) X(48) X(64) X(96) X(128) X(256)
+#define FFTH_GROUP_ITEM(N) N,
+constexpr int GROUP_SIZES[] = {FFTH_GROUP_N(FFTH_GROUP_ITEM)};
+#undef FFTH_GROUP_ITEM
+constexpr bool group_size(int n) {
+  for (int m : GROUP_SIZES)
+    if (m == n) return true;
+  return false;
+}
+
+// Lengths of the multi-size launches (below).
+constexpr int MULTI_SIZES[] = {16, 24, 32, 48, 64, 96, 128};   // the lengths of FFTH_MULTI_SIZES
+constexpr bool multi_size(int n) {
+  for (int m : MULTI_SIZES)
+    if (m == n) return true;
+  return false;
+}
+
+// The rule: R2 of a grid's grouped passes, 0 where it runs the classical ones.
+// (grids of the multi-size launches are grouped in FP32, whatever their axis 2)
+template <typename T> constexpr int group_pick(int n0, int n1, int n2) {
+  if (!group_size(n0) || !group_size(n1) || !group_size(n2)) return 0;
+  const bool multi = sizeof(T) == 4 && multi_size(n0) && multi_size(n1) && multi_size(n2);
+  for (int r2 : {group_r2<T>(n1), group_r2b<T>(n1)}) {
+    if (r2 == 0 || !gx_fits<T>(n2, n1 / r2) || !gz_fits<T>(n0, r2)) continue;
+    if (multi || group_pays(n1 / r2, n2, (long)n0 * n1 * n2)) return r2;
+  }
+  return 0;
+}
+// Whether a grid takes an x-pass of (n2, R1), a z-pass of (n0, R2): the others
+// are not compiled.
+template <typename T> constexpr bool gx_used(int n2, int r1) {
+  for (int n0 : GROUP_SIZES)
+    for (int n1 : GROUP_SIZES)
+      if (n1 % r1 == 0 && group_pick<T>(n0, n1, n2) * r1 == n1) return true;
+  return false;
+}
+template <typename T> constexpr bool gz_used(int n0, int r2) {
+  for (int n1 : GROUP_SIZES)
+    for (int n2 : GROUP_SIZES)
+      if (group_pick<T>(n0, n1, n2) == r2) return true;
+  return false;
+}
+
 // ---------------------------------------------------------------------------
 // Multi-size launches of the FP32 inner iteration: one launch per grouped
 // pass covers loads of grids of different sizes (axis lengths from
@@ -1578,12 +1623,6 @@ template <typename T> constexpr bool gz_fits(int n0, int r2) {
 // ---------------------------------------------------------------------------
 #define FFTH_MULTI_SIZES(X) X(16) X(24) X(32) X(48) X(64) X(96) X(128)
 constexpr int MULTI_NT = 256;
-constexpr int MULTI_SIZES[] = {16, 24, 32, 48, 64, 96, 128};   // the lengths of FFTH_MULTI_SIZES
-constexpr bool multi_size(int n) {
-  for (int m : MULTI_SIZES)
-    if (m == n) return true;
-  return false;
-}
 #define FFTH_MULTI_CHECK(N) static_assert(multi_size(N) && group_r2<float>(N) >= 6 && gz_fits<float>(N, 8) && gx_fits<float>(N, 16), "multi-size lengths are grouped");
 FFTH_MULTI_SIZES(FFTH_MULTI_CHECK)
 #undef FFTH_MULTI_CHECK

@@ -8,73 +8,59 @@
 #error "compile with -DFFTH_REAL=float|double and -DFFTH_PART=0..4"
 #endif
 
-// axis lengths of the grouped passes
-#define FFTH_GROUP_N(X) X(8) X(12) X(16) X(24) X(32) X(48) X(64) X(96) X(128) X(256)
-
 namespace ffth {
 
 using R = FFTH_REAL;
 constexpr bool DBL = sizeof(R) == 8;
 
 #if FFTH_PART == 0
-template <int N, int R2> static void gz_r(dim3 grid, bool h16, hipStream_t s, const Desc* d, int op, int n1,
+template <int N, int R2> static bool gz_r(dim3 grid, bool h16, hipStream_t s, const Desc* d, int op, int n1,
                                           double scale, int kcs, int fin, int nblk_f, int nblk_i) {
-  if constexpr (gz_fits<R>(N, R2)) {
+  if constexpr (gz_used<R>(N, R2)) {
     if constexpr (!DBL) {
       if (h16) {
         hipLaunchKernelGGL((k_gz<R, N, R2, NT, H2>), grid, dim3(NT), 0, s, d, op, n1, scale, kcs, fin, nblk_f, nblk_i);
-        return;
+        return true;
       }
     }
     hipLaunchKernelGGL((k_gz<R, N, R2, NT, C2<R>>), grid, dim3(NT), 0, s, d, op, n1, scale, kcs, fin, nblk_f, nblk_i);
+    return true;
   }
+  return false;
 }
 template <> hipError_t GLaunch<R>::gz(int n0, const GroupShape& g, bool h16, int nb, hipStream_t s, const Desc* d,
                                       int op, int n1, double scale, int fin, int nblk_f, int nblk_i) {
   const dim3 grid(g.zblocks + (fin >= 0 ? 1 : 0), nb);
+  bool ok = false;   // stays so where no kernel is compiled for (n0, R2)
   switch (n0) {
-#define FFTH_CASE(N)                                                                                  \
-  case N:                                                                                             \
-    if (g.r2 == 4) gz_r<N, 4>(grid, h16, s, d, op, n1, scale, g.kcs, fin, nblk_f, nblk_i);           \
-    if (g.r2 == 8) gz_r<N, 8>(grid, h16, s, d, op, n1, scale, g.kcs, fin, nblk_f, nblk_i);           \
-    if (g.r2 == 16) gz_r<N, 16>(grid, h16, s, d, op, n1, scale, g.kcs, fin, nblk_f, nblk_i);         \
-    if constexpr (DBL) {                                                                              \
-      if (g.r2 == 2) gz_r<N, 2>(grid, h16, s, d, op, n1, scale, g.kcs, fin, nblk_f, nblk_i);         \
-    } else {                                                                                          \
-      if (g.r2 == 6) gz_r<N, 6>(grid, h16, s, d, op, n1, scale, g.kcs, fin, nblk_f, nblk_i);         \
-    }                                                                                                 \
-    return hipGetLastError();
+#define FFTH_CASE(N)                                                                                     \
+  case N:                                                                                                \
+    if (g.r2 == 4) ok = gz_r<N, 4>(grid, h16, s, d, op, n1, scale, g.kcs, fin, nblk_f, nblk_i);         \
+    if (g.r2 == 8) ok = gz_r<N, 8>(grid, h16, s, d, op, n1, scale, g.kcs, fin, nblk_f, nblk_i);         \
+    if (g.r2 == 16) ok = gz_r<N, 16>(grid, h16, s, d, op, n1, scale, g.kcs, fin, nblk_f, nblk_i);       \
+    if constexpr (DBL) {                                                                                 \
+      if (g.r2 == 2) ok = gz_r<N, 2>(grid, h16, s, d, op, n1, scale, g.kcs, fin, nblk_f, nblk_i);       \
+    } else {                                                                                             \
+      if (g.r2 == 6) ok = gz_r<N, 6>(grid, h16, s, d, op, n1, scale, g.kcs, fin, nblk_f, nblk_i);       \
+    }                                                                                                    \
+    break;
     FFTH_GROUP_N(FFTH_CASE)
 #undef FFTH_CASE
   }
-  return hipErrorInvalidValue;
+  return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 #ifdef FFTH_GROUP_RULE   // defined for one of the two precisions
-static bool compiled(int n) {
-#define FFTH_CASE(N) if (n == N) return true;
-  FFTH_GROUP_N(FFTH_CASE)
-#undef FFTH_CASE
-  return false;
-}
 template <typename T> static GroupShape shape_of(const int n[3]) {
   GroupShape g;
-  if (!compiled(n[0]) || !compiled(n[1]) || !compiled(n[2])) return g;
-  for (int r2 : {group_r2<T>(n[1]), group_r2b<T>(n[1])}) {
-    const int r1 = r2 > 0 ? n[1] / r2 : 0;
-    if (r2 == 0 || !gx_fits<T>(n[2], r1) || !gz_fits<T>(n[0], r2)) continue;
-    // (grids of the multi-size launches are grouped in FP32, whatever their axis 2)
-    const bool multi = sizeof(T) == 4 && multi_size(n[0]) && multi_size(n[1]) && multi_size(n[2]);
-    if (!multi && !group_pays(r1, n[2], (long)n[0] * n[1] * n[2])) continue;
-    const int grp = group_count(n[2], r1);
-    g.on = true;
-    g.r1 = r1;
-    g.r2 = r2;
-    g.kcs = group_kcs(r2, n[2] / 2);
-    g.xblocks = (n[0] * r2 + grp - 1) / grp;
-    g.zblocks = n[2] / 2 / gz_kc<T>(n[0], r2) * r1;
-    return g;
-  }
+  g.r2 = group_pick<T>(n[0], n[1], n[2]);
+  if (g.r2 == 0) return GroupShape{};
+  g.on = true;
+  g.r1 = n[1] / g.r2;
+  const int grp = group_count(n[2], g.r1);
+  g.kcs = group_kcs(g.r2, n[2] / 2);
+  g.xblocks = (n[0] * g.r2 + grp - 1) / grp;
+  g.zblocks = n[2] / 2 / gz_kc<T>(n[0], g.r2) * g.r1;
   return g;
 }
 GroupShape group_shape(const int n[3], bool dbl) { return dbl ? shape_of<double>(n) : shape_of<float>(n); }
@@ -85,9 +71,9 @@ GroupShape group_shape(const int n[3], bool dbl) { return dbl ? shape_of<double>
 template <int N> struct IC { static constexpr int v = N; };
 template <int N, class F> static bool for_r1(int r1, F&& f) {
   switch (r1) {
-#define FFTH_R1(K) case K: if constexpr (gx_fits<R>(N, K)) { f(IC<N>(), IC<K>()); return true; } break;
-#define FFTH_R1F(K) case K: if constexpr (!DBL && gx_fits<R>(N, K)) { f(IC<N>(), IC<K>()); return true; } break;
-#define FFTH_R1D(K) case K: if constexpr (DBL && gx_fits<R>(N, K)) { f(IC<N>(), IC<K>()); return true; } break;
+#define FFTH_R1(K) case K: if constexpr (gx_used<R>(N, K)) { f(IC<N>(), IC<K>()); return true; } break;
+#define FFTH_R1F(K) case K: if constexpr (!DBL && gx_used<R>(N, K)) { f(IC<N>(), IC<K>()); return true; } break;
+#define FFTH_R1D(K) case K: if constexpr (DBL && gx_used<R>(N, K)) { f(IC<N>(), IC<K>()); return true; } break;
     FFTH_R1(2) FFTH_R1(4) FFTH_R1(8) FFTH_R1(16)
     FFTH_R1D(3) FFTH_R1D(6) FFTH_R1D(12) FFTH_R1F(32)
 #undef FFTH_R1

@@ -337,6 +337,8 @@ __device__ __forceinline__ void fft_stage(C2<T>* buf, const C2<T>* tw) {
   constexpr int R = fac_radix(N, S, PLAN);
   constexpr int NS = fac_prefix(N, S, PLAN);
   constexpr int NB = N / R;
+  // a half table (powers of two) serves radices that read w^r for r <= R / 2 only
+  static_assert(tw_len(N) == N || R == 2 || R == 4 || R == 8 || R == 16, "stage reads past the half twiddle table");
   constexpr int NG = NFFT / V;
   constexpr int ITEMS = NG * NB;
   constexpr int K = (ITEMS + NT - 1) / NT;

@@ -872,7 +872,7 @@ __global__ __launch_bounds__(NT) void k_field_inv(const Desc* __restrict__ descs
 // that stops after an even iteration forms its last x in k_cg3_finish.
 // ---------------------------------------------------------------------------
 // Row block b of nblk (its partial sums go to slot k at part_i + k nblk + b);
-// z: ROWS * 3 * (N2 + N2/16) LDS elements, tw: N2, tw1: ROWS (R1 > 1).
+// z: ROWS * 3 * (N2 + N2/16) LDS elements, tw: tw_len(N2), tw1: ROWS (R1 > 1).
 template <typename T, int N2, bool ISO, int ROWS, int NTB, typename S, int PLAN, int R1 = 1>
 __device__ __forceinline__ void xcg3_tile(const Desc& d, int b, int nblk, long rows_total, long nvox, C2<T>* z,
                                           C2<T>* tw, C2<T>* tw1 = nullptr, int r2 = 1, int kcs = 0) {
@@ -1123,7 +1123,7 @@ __device__ __forceinline__ void ypass_body(S* base, int ncols, int c0, C2<T>* bu
 }
 
 // Tile bid (plane i0 = bid / ntiles, columns from (bid % ntiles) CW) of one
-// load; buf: N1 * CW LDS elements (16-byte aligned), tw: N1.
+// load; buf: N1 * CW LDS elements (16-byte aligned), tw: tw_len(N1).
 template <typename T, int N1, int CW, int NTB, int V, typename S, int PLAN>
 __device__ __forceinline__ void ypass_tile(const Desc& d, int bid, int dir, int ncols, int ntiles, C2<T>* buf,
                                            C2<T>* tw) {
@@ -1240,7 +1240,7 @@ __device__ __forceinline__ void spectral_op(int op, T (&in)[6][2], T (&out)[6][2
 }
 
 // Tile bid (chunk bid / bpc, columns from (bid % bpc) TK) of one load; buf:
-// N0 * 6 TK LDS elements, tw: N0.
+// N0 * 6 TK LDS elements, tw: tw_len(N0).
 // plane: a 2-D grid (axis 0 of length 1).  N0 is then the length of axis 1 (n1
 // is passed as 1), so this pass replaces both y-passes and the z-pass.
 template <typename T, int N0, int TK, int NTB, typename S, int PLAN>
@@ -1513,7 +1513,7 @@ __device__ __forceinline__ void gz_tile(const Desc& d, int bid, int op, int n1, 
   }
 }
 
-// LDS elements of the tile
+// LDS elements of the tile (tw besides: tw_len(N0))
 template <typename T> constexpr int gz_elems(int n0, int r2) { return n0 * (gz_kc<T>(n0, r2) * r2 * 6 + 1); }
 
 template <typename T, int N0, int R2, int NTB, typename S>

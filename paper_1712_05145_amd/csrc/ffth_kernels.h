@@ -96,12 +96,13 @@ template <typename T> constexpr int y_cols_v(int n, int v) {
   return c;
 }
 template <typename T> constexpr int x_threads_v(int, int v) { return v == 3 ? 64 : NT; }
-// (FP64 from 512 points on: 512 threads with every shape; its one-column tile
-// takes 48 KB or more, so few blocks share a CU.  One column, 256 -> 512
-// threads: 512^3 3.90 -> 3.60 ms, 1024x128x128 783 -> 753 us, planes of 512^2
-// 12.9 -> 12.1 and, three fields, 1024^2 124 -> 113 us)
+// (FP64 from 512 points on: 512 threads with the default shape as well; its
+// one-column tile takes 48 KB or more, so few blocks share a CU.  One column,
+// 256 -> 512 threads: 512^3 3.90 -> 3.60 ms, 1024x128x128 783 -> 753 us, planes
+// of 512^2 12.9 -> 12.1 and, three fields, 1024^2 124 -> 113 us.  Variant 1 keeps
+// 256 threads: two columns at 512 points, one at 1024)
 template <typename T> constexpr int z_threads_v(int n, int v) {
-  return v == 2 || v == 3 || (sizeof(T) == 8 && n >= 512) ? 512 : NT;
+  return v == 2 || v == 3 || (v != 1 && sizeof(T) == 8 && n >= 512) ? 512 : NT;
 }
 // variants 4 and 5: the default tile shape (variant 0) with radix plans 1 and 2
 constexpr int plan_of(int v) { return v >= 4 ? v - 3 : 0; }

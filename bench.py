@@ -53,13 +53,28 @@ ALG_CATEGORIES = ("ypass_f32", "zpass_f32", "xcg3_f32", "cg3start_f32")
 XCG3_START_SAVING = 120.0
 
 
-def alg_bytes_per_voxel(h16):
+def alg_bytes_per_voxel(h16, grouped=False):
     """Bytes per voxel of (forward y, inverse y, z, fused CG pass averaged over
-    an even and an odd iteration, start pass) in the inner solve; projection
-    passes move 48 B in each y- and z-pass."""
+    an even and an odd iteration, start pass) in the inner solve, and of the y-
+    and z-passes of a projection ("proj_y" both directions, "proj_z").  grouped:
+    the grid runs grouped passes, which have no y-passes; the others move the
+    same bytes."""
+    ab = {"yf": 48.0, "yi": 48.0, "z": 48.0, "xcg3": 170.0, "start": 50.0}
     if h16:
-        return {"yf": 24.0, "yi": 48.0, "z": 36.0, "xcg3": 158.0, "start": 38.0}
-    return {"yf": 48.0, "yi": 48.0, "z": 48.0, "xcg3": 170.0, "start": 50.0}
+        ab = {"yf": 24.0, "yi": 48.0, "z": 36.0, "xcg3": 158.0, "start": 38.0}
+    ab.update(proj_y=96.0, proj_z=48.0)
+    if grouped:
+        ab.update(yf=0.0, yi=0.0, proj_y=0.0)
+    return ab
+
+
+def inner_models(ab, nvox, inner, proj, starts):
+    """Algorithmic bytes of the FP32 categories over one run: `inner` iterations,
+    `proj` projections and `starts` inner solves of all loads."""
+    return {"ypass_f32": nvox * (inner * (ab["yf"] + ab["yi"]) + proj * ab["proj_y"]),
+            "zpass_f32": nvox * (inner * ab["z"] + proj * ab["proj_z"]),
+            "xcg3_f32": nvox * (inner * ab["xcg3"] - XCG3_START_SAVING * starts),
+            "cg3start_f32": nvox * ab["start"] * starts}
 
 
 # FP64 words are 8 B: a 6-component FP64 field or FP64 half spectrum is 48 B
@@ -74,9 +89,10 @@ BYTES = {
     # FP64 residual sweep of the defect correction (x-forward, mode LS): the
     # first sweep reads ids and writes the spectrum (the iterate is zero and
     # not read); later sweeps also read the iterate and the FP32 correction
-    # and write the iterate back; order 1 also reads the stored
-    # right-hand-side polarization
-    "sweep0_xf": IDB + F64, "sweep_xf": IDB + F64 + F32W + F64 + F64, "rhs_P": F64,
+    # and write the iterate back (the second one does not read it: it is still
+    # zero); order 1 also reads the stored right-hand-side polarization
+    "sweep0_xf": IDB + F64, "sweep1_xf": IDB + F32W + F64 + F64, "sweep_xf": IDB + F64 + F32W + F64 + F64,
+    "rhs_P": F64,
     # its x-inverse (mode RESID): spectrum and iterate read, residual written
     # (the first sweep reads no iterate and writes an FP32 residual, which
     # goes straight to the inner solve)
@@ -88,10 +104,13 @@ BYTES = {
     # plain two-term CG (FP64): x-forward reads r, p, ids, writes p, spectrum;
     # x-inverse reads spectrum, p, x, r, writes x, r
     "cg_xf": F64 + F64 + IDB + F64 + F64, "cg_xi": F64 + 3 * F64 + 2 * F64,
-    # its two start applications: b (iterate zero: read, ids; spectrum
-    # written; x-inverse: spectrum and x read, x written) and r_0 = b - A b
-    # (x-forward the same; x-inverse: spectrum, x read, r written)
-    "ls_xf": IDB + F64 + F64, "bs_xi": F64 + F64 + F64, "resid_xi": F64 + F64 + F64,
+    # its two start applications: b (iterate zero, not read: ids read, spectrum
+    # written; x-inverse: spectrum read, x written) and r_0 = b - A b
+    # (x-forward reads x and ids; x-inverse: spectrum, x read, r written)
+    "first_xf": IDB + F64, "first_xi": F64 + F64, "ls_xf": IDB + F64 + F64, "resid_xi": F64 + F64 + F64,
+    # field passes (an FP64 field in or out, no phase ids): displacement of a
+    # strain (6 components in, 3 out) and theta of g (3 in, 6 accumulated)
+    "disp_xf": F64 + F64, "disp_xi": F64 + 24.0, "theta_xf": 24.0 + F64, "theta_xi": F64 + F64 + F64,
     # three-term CG in FP64: fused pass (spectrum, r_k, r_k-1, ids read; r_k+1
     # and the spectrum written; the x pair read and written on odd iterations,
     # 2 x 48 B a voxel on average), start pass, and per started solve the
@@ -321,11 +340,8 @@ def fibres_run(dev, n):
     inner = sum(r["iters"] for r in res)
     proj = sum(r["projections"] for r in res)
     f64 = sum(r["fp64_applications"] for r in res)
-    ab = alg_bytes_per_voxel(False)
-    starts = prof["cg3start_f32"][2]
-    model = {"xcg3_f32": nvox * (inner * ab["xcg3"] - XCG3_START_SAVING * starts),
-             "ypass_f32": nvox * (inner * (ab["yf"] + ab["yi"]) + proj * 96.0),
-             "zpass_f32": nvox * (inner * ab["z"] + proj * 48.0), "cg3start_f32": nvox * ab["start"] * starts}
+    ab = alg_bytes_per_voxel(False, grouped=prof["ypass_f32"][0] == 0)
+    model = inner_models(ab, nvox, inner, proj, prof["cg3start_f32"][2])
     model.update(mixed_fp64_models([res], nvox))
     ceff = np.array([r["mean_stress"] for r in r0]).T
     out = {"workload": f"fibres{n}-order0x6+order1", "grid": [n] * 3, "stiffness_contrast":
@@ -423,25 +439,23 @@ def fp64_models(results, nvox, scheme, order1_index=6):
     """Algorithmic bytes of the FP64 categories over one run of FP64 steps
     (`results`: the per-load result records of every step).  Each step also
     builds the order-1 right-hand side: six displacement transforms of the
-    order-0 correctors (x-forward copy 98, x-inverse 3 components 72) and
-    the theta transform of g (x-forward 3 components 74, x-inverse accumulate
-    144), one FP64 application each."""
+    order-0 correctors and the theta transform of g, one FP64 application each."""
     B = BYTES
     xf = xi = 0.0
     apps = 0
     for rs in results:
-        xf += 6 * 98.0 + (IDB + 24.0 + F64)
-        xi += 6 * (F64 + 24.0) + (F64 + F64 + F64)
+        xf += 6 * B["disp_xf"] + B["theta_xf"]
+        xi += 6 * B["disp_xi"] + B["theta_xi"]
         apps += 7
         for l, r in enumerate(rs):
             p_read = B["rhs_P"] if l == order1_index else 0.0
             it = r["iters"]
             if scheme == "cg":
-                xf += it * B["cg_xf"] + 2 * (B["ls_xf"] + p_read)
-                xi += it * B["cg_xi"] + B["bs_xi"] + B["resid_xi"]
+                xf += it * B["cg_xf"] + B["first_xf"] + B["ls_xf"] + 2 * p_read
+                xi += it * B["cg_xi"] + B["first_xi"] + B["resid_xi"]
             elif scheme == "cg3":
-                xf += B["ls_xf"] + p_read
-                xi += B["bs_xi"]
+                xf += B["first_xf"] + p_read
+                xi += B["first_xi"]
             apps += r["fp64_applications"]
     # two y-passes (forward, inverse) and one z-pass per application
     m = {"ypass_f64": nvox * apps * 2 * B["y64"], "zpass_f64": nvox * apps * B["z64"]}
@@ -459,19 +473,21 @@ def fp64_models(results, nvox, scheme, order1_index=6):
 def mixed_fp64_models(results, nvox, order1_index=6):
     """Algorithmic bytes of the FP64 sweeps and FP32 projections of the mixed
     runs: per load the first sweep of a solve (x = 0), the later sweeps (with
-    the FP32 correction), the order-1 load's reads of its stored right-hand
-    side, and the order-1 right-hand-side transforms (see fp64_models)."""
+    the FP32 correction; the second reads no iterate), the order-1 load's reads
+    of its stored right-hand side, and the order-1 right-hand-side transforms (see fp64_models)."""
     B = BYTES
     xf = xi = 0.0
     apps = proj = 0
     for rs in results:
-        xf += 6 * 98.0 + (IDB + 24.0 + F64)
-        xi += 6 * (F64 + 24.0) + (F64 + F64 + F64)
+        xf += 6 * B["disp_xf"] + B["theta_xf"]
+        xi += 6 * B["disp_xi"] + B["theta_xi"]
         apps += 7
         for l, r in enumerate(rs):
             sw = r["fp64_applications"]
             later = max(sw - 1, 0)
             xf += B["sweep0_xf"] + later * B["sweep_xf"] + (sw * B["rhs_P"] if l == order1_index else 0.0)
+            if later > 0:
+                xf += B["sweep1_xf"] - B["sweep_xf"]
             xi += B["sweep0_xi"] + later * B["sweep_xi"]
             apps += sw
             proj += r["projections"]
@@ -621,22 +637,14 @@ def main():
     starts = prof["cg3start_f32"][2]
     real_units = {"xcg3_f32": inner, "ypass_f32": 2 * (inner + proj), "zpass_f32": inner + proj}
     prof = {k: (v[0], v[1], real_units.get(k, v[2])) for k, v in prof.items()}
-    ab = alg_bytes_per_voxel(h16)
-
-    def alg_bytes(c, u):
-        if c == "ypass_f32":
-            return nvox * (inner * (ab["yf"] + ab["yi"]) + proj * 96.0)
-        if c == "zpass_f32":
-            return nvox * (inner * ab["z"] + proj * 48.0)
-        if c == "xcg3_f32":
-            return nvox * (inner * ab["xcg3"] - XCG3_START_SAVING * starts)
-        return nvox * ab["start"] * u
+    # no y-pass launched: the grid runs grouped passes
+    ab = alg_bytes_per_voxel(h16, grouped=prof["ypass_f32"][0] == 0)
+    model = inner_models(ab, nvox, inner, proj, starts)
 
     cat = max(ALG_CATEGORIES, key=lambda c: prof[c][1])
     launches, tot_ms, units = prof[cat]
-    bytes_total = alg_bytes(cat, units)
+    bytes_total = model[cat]
     achieved = bytes_total / (tot_ms * 1e-3) / 1e9 if tot_ms > 0 else 0.0
-    model = {c: alg_bytes(c, prof[c][2]) for c in ALG_CATEGORIES}
     model.update(mixed_fp64_models(results, nvox))
     kernels = kernel_table(prof, nvox, model)
     for c in ALG_CATEGORIES:
@@ -656,9 +664,9 @@ def main():
                 "avg_launch_ms": round(tot_ms / max(launches, 1), 4),
                 "copy_GBs": round(copy_gbs, 1), "frac_of_copy": round(achieved / copy_gbs, 4)}
 
-    # one FP32 inner iteration of one load over its four passes (fused CG pass,
-    # forward y, z with the Green operator, inverse y): algorithmic bytes per
-    # voxel and the per-load times of the same timed steps
+    # one FP32 inner iteration of one load over its passes (fused CG pass, z with
+    # the Green operator, forward and inverse y where there are any): algorithmic
+    # bytes per voxel and the per-load times of the same timed steps
     it_ms = {c: prof[c][1] / max(prof[c][2], 1) for c in ("xcg3_f32", "ypass_f32", "zpass_f32")}
     it_ms_total = it_ms["xcg3_f32"] + 2 * it_ms["ypass_f32"] + it_ms["zpass_f32"]
     it_bpv = ab["xcg3"] + ab["yf"] + ab["yi"] + ab["z"]

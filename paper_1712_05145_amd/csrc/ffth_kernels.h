@@ -763,7 +763,7 @@ __global__ __launch_bounds__(NTB) void k_xinv(const Desc* __restrict__ descs, in
 // descriptor in the launch arguments (no setup launch) an operator call takes,
 // before -> now: 16^3 19.6 -> 15.6 us, 48x96x24 47.6 -> 41.0 us; the forward
 // pass of 512^3 3.1 -> 2.4 ms (5.4 TB/s), the inverse 3.6 -> 2.6 (5.0 TB/s);
-// two order-2 right-hand sides of 64^3 725 -> 683 us.
+// the order-2 right-hand side of 64^3 725 -> 683 us.
 // ---------------------------------------------------------------------------
 template <typename T, int N2, int ROWS, int R1>
 __device__ __forceinline__ void field_fwd_tile(const Desc& d, int bid, long rows_total, long nvox, int r2, int kcs,
@@ -1406,9 +1406,12 @@ __global__ __launch_bounds__(NTB) void k_zpass(const Desc* __restrict__ descs, i
 // q, every b and i0; a row of the tile, [b][k2][6], is contiguous.  Rows are
 // an odd number of elements apart (WP): the passes along a column and the
 // operator's threads then spread over the banks.
-// Bound by vector instructions and LDS traffic more than by memory (128^3, FP32,
-// launches of 2.9 loads on average: 74 us, two y-passes and a z-pass before 139;
-// the fused pass rose from 164 to 189).
+// Bound by vector instructions more than by memory: 128^3, six loads, binary16
+// in, 151 MB read and 302 MB written in 150 us (3.0 TB/s; 77 us at the rate of
+// an in-place stream), in which the SIMDs issue vector instructions for 101 us
+// and LDS instructions for 29 us (bank conflicts 8 us).  FP32, launches of 2.9
+// loads on average: 74 us, two y-passes and a z-pass before 139; the fused pass
+// rose from 164 to 189.
 // ---------------------------------------------------------------------------
 template <typename T> __host__ __device__ constexpr int gz_kc(int n0, int r2) { return n0 * r2 * 6 * 2 * (int)sizeof(T) <= 16384 ? 2 : 1; }
 
